@@ -142,11 +142,11 @@ ProductWs carve_product(Arena& a, int64_t Nr, int64_t Nc, int64_t D, int b) {
   w.rows = carve_pack(a, Nr, dp, ROW_PAD);
   w.cols = carve_pack(a, Nc, dp, COL_PAD);
   w.vp = a.fspan(size_t(w.cols.npad) * w.plan.ncb * 16);
-  w.vscale = a.fspan(128);
+  w.vscale = a.fspan(VSCALE_FLOATS);
   w.part = a.fspan(part_rows_bound(w.rows.npad, Nc) * w.plan.ncb * 16);
   w.tmp = a.fspan(size_t(Nr));
   w.flag = a.take<int>(1);
-  w.centre = carve_centre(a, Nc);
+  w.centre = carve_centre(a, Nc, Nr);
   return w;
 }
 
@@ -159,14 +159,14 @@ static ProductWs carve_product_exact(Arena& a, int64_t Nr, int64_t Nc, int64_t D
   w.rows = carve_pack(a, Nr, dp, ROW_PAD);
   w.cols = carve_pack(a, Nc, dp, COL_PAD);
   w.vp = a.fspan(size_t(w.cols.npad) * w.plan.ncb * 16);
-  w.vscale = a.fspan(128);
+  w.vscale = a.fspan(VSCALE_FLOATS);
   const KVPlan rp = plan_rowsum(Nr, Nc, dp);
   const size_t part_prod = size_t(w.plan.nsplit) * w.rows.npad * w.plan.ncb * 16;
   const size_t part_row = size_t(rp.nsplit) * w.rows.npad;
   w.part = a.fspan(b == 1 ? part_row : part_prod);
   w.tmp = a.fspan(size_t(Nr));
   w.flag = a.take<int>(1);
-  w.centre = carve_centre(a, Nc);
+  w.centre = carve_centre(a, Nc, Nr);
   return w;
 }
 
@@ -229,21 +229,73 @@ ProductWs product_view(const ProductWs& big, const PointPack& rows, const PointP
   return w;
 }
 
-void product_apply(ProductWs& w, const float* sl, const float* sr, const float* V, int64_t ldv,
-                   int b, float* Y, int64_t ldy, bool diag, hipStream_t stream) {
+// The passes of a product whose points and V are packed.
+static void product_run(ProductWs& w, const float* sl, int b, float* Y, int64_t ldy, bool diag,
+                        const PoisonGate& poison, hipStream_t stream) {
   if (b == 1) {
     // one right-hand side: weighted row sums K (sr v) on the vector ALUs (no
     // matrix-core contraction padded to 16 columns), then the row scale
-    launch_pack_wv(V, ldv, sr, w.cols.n, w.cols.npad, w.vp, stream);
     const KVPlan rp = plan_rowsum(w.rows.n, w.cols.n, w.rows.dp);
     check_span(w.tmp, size_t(w.rows.n), "single-column row sums");
     launch_rowsum(rp, w.rows, w.cols, w.vp, diag, w.tmp.p, w.part, stream);
-    launch_scale_rows(w.tmp.p, sl, w.rows.n, Y, ldy, stream);
+    launch_scale_rows(w.tmp.p, sl, w.rows.n, Y, ldy, poison, stream);
     return;
   }
-  launch_pack_v_for(w.rows, V, w.cols.n, b, ldv, sr, w.plan.ncb, w.cols.npad, w.vp, w.vscale,
-                    stream);
-  launch_product(w.plan, w.rows, w.cols, w.vp, w.vscale, diag, sl, Y, ldy, b, w.part, stream);
+  launch_product(w.plan, w.rows, w.cols, w.vp, w.vscale, diag, sl, Y, ldy, b, w.part, poison,
+                 stream);
+}
+
+void product_apply(ProductWs& w, const float* sl, const float* sr, const float* V, int64_t ldv,
+                   int b, float* Y, int64_t ldy, bool diag, hipStream_t stream) {
+  launch_pack_v_split(V, w.cols.n, b, ldv, sr, b == 1 ? 0 : w.plan.ncb, w.cols.npad, w.vp,
+                      w.vscale, stream);
+  product_run(w, sl, b, Y, ldy, diag, PoisonGate{}, stream);
+}
+
+// One product from raw inputs: prologue, packs, product passes (whose last
+// kernel writes NaN where the call is poisoned).
+static void matmul_run(ProductWs& w, const void* Xr, const void* Xc, int64_t D, int64_t ldx,
+                       fd_dtype xt, double beta, const float* sl, const float* sr, const float* V,
+                       int b, int64_t ldv, float* Y, int64_t ldy, hipStream_t st) {
+  // same base pointer and ldx: index i names the same point in both sets
+  const bool diag = Xr == Xc;
+  PrologueIn pro;
+  // one centre for both sets: the column set's mean, the radius over both
+  pro.X = Xc;
+  pro.xt = xt;
+  pro.n = w.cols.n;
+  pro.D = D;
+  pro.ldx = ldx;
+  if (!diag || w.rows.n > w.cols.n) {
+    pro.X2 = Xr;
+    pro.n2 = w.rows.n;
+  }
+  if (b > 1) {
+    pro.V = V;
+    pro.nv = w.cols.n;
+    pro.b = b;
+    pro.ldv = ldv;
+    pro.sr = sr;
+  }
+  launch_prologue(pro, w.centre, w.vscale, st);
+  PackIn in;
+  in.Xr = Xr;
+  in.Xc = Xc;
+  in.xt = xt;
+  in.D = D;
+  in.ldx = ldx;
+  in.beta = beta;
+  in.flag = w.flag;
+  in.V = V;
+  in.b = b;
+  in.ldv = ldv;
+  in.sr = sr;
+  in.ncb = b == 1 ? 0 : w.plan.ncb;
+  in.vp = w.vp;
+  in.vscale = w.vscale;
+  in.nvmax = vmax_blocks(w.cols.n);
+  launch_packs(in, w.rows, w.cols, w.centre, st);
+  product_run(w, sl, b, Y, ldy, diag, poison_gate(xt, w.centre, beta, w.flag), st);
 }
 
 // ---------------------------------------------------------------- degree
@@ -260,47 +312,85 @@ DegreeWs carve_degree(Arena& a, int64_t N, int64_t D) {
   w.w = a.take<float>(size_t(N));
   w.part = a.fspan(std::max(part_rows_bound(w.rows.npad, N), sym_part_rows(w.rows.npad, SYM_NIB)));
   w.colfix = a.take<unsigned long long>(size_t(w.rows.npad));
+  w.qsum = a.take<double>(2 * size_t(qsum_words(w.rows.npad)));
   w.flag = a.take<int>(1);
   w.centre = carve_centre(a, N);
   return w;
 }
 
-void degree_run(DegreeWs& w, const void* X, fd_dtype xt, int64_t N, int64_t D, int64_t ldx,
-                double beta, double alpha, float* q, float* d, float* s, double* s_off,
-                bool pack, hipStream_t stream) {
-  if (pack) {
-    launch_centre(X, xt, N, D, ldx, w.centre, stream);
-    launch_pack_points(X, xt, N, D, ldx, beta, true, w.rows, &w.centre, stream);
-    launch_pack_points(X, xt, N, D, ldx, beta, false, w.cols, &w.centre, stream);
-  }
+// Row and column packs of one point set at one bandwidth, with the column-sum
+// words of the symmetric passes cleared (sq: the squared kernel's too).
+static void degree_packs(DegreeWs& w, const void* X, fd_dtype xt, int64_t D, int64_t ldx,
+                         double beta, bool sq, int* flag, hipStream_t stream) {
+  PackIn in;
+  in.Xr = in.Xc = X;
+  in.xt = xt;
+  in.D = D;
+  in.ldx = ldx;
+  in.beta = beta;
+  in.flag = flag;
+  in.zero1 = w.colfix;
+  in.zero2 = sq ? w.sq_colfix : nullptr;
+  in.nzero = w.rows.npad;
+  launch_packs(in, w.rows, w.cols, w.centre, stream);
+}
+
+static void degree_prologue(DegreeWs& w, const void* X, fd_dtype xt, int64_t N, int64_t D,
+                            int64_t ldx, hipStream_t stream) {
+  PrologueIn pro;
+  pro.X = X;
+  pro.xt = xt;
+  pro.n = N;
+  pro.D = D;
+  pro.ldx = ldx;
+  launch_prologue(pro, w.centre, FSpan{}, stream);
+}
+
+// The passes of fd_degree on filled packs.
+static void degree_passes(DegreeWs& w, int64_t N, double alpha, float* q, float* d, float* s,
+                          double* s_off, const PoisonGate& poison, hipStream_t stream) {
   float* qq = q != nullptr ? q : w.q;
+  const int64_t nq = qsum_words(w.rows.npad);
   if (rowsum_sym_applies(w.rows, w.cols, true, w.colfix)) {
     // symmetric row sums with the epilogues fused into their reductions; the
     // first reduction leaves the column-sum words zeroed for the second pass
     const SymPass p1 = launch_rowsum_sym_pass(w.plan, w.rows, w.cols, FSpan{}, w.part, w.colfix,
-                                              true, stream);
+                                              stream);
     launch_degree_reduce_q(p1, w.rows, w.cols, w.part, w.colfix, qq, alpha,
-                           alpha == 0.0 ? FSpan{} : w.wp, stream);
-    if (s_off != nullptr) launch_sum_minus_n(qq, N, s_off, stream);
+                           alpha == 0.0 ? FSpan{} : w.wp, w.qsum, poison, stream);
     if (alpha == 0.0) {
-      launch_degree_finish(qq, qq, N, 0.0, d, s, stream);
+      launch_degree_finish(qq, qq, N, 0.0, d, s, w.qsum, nq, s_off, poison, stream);
       return;
     }
     const SymPass p2 = launch_rowsum_sym_pass(w.plan, w.rows, w.cols, w.wp, w.part, w.colfix,
-                                              false, stream);
-    launch_degree_reduce_ds(p2, w.rows, w.part, w.colfix, qq, alpha, d, s, stream);
+                                              stream);
+    launch_degree_reduce_ds(p2, w.rows, w.part, w.colfix, qq, alpha, d, s, w.qsum, s_off, poison,
+                            stream);
     return;
   }
-  launch_rowsum(w.plan, w.rows, w.cols, FSpan{}, true, qq, w.part, stream, w.colfix);
+  launch_rowsum(w.plan, w.rows, w.cols, FSpan{}, true, qq, w.part, stream);
   if (s_off != nullptr) launch_sum_minus_n(qq, N, s_off, stream);
   if (alpha == 0.0) {
-    launch_degree_finish(qq, qq, N, 0.0, d, s, stream);
-    return;
+    launch_degree_finish(qq, qq, N, 0.0, d, s, nullptr, 0, nullptr, poison, stream);
+  } else {
+    launch_pow_neg(qq, N, alpha, w.w, stream);
+    launch_pack_w(w.w, N, w.cols.npad, w.wp, stream);
+    launch_rowsum(w.plan, w.rows, w.cols, w.wp, true, w.t, w.part, stream);
+    launch_degree_finish(qq, w.t, N, alpha, d, s, nullptr, 0, nullptr, poison, stream);
   }
-  launch_pow_neg(qq, N, alpha, w.w, stream);
-  launch_pack_w(w.w, N, w.cols.npad, w.wp, stream);
-  launch_rowsum(w.plan, w.rows, w.cols, w.wp, true, w.t, w.part, stream, w.colfix);
-  launch_degree_finish(qq, w.t, N, alpha, d, s, stream);
+  if (poison.flag != nullptr) {
+    launch_poison(poison.flag, q, N, 1, 1, stream);
+    launch_poison(poison.flag, s_off, 1, stream);
+  }
+}
+
+void degree_run(DegreeWs& w, const void* X, fd_dtype xt, int64_t N, int64_t D, int64_t ldx,
+                double beta, double alpha, float* q, float* d, float* s, double* s_off,
+                bool poison, hipStream_t stream) {
+  degree_prologue(w, X, xt, N, D, ldx, stream);
+  int* flag = poison ? w.flag : nullptr;
+  degree_packs(w, X, xt, D, ldx, beta, false, flag, stream);
+  degree_passes(w, N, alpha, q, d, s, s_off, poison_gate(xt, w.centre, beta, flag), stream);
 }
 
 DegreeWs carve_degree_dyadic(Arena& a, int64_t N, int64_t D) {
@@ -314,44 +404,46 @@ void degree_run_dyadic(DegreeWs& w, const void* X, fd_dtype xt, int64_t N, int64
                        int64_t ldx, double beta0, int nb, double alpha, float* q, float* d,
                        float* s, double* s_off, hipStream_t stream) {
   auto at = [N](float* v, int l) { return v != nullptr ? v + int64_t(l) * N : nullptr; };
+  auto off_at = [s_off](int l) { return s_off != nullptr ? s_off + l : nullptr; };
   auto beta_of = [beta0](int l) { return std::ldexp(beta0, l); };
-  launch_centre(X, xt, N, D, ldx, w.centre, stream);
-  launch_pack_points(X, xt, N, D, ldx, beta_of(0), true, w.rows, &w.centre, stream);
-  launch_pack_points(X, xt, N, D, ldx, beta_of(0), false, w.cols, &w.centre, stream);
+  degree_prologue(w, X, xt, N, D, ldx, stream);
+  degree_packs(w, X, xt, D, ldx, beta_of(0), true, w.flag, stream);
+  // the largest bandwidth decides (every level's outputs are poisoned)
+  const PoisonGate poison = poison_gate(xt, w.centre, beta_of(nb - 1), w.flag);
   if (alpha == 0.0 || !rowsum_sym_applies(w.rows, w.cols, true, w.colfix)) {
     // no weighted pass to carry the squares (alpha = 0), or not the symmetric
     // path: fd_degree's passes, level by level
-    for (int l = 0; l < nb; ++l)
-      degree_run(w, X, xt, N, D, ldx, beta_of(l), alpha, at(q, l), at(d, l), at(s, l),
-                 s_off != nullptr ? s_off + l : nullptr, l > 0, stream);
+    for (int l = 0; l < nb; ++l) {
+      if (l > 0) degree_packs(w, X, xt, D, ldx, beta_of(l), false, nullptr, stream);
+      degree_passes(w, N, alpha, at(q, l), at(d, l), at(s, l), off_at(l), poison, stream);
+    }
     return;
   }
   // q of the current level and of the next, in the caller's arrays or in two
-  // workspace vectors used in turn
+  // workspace vectors used in turn; likewise its partial sums
   auto q_of = [&](int l) { return q != nullptr ? q + int64_t(l) * N : (l % 2 ? w.w : w.q); };
+  const int64_t nq = qsum_words(w.rows.npad);
+  auto qsum_of = [&](int l) { return w.qsum + (l % 2) * nq; };
   const SymPass p1 = launch_rowsum_sym_pass(w.plan, w.rows, w.cols, FSpan{}, w.part, w.colfix,
-                                            true, stream);
-  launch_degree_reduce_q(p1, w.rows, w.cols, w.part, w.colfix, q_of(0), alpha, w.wp, stream);
-  if (s_off != nullptr) launch_sum_minus_n(q_of(0), N, s_off, stream);
-  launch_zero_u64(w.sq_colfix, w.rows.npad, stream);
+                                            stream);
+  launch_degree_reduce_q(p1, w.rows, w.cols, w.part, w.colfix, q_of(0), alpha, w.wp, qsum_of(0),
+                         poison, stream);
   for (int l = 0; l < nb; ++l) {
-    if (l > 0) {
-      launch_pack_points(X, xt, N, D, ldx, beta_of(l), true, w.rows, &w.centre, stream);
-      launch_pack_points(X, xt, N, D, ldx, beta_of(l), false, w.cols, &w.centre, stream);
-    }
+    // (the column-sum words are zero already; clearing them again is harmless)
+    if (l > 0) degree_packs(w, X, xt, D, ldx, beta_of(l), true, nullptr, stream);
     if (l + 1 == nb) {
       const SymPass p2 = launch_rowsum_sym_pass(w.plan, w.rows, w.cols, w.wp, w.part, w.colfix,
-                                                false, stream);
+                                                stream);
       launch_degree_reduce_ds(p2, w.rows, w.part, w.colfix, q_of(l), alpha, at(d, l), at(s, l),
-                              stream);
+                              qsum_of(l), off_at(l), poison, stream);
       break;
     }
     // weighted pass of level l with the squared sums: t_l and q_{l+1}
     const SymPass p2 = launch_rowsum_sym_pass(w.plan, w.rows, w.cols, w.wp, w.part, w.colfix,
-                                              false, stream, w.sq_part, w.sq_colfix);
+                                              stream, w.sq_part, w.sq_colfix);
     launch_degree_reduce_dsq(p2, w.rows, w.cols, w.part, w.colfix, q_of(l), alpha, at(d, l),
-                             at(s, l), w.sq_part, w.sq_colfix, q_of(l + 1), w.wp, stream);
-    if (s_off != nullptr) launch_sum_minus_n(q_of(l + 1), N, s_off + l + 1, stream);
+                             at(s, l), w.sq_part, w.sq_colfix, q_of(l + 1), w.wp, qsum_of(l),
+                             off_at(l), qsum_of(l + 1), poison, stream);
   }
 }
 
@@ -458,18 +550,7 @@ fd_status fd_kernel_matmul(const void* Xr, int64_t Nr, const void* Xc, int64_t N
     a.cap = ws_bytes;
     ProductWs w = carve_product(a, Nr, Nc, D, int(b));
     hipStream_t st = static_cast<hipStream_t>(stream);
-    launch_scan_nonfinite(Xr, xt, Nr, D, ldx, w.flag, true, st);
-    if (Xc != Xr) launch_scan_nonfinite(Xc, xt, Nc, D, ldx, w.flag, false, st);
-    // one centre for both sets: the column set's mean, the radius over both
-    launch_centre(Xc, xt, Nc, D, ldx, w.centre, st);
-    if (Xr != Xc || Nr > Nc) launch_radius_more(Xr, xt, Nr, D, ldx, w.centre, st);
-    launch_pack_points(Xr, xt, Nr, D, ldx, beta, true, w.rows, &w.centre, st);
-    launch_pack_points(Xc, xt, Nc, D, ldx, beta, false, w.cols, &w.centre, st);
-    // same base pointer and ldx: index i names the same point in both sets
-    const bool diag = (Xr == Xc);
-    product_apply(w, sl, sr, V, ldv, int(b), Y, ldy, diag, st);
-    launch_range_check(xt, w.centre, beta, w.flag, st);
-    launch_poison(w.flag, Y, Nr, b, ldy, st);
+    matmul_run(w, Xr, Xc, D, ldx, xt, beta, sl, sr, V, int(b), ldv, Y, ldy, st);
   });
 }
 
@@ -496,17 +577,7 @@ fd_status fd_kernel_matmul_noalloc(const void* Xr, int64_t Nr, const void* Xc, i
     a.cap = SCRATCH_BYTES;
     ProductWs w = carve_product_exact(a, Nr, Nc, D, int(b));
     hipStream_t st = static_cast<hipStream_t>(stream);
-    launch_scan_nonfinite(Xr, xt, Nr, D, ldx, w.flag, true, st);
-    if (Xc != Xr) launch_scan_nonfinite(Xc, xt, Nc, D, ldx, w.flag, false, st);
-    // one centre for both sets: the column set's mean, the radius over both
-    launch_centre(Xc, xt, Nc, D, ldx, w.centre, st);
-    if (Xr != Xc || Nr > Nc) launch_radius_more(Xr, xt, Nr, D, ldx, w.centre, st);
-    launch_pack_points(Xr, xt, Nr, D, ldx, beta, true, w.rows, &w.centre, st);
-    launch_pack_points(Xc, xt, Nc, D, ldx, beta, false, w.cols, &w.centre, st);
-    const bool diag = (Xr == Xc);
-    product_apply(w, sl, sr, V, ldv, int(b), Y, ldy, diag, st);
-    launch_range_check(xt, w.centre, beta, w.flag, st);
-    launch_poison(w.flag, Y, Nr, b, ldy, st);
+    matmul_run(w, Xr, Xc, D, ldx, xt, beta, sl, sr, V, int(b), ldv, Y, ldy, st);
   });
 }
 
@@ -528,11 +599,7 @@ fd_status fd_degree(const void* X, fd_dtype xt, int64_t N, int64_t D, int64_t ld
     a.cap = ws_bytes;
     DegreeWs w = carve_degree(a, N, D);
     hipStream_t st = static_cast<hipStream_t>(stream);
-    launch_scan_nonfinite(X, xt, N, D, ldx, w.flag, true, st);
     degree_run(w, X, xt, N, D, ldx, beta, alpha, q, d, s, s_off, true, st);
-    launch_range_check(xt, w.centre, beta, w.flag, st);
-    for (float* v : {q, d, s}) launch_poison(w.flag, v, N, 1, 1, st);
-    launch_poison(w.flag, s_off, 1, st);
   });
 }
 
@@ -556,12 +623,7 @@ fd_status fd_degree_dyadic(const void* X, fd_dtype xt, int64_t N, int64_t D, int
     a.cap = ws_bytes;
     DegreeWs w = carve_degree_dyadic(a, N, D);
     hipStream_t st = static_cast<hipStream_t>(stream);
-    launch_scan_nonfinite(X, xt, N, D, ldx, w.flag, true, st);
     degree_run_dyadic(w, X, xt, N, D, ldx, beta0, int(nbeta), alpha, q, d, s, s_off, st);
-    // the largest bandwidth decides (every level's outputs are poisoned)
-    launch_range_check(xt, w.centre, std::ldexp(double(beta0), nbeta - 1), w.flag, st);
-    for (float* v : {q, d, s}) launch_poison(w.flag, v, int64_t(nbeta) * N, 1, 1, st);
-    launch_poison(w.flag, s_off, nbeta, st);
   });
 }
 

@@ -115,21 +115,40 @@ struct PointPack {
 };
 
 // Centring of a float32 point set (the kernel is translation invariant, and
-// the Gram-form exponent is most accurate around the mean): column means mu
-// (float64) and the largest squared distance of a point from them.
+// the Gram-form exponent is most accurate around the mean): partial column sums
+// (float64, one row of D per prologue workgroup; every consumer adds them in
+// the same order) and the largest squared distance of a point from the mean.
+// flags: one word per prologue workgroup, non-zero where it met a NaN or an
+// infinity.
 struct CentreWs {
-  double* part = nullptr;             // nblk x D column partial sums
-  double* mu = nullptr;               // D
-  unsigned long long* r2max = nullptr;  // float64 bits of max ||x - mu||^2
-  int nblk = 0;
+  double* part = nullptr;               // nblk x D column partial sums
+  unsigned long long* r2max = nullptr;  // float64 bits of max ||x - mean||^2
+  int* flags = nullptr;                 // nblk words, then nblk2 of a second point set
+  int64_t n = 0;                        // points the partial sums cover (set by the prologue)
+  int nblk = 0, nblk2 = 0;              // workgroups carved for
+  int used = 0, used2 = 0;              // workgroups the last prologue ran
 };
-CentreWs carve_centre(Arena& a, int64_t n);
-// mu of X[0:n] and r2max over it (float32 X; a no-op for bfloat16).
-void launch_centre(const void* X, fd_dtype xt, int64_t n, int64_t D, int64_t ldx,
+CentreWs carve_centre(Arena& a, int64_t n, int64_t n2 = 0);
+
+// What one call reads before its kernel passes: the points X (column sums and
+// finiteness), a second point set X2 (finiteness), and a block V (column
+// maxima of sr V for the split pack).
+struct PrologueIn {
+  const void* X = nullptr;
+  fd_dtype xt = FD_F32;
+  int64_t n = 0, D = 0, ldx = 0;
+  const void* X2 = nullptr;
+  int64_t n2 = 0;
+  const float* V = nullptr;
+  int64_t nv = 0, b = 0, ldv = 0;
+  const float* sr = nullptr;
+};
+// Everything in one launch: centre.part, centre.flags, vscale's partial
+// maxima; clears centre.r2max (the packs raise it).
+void launch_prologue(const PrologueIn& in, CentreWs& c, FSpan vscale, hipStream_t stream);
+// r2max over X[0:n] from the prologue's sums, without packing (a no-op for bfloat16).
+void launch_radius(const void* X, fd_dtype xt, int64_t n, int64_t D, int64_t ldx,
                    const CentreWs& c, hipStream_t stream);
-// r2max also over X2[0:n2], centred on the same mu.
-void launch_radius_more(const void* X2, fd_dtype xt, int64_t n2, int64_t D, int64_t ldx,
-                        const CentreWs& c, hipStream_t stream);
 
 // Exponent budget of the short split layouts: above beta log2(e) max ||x - mu||^2
 // = 64 the kernels take the layout that keeps all three offset pieces (the
@@ -161,10 +180,16 @@ bool exponent_in_range(fd_dtype xt, double beta, double r2max);
 double exponent_radius(fd_dtype xt, const CentreWs& c, hipStream_t stream);
 // Synchronous check: FD_ERR_UNSUPPORTED when beta is outside the range.
 void require_exponent_range(fd_dtype xt, const CentreWs& c, double beta, hipStream_t stream);
-// Asynchronous check: sets bit 2 of *flag (the non-finite-input flag, whose
-// poison fills the outputs with NaN) when beta is outside the range.
-void launch_range_check(fd_dtype xt, const CentreWs& c, double beta, int* flag,
-                        hipStream_t stream);
+// Asynchronous check: where it holds, the kernel that writes an output of the
+// call writes NaN instead (a point is not finite, or beta is outside the
+// exponent range).  flag == NULL: no check.
+struct PoisonGate {
+  const int* flag = nullptr;
+  const unsigned long long* r2max = nullptr;  // NULL for bfloat16 X
+  double bl = 0.0;                            // beta log2(e)
+  double f2 = 0.0;                            // square of the larger coordinate scale
+};
+PoisonGate poison_gate(fd_dtype xt, const CentreWs& c, double beta, const int* flag);
 
 // Floats per point of a pack region (large enough for either pack kind).
 int pack_floats_per_point(int64_t D);
@@ -188,42 +213,57 @@ KVPlan plan_rowsum(int64_t Nr, int64_t Nc, int dp);
 PointPack carve_pack(Arena& a, int64_t n, int dp, int64_t pad);
 
 // Launchers (enqueue on stream; throw Error on failure).
-void launch_pack_points(const void* X, fd_dtype xt, int64_t n, int64_t D, int64_t ldx,
-                        double beta, bool row_side, PointPack& out, const CentreWs* centre,
-                        hipStream_t stream);
+// The packs of one call in one launch: the row pack of Xr and the column pack
+// of Xc (float32: centred on the prologue's mean, r2max raised to both sets'
+// radius), the block V (split pack, or with ncb = 0 the weight pack of its one
+// column), and 64-bit words to clear.  flag: receives whether the prologue met
+// a non-finite value.
+struct PackIn {
+  const void *Xr = nullptr, *Xc = nullptr;
+  fd_dtype xt = FD_F32;
+  int64_t D = 0, ldx = 0;
+  double beta = 0.0;
+  int* flag = nullptr;
+  const float* V = nullptr;
+  int64_t b = 0, ldv = 0;
+  const float* sr = nullptr;
+  int ncb = 0;
+  FSpan vp, vscale;
+  int64_t nvmax = 0;  // prologue workgroups that left column maxima
+  unsigned long long *zero1 = nullptr, *zero2 = nullptr;
+  int64_t nzero = 0;
+};
+void launch_packs(const PackIn& in, PointPack& rows, PointPack& cols, const CentreWs& centre,
+                  hipStream_t stream);
 void launch_pack_w(const float* w, int64_t n, int64_t npad, FSpan wp, hipStream_t stream);
-// Weight pack of sr * v for one column v (row stride ldv; sr may be NULL).
-void launch_pack_wv(const float* v, int64_t ldv, const float* sr, int64_t n, int64_t npad,
-                    FSpan wp, hipStream_t stream);
 // Y[i * ldy] = sl[i] * t[i] (sl NULL: t[i]).
 void launch_scale_rows(const float* t, const float* sl, int64_t n, float* Y, int64_t ldy,
-                       hipStream_t stream);
-// Pack sr * V for the product that matches the row pack's kind.
-void launch_pack_v_for(const PointPack& rows, const float* V, int64_t n, int64_t b, int64_t ldv,
-                       const float* sr, int ncb, int64_t npad, FSpan vp, FSpan vscale,
-                       hipStream_t stream);
-// Split float16 pack of sr * V with per-column power-of-two scales (vscale:
-// 64 max-abs bit patterns followed by 64 inverse scales).
+                       const PoisonGate& poison, hipStream_t stream);
+// Split float16 pack of sr * V with per-column power-of-two scales, in two
+// launches (column maxima, pack).  vscale (VSCALE_FLOATS): 64 inverse scales,
+// then VMAX_BLOCKS x 64 partial maxima.
+constexpr int VMAX_BLOCKS = 128;
+constexpr int VSCALE_FLOATS = 64 + 64 * VMAX_BLOCKS;
+int64_t vmax_blocks(int64_t n);
 void launch_pack_v_split(const float* V, int64_t n, int64_t b, int64_t ldv, const float* sr,
                          int ncb, int64_t npad, FSpan vp, FSpan vscale, hipStream_t stream);
 // Y = diag(sl) K diag(sr) V from packed operands (V packed with sr applied).
 void launch_product(const KVPlan& p, const PointPack& rows, const PointPack& cols, FSpan vp,
                     FSpan vscale, bool diag, const float* sl, float* Y, int64_t ldy, int b,
-                    FSpan part, hipStream_t stream);
-// out = K w (wp.p == NULL: w = 1).  With colfix (npad 64-bit words of
-// scratch) and rows and columns the same float32 point set, the symmetric
-// kernel is used (weights must lie in [0, 1]).
+                    FSpan part, const PoisonGate& poison, hipStream_t stream);
+// out = K w (wp.p == NULL: w = 1).
 void launch_rowsum(const KVPlan& p, const PointPack& rows, const PointPack& cols, FSpan wp,
-                   bool diag, float* out, FSpan part, hipStream_t stream,
-                   unsigned long long* colfix = nullptr);
+                   bool diag, float* out, FSpan part, hipStream_t stream);
 KVPlan plan_rowsum_sym(int64_t N, int64_t npad, int dp, int nib);
 // The symmetric path piece by piece (the two normalisation passes fuse their
 // epilogues into its reduction): whether it applies, one pass of the kernel
-// (row partials in part, fixed-point column sums added into colfix, which is
-// zeroed first if asked), and the fused reductions.  Each reduction leaves
+// (row partials in part, fixed-point column sums added into colfix, which the
+// pack or the last reduction cleared), and the fused reductions.  Each reduction leaves
 // colfix zeroed.  launch_degree_reduce_q: q, and w = q^-alpha into the weight
 // pack (the column pack's extent) when wp.p is set; launch_degree_reduce_ds: d = w t and s = w d^-1/2
-// (either may be NULL).
+// (either may be NULL).  Each workgroup of a reduction that makes q leaves the
+// sum of its q in qsum; the next reduction's first workgroup adds those to
+// s_off = sum(q) - n.
 struct SymPass {
   int nsplit = 0;
   double inv_fix = 0.0;
@@ -240,15 +280,16 @@ bool rowsum_sym_applies(const PointPack& rows, const PointPack& cols, bool diag,
 // sq_part / sq_colfix (weighted passes only): also the squared-kernel sums, whose
 // reduction uses the returned inv_fix as well.
 SymPass launch_rowsum_sym_pass(const KVPlan& p, const PointPack& rows, const PointPack& cols,
-                               FSpan wp, FSpan part, unsigned long long* colfix, bool zero_colfix,
+                               FSpan wp, FSpan part, unsigned long long* colfix,
                                hipStream_t stream, FSpan sq_part = FSpan{},
                                unsigned long long* sq_colfix = nullptr);
 void launch_degree_reduce_q(const SymPass& sp, const PointPack& rows, const PointPack& cols,
                             FSpan part, unsigned long long* colfix, float* q, double alpha,
-                            FSpan wp, hipStream_t stream);
+                            FSpan wp, double* qsum, const PoisonGate& poison, hipStream_t stream);
 void launch_degree_reduce_ds(const SymPass& sp, const PointPack& rows, FSpan part,
                              unsigned long long* colfix, const float* q, double alpha, float* d,
-                             float* s, hipStream_t stream);
+                             float* s, const double* qsum, double* s_off,
+                             const PoisonGate& poison, hipStream_t stream);
 // launch_degree_reduce_ds plus the squared-kernel sums of the same pass: the
 // next dyadic level's q_next = K(2 beta) 1 and its w = q_next^-alpha into the
 // weight pack wp (the column pack's extent); leaves both colfix arrays zeroed.
@@ -256,16 +297,20 @@ void launch_degree_reduce_dsq(const SymPass& sp, const PointPack& rows, const Po
                               FSpan part, unsigned long long* colfix, const float* q,
                               double alpha, float* d, float* s, FSpan sq_part,
                               unsigned long long* sq_colfix, float* q_next, FSpan wp,
-                              hipStream_t stream);
-void launch_zero_u64(unsigned long long* p, int64_t n, hipStream_t stream);
+                              const double* qsum, double* s_off, double* qsum_next,
+                              const PoisonGate& poison, hipStream_t stream);
+// Words of a partial-sum buffer of q (one per reduction workgroup).
+int64_t qsum_words(int64_t npad);
 // Row tiles per wave of the symmetric row sums, and the fewest column splits
 // of their large-problem plans.
 constexpr int SYM_NIB = 8;
 constexpr int64_t SYM_MIN_SPLITS = 16;
 // Row slots of the partial sums of a symmetric row-sum plan with npad rows.
 size_t sym_part_rows(int64_t npad, int nib);
+// d, s from q and t; with qsum (nqsum words) also s_off.
 void launch_degree_finish(const float* q, const float* t, int64_t n, double alpha, float* d,
-                          float* s, hipStream_t stream);
+                          float* s, const double* qsum, int64_t nqsum, double* s_off,
+                          const PoisonGate& poison, hipStream_t stream);
 void launch_pow_neg(const float* q, int64_t n, double alpha, float* w, hipStream_t stream);
 void launch_sum_minus_n(const float* q, int64_t n, double* out, hipStream_t stream);
 

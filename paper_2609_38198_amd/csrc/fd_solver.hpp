@@ -23,6 +23,7 @@ struct DegreeWs {
   float* t = nullptr;
   float* w = nullptr;
   unsigned long long* colfix = nullptr;  // npad words: column sums of the symmetric row sums
+  double* qsum = nullptr;                // twice qsum_words(npad): partial sums of q
   FSpan sq_part;                          // squared-kernel row partials (dyadic levels)
   unsigned long long* sq_colfix = nullptr;
   int* flag = nullptr;  // set when X holds a non-finite value
@@ -39,10 +40,11 @@ void product_apply(ProductWs& w, const float* sl, const float* sr, const float* 
                    int b, float* Y, int64_t ldy, bool diag, hipStream_t stream);
 
 DegreeWs carve_degree(Arena& a, int64_t N, int64_t D);
-// q, d, s (any may be NULL) and s_off; `pack` = fill the point packs first.
+// q, d, s (any may be NULL) and s_off, from X; with `poison` the outputs are NaN
+// where X is not finite or beta is out of range.
 void degree_run(DegreeWs& w, const void* X, fd_dtype xt, int64_t N, int64_t D, int64_t ldx,
                 double beta, double alpha, float* q, float* d, float* s, double* s_off,
-                bool pack, hipStream_t stream);
+                bool poison, hipStream_t stream);
 
 // carve_degree plus the squared-kernel buffers of the dyadic ladder.
 DegreeWs carve_degree_dyadic(Arena& a, int64_t N, int64_t D);

@@ -343,37 +343,88 @@ __device__ __forceinline__ void hx_emit(const float (&px)[M][3], const float (&p
   }
 }
 
-template <int RID, bool ROW>
-__global__ __launch_bounds__(256) void pack_hx_point_kernel(const float* __restrict__ X, int64_t n,
-                                                            int D, int64_t ldx, double scale,
-                                                            double neg_bl, double shift,
-                                                            int64_t npad,
-                                                            uintx4* __restrict__ out,
-                                                            const double* __restrict__ mu,
-                                                            HxGate gate) {
+//
+// One launch packs both sides of a call (workgroups [0, nbr): the row set,
+// then the column set, then the block V), adds the column means of the
+// prologue's partial sums, and raises r2max to the largest ||x - mu||^2.
+// Recipes that drop the third offset piece (WIDE >= 0) are written in both
+// layouts here and now: the choice between them needs r2max, which only this
+// launch completes.  The kernel is latency bound at small N (its workgroups
+// are small so that 2,048 points already spread over 32 of them) and writes
+// 64-byte words per point and chunk at large N.
+struct PackHxSide {
+  const float* X;
+  int64_t n, npad;
+  uintx4 *out, *out2;
+  double scale, shift;
+};
+struct PackHxArgs {
+  PackHxSide row, col;
+  int64_t ldx, nbr, nbc;
+  int D, nblk;
+  double neg_bl;
+  const double* part;  // prologue sums (nblk x D) over nmean points
+  int64_t nmean;
+  unsigned long long* r2max;
+  const int* flags;
+  int nflags;
+  int* flag;
+  PackV v;
+  unsigned long long *zero1, *zero2;
+  int64_t nzero;
+};
+
+template <int RID, int WIDE, bool ROW>
+__device__ __forceinline__ void pack_hx_point(const PackHxArgs& a, const PackHxSide& s, int64_t i,
+                                              const double* mu) {
   constexpr int M = HX_TABLE[RID].maxd;
-  constexpr int NCH = ROW ? HX_TABLE[RID].nb : HX_TABLE[RID].nc;
-  if (hx_gate_closed(gate)) return;
-  const int64_t i = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
-  if (i >= npad) return;
-  const bool real = i < n;
-  const float* xi = X + min(i, n - 1) * ldx;
+  const bool real = i < s.n;
+  const float* xi = s.X + min(i, s.n - 1) * a.ldx;
   float xv[M];
 #pragma unroll
-  for (int f = 0; f < M; ++f) xv[f] = xi[min(f, D - 1)];
+  for (int f = 0; f < M; ++f) xv[f] = xi[min(f, a.D - 1)];
   float px[M][3];
   double r = 0.0;
 #pragma unroll
   for (int f = 0; f < M; ++f) {
-    const bool use = real && f < D;
     // centred on mu in float64 (translation invariance of the kernel)
-    const double v = use ? double(xv[f]) - (mu != nullptr ? mu[min(f, D - 1)] : 0.0) : 0.0;
+    const double v = real && f < a.D ? double(xv[f]) - mu[min(f, a.D - 1)] : 0.0;
     r += v * v;
-    pieces3(scale * v, px[f]);
+    pieces3(s.scale * v, px[f]);
   }
   float pa[3];
-  pieces3(real ? neg_bl * r + shift : -65504.0, pa);
-  hx_emit<RID, ROW, NCH, M>(px, pa, out, i / TILE, int(i % TILE));
+  pieces3(real ? a.neg_bl * r + s.shift : -65504.0, pa);
+  hx_emit<RID, ROW, ROW ? HX_TABLE[RID].nb : HX_TABLE[RID].nc, M>(px, pa, s.out, i / TILE,
+                                                                  int(i % TILE));
+  if constexpr (WIDE >= 0)
+    hx_emit<WIDE, ROW, ROW ? HX_TABLE[WIDE].nb : HX_TABLE[WIDE].nc, M>(px, pa, s.out2, i / TILE,
+                                                                       int(i % TILE));
+  raise_r2max(r, a.r2max);
+}
+
+template <int RID, int WIDE>
+__global__ __launch_bounds__(PACK_THREADS) void pack_hx_kernel(PackHxArgs a) {
+  __shared__ double mu[MAX_D], red[PACK_THREADS];
+  __shared__ int ex[64];
+  int64_t blk = blockIdx.x;
+  if (blk == 0 && a.flag != nullptr) pack_flag(a.flags, a.nflags, a.flag);
+  if (blk >= a.nbr + a.nbc) {
+    pack_v_block(a.v, blk - a.nbr - a.nbc, ex);
+    return;
+  }
+  centre_means(a.part, a.nblk, a.D, a.nmean, mu, red);
+  // npad is a multiple of 32: a wave's lanes past it take the last point again
+  if (blk < a.nbr) {
+    const int64_t i = blk * PACK_THREADS + threadIdx.x;
+    if (i < a.nzero) {
+      if (a.zero1 != nullptr) a.zero1[i] = 0ull;
+      if (a.zero2 != nullptr) a.zero2[i] = 0ull;
+    }
+    pack_hx_point<RID, WIDE, true>(a, a.row, min(i, a.row.npad - 1), mu);
+  } else {
+    const int64_t i = (blk - a.nbr) * PACK_THREADS + threadIdx.x;
+    pack_hx_point<RID, WIDE, false>(a, a.col, min(i, a.col.npad - 1), mu);
+  }
 }
 
 // ------------------------------------------------------------------ exponent
@@ -490,7 +541,8 @@ __attribute__((amdgpu_waves_per_eu(hx_waves<RID, NCB, NIB>()))) void product_hx_
     const uintx4* __restrict__ xc, const VSplit* __restrict__ vp, const uintx4* __restrict__ xr,
     int64_t nrt, int64_t njp, int64_t jp_per_split, int diag, float m1,
     const float* __restrict__ colscale, const float* __restrict__ sl, float* __restrict__ Y,
-    int64_t ldy, int64_t Nr, int b, float* __restrict__ part, int64_t nrpad, HxGate gate) {
+    int64_t ldy, int64_t Nr, int b, float* __restrict__ part, int64_t nrpad, HxGate gate,
+    PoisonGate poison) {
   constexpr int NB = Hx<RID>::nb;
   __shared__ floatx4 tot[4][NIB][NCB][64];
   if (hx_gate_closed(gate)) return;
@@ -566,7 +618,7 @@ __attribute__((amdgpu_waves_per_eu(hx_waves<RID, NCB, NIB>()))) void product_hx_
           part[(split * nrpad + i) * (NCB * 16) + c] = v[e];
         } else if (i < Nr && c < b) {
           const float y = v[e] * colscale[c];
-          Y[i * ldy + c] = (sl != nullptr) ? y * sl[i] : y;
+          Y[i * ldy + c] = poisoned(poison) ? __builtin_nanf("") : (sl != nullptr) ? y * sl[i] : y;
         }
       }
     }
@@ -1046,27 +1098,29 @@ __attribute__((amdgpu_waves_per_eu(hx_sym_waves<RID, NIB, SQ>()))) void rowsum_s
 template <int RID, int NCB, int NIB>
 void product_hx_launch(const KVPlan& p, const PointPack& rows, const PointPack& cols,
                        const float* vp, const float* colscale, bool diag, const float* sl,
-                       float* Y, int64_t ldy, int b, float* part, hipStream_t stream) {
+                       float* Y, int64_t ldy, int b, float* part,
+                       const PoisonGate& poison, hipStream_t stream) {
   const unsigned grid = unsigned(p.nrt * p.nsplit);
   hipLaunchKernelGGL((product_hx_kernel<RID, NCB, NIB>), dim3(grid), dim3(WG_THREADS), 0, stream,
                      reinterpret_cast<const uintx4*>(cols.xp.p),
                      reinterpret_cast<const VSplit*>(vp),
                      reinterpret_cast<const uintx4*>(rows.xp.p), p.nrt, ceil_div(p.njb, 2),
                      p.jb_per_split / 2, int(diag), -1.0f, colscale, sl, Y, ldy, rows.n, b, part,
-                     rows.npad, gate_of(rows));
+                     rows.npad, gate_of(rows), poison);
   FD_LAUNCH_CHECK();
 }
 
 template <int RID, int NCB>
 void product_hx_nib(const KVPlan& p, const PointPack& rows, const PointPack& cols,
                     const float* vp, const float* cs, bool diag, const float* sl, float* Y,
-                    int64_t ldy, int b, float* part, hipStream_t stream) {
+                    int64_t ldy, int b, float* part, const PoisonGate& poison,
+                    hipStream_t stream) {
   switch (p.nib) {
-    case 2: return product_hx_launch<RID, NCB, 2>(p, rows, cols, vp, cs, diag, sl, Y, ldy, b, part, stream);
-    case 4: return product_hx_launch<RID, NCB, 4>(p, rows, cols, vp, cs, diag, sl, Y, ldy, b, part, stream);
+    case 2: return product_hx_launch<RID, NCB, 2>(p, rows, cols, vp, cs, diag, sl, Y, ldy, b, part, poison, stream);
+    case 4: return product_hx_launch<RID, NCB, 4>(p, rows, cols, vp, cs, diag, sl, Y, ldy, b, part, poison, stream);
     case 8:
       if constexpr (RID <= 3 && NCB <= 2)
-        return product_hx_launch<RID, NCB, 8>(p, rows, cols, vp, cs, diag, sl, Y, ldy, b, part, stream);
+        return product_hx_launch<RID, NCB, 8>(p, rows, cols, vp, cs, diag, sl, Y, ldy, b, part, poison, stream);
       break;
   }
   throw Error{FD_ERR_INVALID_ARG, "internal: unsupported rows per wave"};
@@ -1075,12 +1129,13 @@ void product_hx_nib(const KVPlan& p, const PointPack& rows, const PointPack& col
 template <int RID>
 void product_hx_ncb(const KVPlan& p, const PointPack& rows, const PointPack& cols,
                     const float* vp, const float* cs, bool diag, const float* sl, float* Y,
-                    int64_t ldy, int b, float* part, hipStream_t stream) {
+                    int64_t ldy, int b, float* part, const PoisonGate& poison,
+                    hipStream_t stream) {
   switch (p.ncb) {
-    case 1: return product_hx_nib<RID, 1>(p, rows, cols, vp, cs, diag, sl, Y, ldy, b, part, stream);
-    case 2: return product_hx_nib<RID, 2>(p, rows, cols, vp, cs, diag, sl, Y, ldy, b, part, stream);
-    case 3: return product_hx_nib<RID, 3>(p, rows, cols, vp, cs, diag, sl, Y, ldy, b, part, stream);
-    case 4: return product_hx_nib<RID, 4>(p, rows, cols, vp, cs, diag, sl, Y, ldy, b, part, stream);
+    case 1: return product_hx_nib<RID, 1>(p, rows, cols, vp, cs, diag, sl, Y, ldy, b, part, poison, stream);
+    case 2: return product_hx_nib<RID, 2>(p, rows, cols, vp, cs, diag, sl, Y, ldy, b, part, poison, stream);
+    case 3: return product_hx_nib<RID, 3>(p, rows, cols, vp, cs, diag, sl, Y, ldy, b, part, poison, stream);
+    case 4: return product_hx_nib<RID, 4>(p, rows, cols, vp, cs, diag, sl, Y, ldy, b, part, poison, stream);
   }
   throw Error{FD_ERR_UNSUPPORTED, "block width above 64"};
 }
@@ -1198,65 +1253,66 @@ int hx_full_offset_recipe(int rid) {
   return rid == 3 ? 4 : rid == 5 ? 6 : -1;
 }
 
-template <int RID, bool ROW>
-static void pack_hx_launch(const float* X, int64_t n, int64_t D, int64_t ldx, double beta,
-                           FSpan xp, int64_t npad, const double* mu, HxGate gate,
-                           hipStream_t stream) {
-  const HxRecipe& R = HX_TABLE[RID];
-  const int nch = ROW ? R.nb : R.nc;
-  check_span(xp, size_t(npad / TILE) * nch * 64 * 4, "split point pack");
-  FD_REQUIRE(D <= R.maxd, FD_ERR_INVALID_ARG, "internal: recipe too narrow for D");
-  const double bl = beta * LOG2E;
-  const double s = hx_coord_scale(beta);
-  const double scale = ROW ? 2.0 * bl / s : s;
-  const double shift = ROW ? double(SHIFT) : 0.0;
-  hipLaunchKernelGGL((pack_hx_point_kernel<RID, ROW>), dim3(blocks_for(npad, 256)), dim3(256), 0,
-                     stream, X, n, int(D), ldx, scale, -bl, shift, npad,
-                     reinterpret_cast<uintx4*>(xp.p), mu, gate);
-  FD_LAUNCH_CHECK();
-}
-
-template <bool ROW>
-static void pack_hx_rid(int rid, const float* X, int64_t n, int64_t D, int64_t ldx, double beta,
-                        FSpan xp, int64_t npad, const double* mu, HxGate gate,
-                        hipStream_t stream) {
-  switch (rid) {
-    case 0: return pack_hx_launch<0, ROW>(X, n, D, ldx, beta, xp, npad, mu, gate, stream);
-    case 1: return pack_hx_launch<1, ROW>(X, n, D, ldx, beta, xp, npad, mu, gate, stream);
-    case 2: return pack_hx_launch<2, ROW>(X, n, D, ldx, beta, xp, npad, mu, gate, stream);
-    case 3: return pack_hx_launch<3, ROW>(X, n, D, ldx, beta, xp, npad, mu, gate, stream);
-    case 4: return pack_hx_launch<4, ROW>(X, n, D, ldx, beta, xp, npad, mu, gate, stream);
-    case 5: return pack_hx_launch<5, ROW>(X, n, D, ldx, beta, xp, npad, mu, gate, stream);
-    case 6: return pack_hx_launch<6, ROW>(X, n, D, ldx, beta, xp, npad, mu, gate, stream);
-  }
-  throw Error{FD_ERR_UNSUPPORTED, "feature dimension above 64"};
-}
-
-void launch_pack_points_hx(const float* X, int64_t n, int64_t D, int64_t ldx, double beta,
-                           bool row_side, PointPack& out, const CentreWs* centre,
-                           hipStream_t stream) {
-  const int rid = hx_recipe_for(D);
-  FD_REQUIRE(rid >= 0, FD_ERR_UNSUPPORTED, "feature dimension above 64");
-  FD_REQUIRE(out.npad % (2 * TILE) == 0 && out.npad >= n, FD_ERR_INVALID_ARG,
+// One side's geometry; the recipe's extents are checked here.
+static PackHxSide pack_hx_side(const void* X, PointPack& out, const PackIn& in, int rid, int wide,
+                               bool row_side, const CentreWs& centre) {
+  FD_REQUIRE(out.npad % (2 * TILE) == 0 && out.npad >= out.n && out.n >= 1, FD_ERR_INVALID_ARG,
              "internal: bad split pack geometry");
-  const double* mu = centre != nullptr ? centre->mu : nullptr;
-  const int wide = centre != nullptr ? hx_full_offset_recipe(rid) : -1;
+  auto extent = [&](int r) {
+    return size_t(out.npad / TILE) * (row_side ? HX_TABLE[r].nb : HX_TABLE[r].nc) * 64 * 4;
+  };
+  check_span(out.xp, extent(rid), "split point pack");
+  if (wide >= 0) check_span(out.xp2, extent(wide), "full-offset point pack");
   out.rid = rid;
   out.row_side = row_side;
   out.rid2 = wide;
   out.variant = wide >= 0 ? 1 : 0;
-  out.r2max = wide >= 0 ? centre->r2max : nullptr;
-  const HxGate g1{out.r2max, beta * LOG2E, out.variant};
-  if (row_side)
-    pack_hx_rid<true>(rid, X, n, D, ldx, beta, out.xp, out.npad, mu, g1, stream);
-  else
-    pack_hx_rid<false>(rid, X, n, D, ldx, beta, out.xp, out.npad, mu, g1, stream);
-  if (wide >= 0) {
-    const HxGate g2{out.r2max, beta * LOG2E, 2};
-    if (row_side)
-      pack_hx_rid<true>(wide, X, n, D, ldx, beta, out.xp2, out.npad, mu, g2, stream);
-    else
-      pack_hx_rid<false>(wide, X, n, D, ldx, beta, out.xp2, out.npad, mu, g2, stream);
+  out.r2max = wide >= 0 ? centre.r2max : nullptr;
+  const double s = hx_coord_scale(in.beta);
+  return PackHxSide{static_cast<const float*>(X), out.n, out.npad,
+                    reinterpret_cast<uintx4*>(out.xp.p), reinterpret_cast<uintx4*>(out.xp2.p),
+                    row_side ? 2.0 * (in.beta * LOG2E) / s : s, row_side ? double(SHIFT) : 0.0};
+}
+
+void launch_packs_hx(const PackIn& in, const PackV& v, PointPack& rows, PointPack& cols,
+                     const CentreWs& centre, hipStream_t stream) {
+  const int rid = hx_recipe_for(in.D);
+  FD_REQUIRE(rid >= 0, FD_ERR_UNSUPPORTED, "feature dimension above 64");
+  FD_REQUIRE(centre.part != nullptr && centre.used > 0 && in.nzero <= rows.npad,
+             FD_ERR_INVALID_ARG, "internal: packs before the prologue");
+  const int wide = hx_full_offset_recipe(rid);
+  PackHxArgs a{};
+  a.row = pack_hx_side(in.Xr, rows, in, rid, wide, true, centre);
+  a.col = pack_hx_side(in.Xc, cols, in, rid, wide, false, centre);
+  a.ldx = in.ldx;
+  a.nbr = ceil_div(rows.npad, PACK_THREADS);
+  a.nbc = ceil_div(cols.npad, PACK_THREADS);
+  a.D = int(in.D);
+  a.nblk = centre.used;
+  a.neg_bl = -(in.beta * LOG2E);
+  a.part = centre.part;
+  a.nmean = centre.n;
+  a.r2max = centre.r2max;
+  a.flags = centre.flags;
+  a.nflags = centre.used + centre.used2;
+  a.flag = in.flag;
+  a.v = v;
+  a.zero1 = in.zero1;
+  a.zero2 = in.zero2;
+  a.nzero = in.nzero;
+  const dim3 grid{unsigned(a.nbr + a.nbc + ceil_div(pack_v_items(v), PACK_THREADS))};
+  auto go = [&](auto kernel) {
+    hipLaunchKernelGGL(kernel, grid, dim3(PACK_THREADS), 0, stream, a);
+    FD_LAUNCH_CHECK();
+  };
+  switch (rid) {
+    case 0: return go(pack_hx_kernel<0, -1>);
+    case 1: return go(pack_hx_kernel<1, -1>);
+    case 2: return go(pack_hx_kernel<2, -1>);
+    case 3: return go(pack_hx_kernel<3, 4>);
+    case 4: return go(pack_hx_kernel<4, -1>);
+    case 5: return go(pack_hx_kernel<5, 6>);
+    case 6: return go(pack_hx_kernel<6, -1>);
   }
 }
 
@@ -1286,17 +1342,18 @@ static void dual_dispatch(const PointPack& rows, const PointPack& cols, fd_kerne
 
 void launch_product_hx(const KVPlan& p, const PointPack& rows, const PointPack& cols,
                        const float* vp, const float* cs, bool diag, const float* sl, float* Y,
-                       int64_t ldy, int b, float* part, hipStream_t stream) {
+                       int64_t ldy, int b, float* part, const PoisonGate& poison,
+                    hipStream_t stream) {
   dual_dispatch(rows, cols, FD_KERNEL_PRODUCT, stream, [&](const PointPack& r, const PointPack& c) {
     check_hx(p, r, c);
     switch (r.rid) {
-      case 0: return product_hx_ncb<0>(p, r, c, vp, cs, diag, sl, Y, ldy, b, part, stream);
-      case 1: return product_hx_ncb<1>(p, r, c, vp, cs, diag, sl, Y, ldy, b, part, stream);
-      case 2: return product_hx_ncb<2>(p, r, c, vp, cs, diag, sl, Y, ldy, b, part, stream);
-      case 3: return product_hx_ncb<3>(p, r, c, vp, cs, diag, sl, Y, ldy, b, part, stream);
-      case 4: return product_hx_ncb<4>(p, r, c, vp, cs, diag, sl, Y, ldy, b, part, stream);
-      case 5: return product_hx_ncb<5>(p, r, c, vp, cs, diag, sl, Y, ldy, b, part, stream);
-      case 6: return product_hx_ncb<6>(p, r, c, vp, cs, diag, sl, Y, ldy, b, part, stream);
+      case 0: return product_hx_ncb<0>(p, r, c, vp, cs, diag, sl, Y, ldy, b, part, poison, stream);
+      case 1: return product_hx_ncb<1>(p, r, c, vp, cs, diag, sl, Y, ldy, b, part, poison, stream);
+      case 2: return product_hx_ncb<2>(p, r, c, vp, cs, diag, sl, Y, ldy, b, part, poison, stream);
+      case 3: return product_hx_ncb<3>(p, r, c, vp, cs, diag, sl, Y, ldy, b, part, poison, stream);
+      case 4: return product_hx_ncb<4>(p, r, c, vp, cs, diag, sl, Y, ldy, b, part, poison, stream);
+      case 5: return product_hx_ncb<5>(p, r, c, vp, cs, diag, sl, Y, ldy, b, part, poison, stream);
+      case 6: return product_hx_ncb<6>(p, r, c, vp, cs, diag, sl, Y, ldy, b, part, poison, stream);
     }
   });
 }

@@ -79,6 +79,148 @@ __device__ __forceinline__ void split2m(float a, float b, float m1, unsigned& hi
   lo = __builtin_bit_cast(unsigned, l);
 }
 
+// Whether a call's outputs are NaN (PoisonGate).
+__device__ __forceinline__ bool poisoned(const PoisonGate& g) {
+  if (g.flag == nullptr) return false;
+  if (*g.flag != 0) return true;
+  if (g.r2max == nullptr) return false;
+  const double r2 = __longlong_as_double(static_cast<long long>(*g.r2max));
+  return !(g.bl * r2 <= HX_EXP_RANGE && g.f2 * r2 <= HX_PIECE_MAX * HX_PIECE_MAX);
+}
+
+// ---------------------------------------------------------------- V and weight packs
+
+constexpr int PACK_THREADS = 128;  // workgroup of the pack kernels
+
+// The V part of a pack launch: V (n x b, ldv) times sr, as the split pack of
+// ncb 16-column blocks over npairs pairs of 16-point tiles, or (ncb = 0) as the
+// weight pack of its one column over ntiles tiles.
+struct PackV {
+  const float* V = nullptr;
+  const float* sr = nullptr;
+  int64_t n = 0, ldv = 0, npairs = 0, ntiles = 0;
+  int b = 0, ncb = 0, nvmax = 0;
+  const float* vpart = nullptr;  // nvmax x 64 partial column maxima
+  float* colscale = nullptr;
+  VSplit* vp = nullptr;
+  floatx4* wp = nullptr;
+};
+inline int64_t pack_v_items(const PackV& a) {
+  return a.V == nullptr ? 0 : a.ncb > 0 ? a.npairs * a.ncb * 64 : a.ntiles * 64;
+}
+
+__device__ __forceinline__ int vscale_exponent(float mx) {
+  if (!(mx > 0.f)) return 0;
+  int e;
+  (void)frexpf(mx, &e);  // max < 2^e
+  return 14 - e;         // scaled max < 2^14
+}
+
+// Workgroup `blk` of the V part (PACK_THREADS threads); ex: 64 LDS words.
+__device__ __forceinline__ void pack_v_block(const PackV& a, int64_t blk, int* ex) {
+  const int64_t idx = blk * PACK_THREADS + threadIdx.x;
+  const int lane = int(threadIdx.x & 63);
+  const int g = lane >> 4, p = lane & 15;
+  if (a.ncb == 0) {
+    if (idx >= a.ntiles * 64) return;
+    floatx4 out;
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      const int64_t j = (idx >> 6) * TILE + 4 * g + r;
+      out[r] = 0.f;
+      if (j < a.n) out[r] = a.sr != nullptr ? a.sr[j] * a.V[j * a.ldv] : a.V[j * a.ldv];
+    }
+    a.wp[idx] = out;
+    return;
+  }
+  // column exponents from the prologue's partial maxima: two threads a column
+  // (a maximum does not depend on the order)
+  {
+    const int c = int(threadIdx.x) >> 1, h = int(threadIdx.x) & 1;
+    float m = 0.f;
+    if (c < a.b) {
+#pragma unroll 8
+      for (int k = h; k < a.nvmax; k += 2) m = fmaxf(m, a.vpart[k * 64 + c]);
+    }
+    m = fmaxf(m, __shfl_xor(m, 1));
+    if (h == 0) ex[c] = vscale_exponent(m);
+  }
+  __syncthreads();
+  if (blk == 0 && int(threadIdx.x) < a.b) a.colscale[threadIdx.x] = ldexpf(1.f, -ex[threadIdx.x] - 15);
+  if (idx >= a.npairs * a.ncb * 64) return;
+  const int cb = int((idx >> 6) % a.ncb);
+  const int64_t jp = idx / (64 * a.ncb);
+  const int c = cb * 16 + p;
+  const float scale = ldexpf(1.f, c < a.b ? ex[c] : 0);
+  float v[8];
+#pragma unroll
+  for (int e = 0; e < 8; ++e) {
+    const int64_t j = jp * 32 + (e < 4 ? 4 * g + e : 16 + 4 * g + (e - 4));
+    float x = 0.f;
+    if (j < a.n && c < a.b) {
+      x = a.V[j * a.ldv + c];
+      if (a.sr != nullptr) x *= a.sr[j];
+    }
+    v[e] = x * scale;
+  }
+  uintx4 hw, lw;
+#pragma unroll
+  for (int e = 0; e < 8; e += 2) {
+    unsigned h, l;
+    split2(v[e], v[e + 1], h, l);
+    hw[e / 2] = h;
+    lw[e / 2] = l;
+  }
+  VSplit out;
+  out.hi = __builtin_bit_cast(halfx8, hw);
+  out.lo = __builtin_bit_cast(halfx8, lw);
+  a.vp[idx] = out;
+}
+
+// The flag word of a call from the prologue's words (one workgroup).
+__device__ __forceinline__ void pack_flag(const int* __restrict__ flags, int nflags,
+                                          int* __restrict__ flag) {
+  int bad = 0;
+  for (int k = threadIdx.x; k < nflags; k += PACK_THREADS) bad |= flags[k];
+  bad = __syncthreads_or(bad);
+  if (threadIdx.x == 0) *flag = bad;
+}
+
+// Columns side by side in a row-major sweep: the power of two >= b.
+inline int column_lanes(int64_t b) {
+  int tc = 1;
+  while (tc < b) tc *= 2;
+  return tc;
+}
+
+// Means of the D columns from the prologue's partial sums, in LDS (mu: MAX_D
+// doubles, red: 128 doubles); every workgroup of every kernel adds
+// them in the same order (two teams; workgroups of at least 128 threads).
+__device__ __forceinline__ void centre_means(const double* __restrict__ part, int nblk, int D,
+                                             int64_t n, double* mu, double* red) {
+  const int f = int(threadIdx.x) % 64, team = int(threadIdx.x) / 64;
+  double acc = 0.0;
+  if (f < D && team < 2) {
+#pragma unroll 8
+    for (int k = team; k < nblk; k += 2) acc += part[int64_t(k) * D + f];
+  }
+  if (team < 2) red[threadIdx.x] = acc;
+  __syncthreads();
+  if (int(threadIdx.x) < D) mu[threadIdx.x] = (red[threadIdx.x] + red[64 + threadIdx.x]) / double(n);
+  __syncthreads();
+}
+
+// Raises *r2max (float64 bits; non-negative values order like them) to the
+// wave's maximum.  The word only grows during a launch, so a wave that reads a
+// value at least as large has nothing to add; most do after the first few.
+__device__ __forceinline__ void raise_r2max(double r, unsigned long long* r2max) {
+  for (int o = 32; o > 0; o >>= 1) r = fmax(r, __shfl_xor(r, o));
+  if ((threadIdx.x & 63) != 0) return;
+  const unsigned long long bits = static_cast<unsigned long long>(__double_as_longlong(r));
+  if (r > 0.0 && bits > __hip_atomic_load(r2max, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT))
+    atomicMax(r2max, bits);
+}
+
 inline unsigned blocks_for(int64_t n, int t) { return unsigned(ceil_div(n, t)); }
 
 // ---------------------------------------------------------------- float32 path
@@ -90,15 +232,15 @@ int hx_recipe_for(int64_t D);
 int hx_col_chunks(int rid);
 int hx_row_chunks(int rid);
 
-void launch_pack_points_hx(const float* X, int64_t n, int64_t D, int64_t ldx, double beta,
-                           bool row_side, PointPack& out, const CentreWs* centre,
-                           hipStream_t stream);
+void launch_packs_hx(const PackIn& in, const PackV& v, PointPack& rows, PointPack& cols,
+                     const CentreWs& centre, hipStream_t stream);
 // Recipe that keeps all three offset pieces for a short recipe that drops the
 // third (-1: the recipe keeps them).
 int hx_full_offset_recipe(int rid);
 void launch_product_hx(const KVPlan& p, const PointPack& rows, const PointPack& cols,
                        const float* vp, const float* colscale, bool diag, const float* sl,
-                       float* Y, int64_t ldy, int b, float* part, hipStream_t stream);
+                       float* Y, int64_t ldy, int b, float* part, const PoisonGate& poison,
+                       hipStream_t stream);
 void launch_rowsum_hx(const KVPlan& p, const PointPack& rows, const PointPack& cols,
                       const float* wp, bool diag, float* out, float* part, hipStream_t stream);
 // Symmetric row sums of one point set (rows.n == cols.n): per-split row partials

@@ -53,43 +53,195 @@ PointPack carve_pack(Arena& a, int64_t n, int dp, int64_t pad) {
   return p;
 }
 
-// ------------------------------------------------------------------ centring
+// ------------------------------------------------------------------ prologue
+//
+// One launch reads everything a call's packs depend on: the column sums of X
+// (float64), whether X (and a second point set X2) is finite, and the column
+// maxima of sr V.  These are reductions over inputs of at most a few hundred MB
+// in front of an N^2 pass, so what counts is the number of launches and the
+// latency of each, not their bandwidth: workgroups own consecutive rows, the
+// lanes of a wave lie along the columns (coalesced; the earlier sums, one
+// column after the other with lanes along the rows, took 61 us at 5,003 x 30
+// and 101 us at 65,536 x 32), four rows in flight per lane, and every
+// workgroup leaves its partial result for the consumer to add, so that nothing
+// has to be cleared beforehand.
 
-// Column partial sums of X rows [blk rpb, (blk + 1) rpb) in float64.
-__global__ void centre_sum_kernel(const float* __restrict__ X, int64_t n, int D, int64_t ldx,
-                                  int64_t rpb, double* __restrict__ part) {
-  __shared__ double red[256];
-  const int64_t r0 = int64_t(blockIdx.x) * rpb;
-  const int64_t r1 = min(n, r0 + rpb);
-  for (int f = 0; f < D; ++f) {
-    double acc = 0.0;
-    for (int64_t i = r0 + threadIdx.x; i < r1; i += blockDim.x) acc += double(X[i * ldx + f]);
-    red[threadIdx.x] = acc;
-    __syncthreads();
-    for (int w = 128; w > 0; w >>= 1) {
-      if (int(threadIdx.x) < w) red[threadIdx.x] += red[threadIdx.x + w];
-      __syncthreads();
+constexpr int PRO_BLOCKS = 128;     // workgroups per point set
+constexpr int PRO_MIN_ROWS = 128;   // rows a workgroup should at least have
+
+static int prologue_blocks(int64_t n) {
+  return int(std::min<int64_t>(PRO_BLOCKS, std::max<int64_t>(1, ceil_div(n, PRO_MIN_ROWS))));
+}
+
+int64_t vmax_blocks(int64_t n) {
+  return std::min<int64_t>(VMAX_BLOCKS, std::max<int64_t>(1, ceil_div(n, PRO_MIN_ROWS)));
+}
+
+__device__ __forceinline__ bool x_load(const float* X, int64_t e, float& v) {
+  v = X[e];
+  return isfinite(v);
+}
+__device__ __forceinline__ bool x_load(const uint16_t* X, int64_t e, float& v) {
+  const uint32_t u = X[e];
+  v = __uint_as_float(u << 16);
+  return (u & 0x7F80u) != 0x7F80u;
+}
+
+struct PrologueArgs {
+  const void* X;
+  const void* X2;
+  int64_t n, n2, ldx;
+  int D, tcx, nblk, nblk2;
+  double* part;
+  unsigned long long* r2max;
+  int* flags;
+  const float* V;
+  const float* sr;
+  int64_t nv, ldv;
+  int b, tcv, nblkv;
+  float* vpart;
+};
+
+// Rows [blk rpb, (blk + 1) rpb) of X: whether they are finite and, with part,
+// their column sums (thread (row lane, column); four rows in flight).
+template <typename T>
+__device__ __forceinline__ void prologue_points(const T* __restrict__ X, int64_t n, int D,
+                                                int64_t ldx, int tc, int nblk, int blk,
+                                                double* __restrict__ part, int* __restrict__ flag,
+                                                double* red) {
+  const int f = int(threadIdx.x) % tc, rl = int(threadIdx.x) / tc, nrl = 256 / tc;
+  const int64_t rpb = (n + nblk - 1) / nblk;
+  const int64_t r0 = int64_t(blk) * rpb, r1 = min(n, r0 + rpb);
+  double acc = 0.0;
+  bool ok = true;
+  if (f < D) {
+    for (int64_t i = r0 + rl; i < r1; i += 4 * nrl) {
+      float v[4];
+      bool fin[4];
+#pragma unroll
+      for (int u = 0; u < 4; ++u) fin[u] = x_load(X, min(i + u * nrl, r1 - 1) * ldx + f, v[u]);
+#pragma unroll
+      for (int u = 0; u < 4; ++u) {
+        ok = ok && fin[u];
+        if (i + u * nrl < r1) acc += double(v[u]);
+      }
     }
-    if (threadIdx.x == 0) part[int64_t(blockIdx.x) * D + f] = red[0];
+  }
+  const int bad = __syncthreads_or(ok ? 0 : 1);
+  if (threadIdx.x == 0) *flag = bad;
+  if (part == nullptr) return;
+  red[threadIdx.x] = acc;
+  __syncthreads();
+  for (int w = 128; w >= tc; w >>= 1) {
+    if (int(threadIdx.x) < w) red[threadIdx.x] += red[threadIdx.x + w];
     __syncthreads();
   }
+  if (int(threadIdx.x) < D) part[int64_t(blk) * D + threadIdx.x] = red[threadIdx.x];
 }
 
-// mu = column means (fixed order over the blocks); clears r2max.
-__global__ void centre_mean_kernel(const double* __restrict__ part, int nblk, int D, int64_t n,
-                                   double* __restrict__ mu, unsigned long long* r2max) {
-  const int f = threadIdx.x;
-  if (f == 0) *r2max = 0ull;
-  if (f >= D) return;
-  double acc = 0.0;
-  for (int b = 0; b < nblk; ++b) acc += part[int64_t(b) * D + f];
-  mu[f] = acc / double(n);
+// Largest |sr_j V[j][c]| per column c over the workgroup's rows.
+__device__ __forceinline__ void prologue_vmax(const PrologueArgs& a, int blk, float* red) {
+  const int c = int(threadIdx.x) % a.tcv, rl = int(threadIdx.x) / a.tcv, nrl = 256 / a.tcv;
+  const int64_t rpb = (a.nv + a.nblkv - 1) / a.nblkv;
+  const int64_t r0 = int64_t(blk) * rpb, r1 = min(a.nv, r0 + rpb);
+  float m = 0.f;
+  if (c < a.b) {
+    for (int64_t i = r0 + rl; i < r1; i += 4 * nrl) {
+      float v[4];
+#pragma unroll
+      for (int u = 0; u < 4; ++u) {
+        const int64_t r = min(i + u * nrl, r1 - 1);
+        v[u] = a.V[r * a.ldv + c];
+        if (a.sr != nullptr) v[u] *= a.sr[r];
+      }
+#pragma unroll
+      for (int u = 0; u < 4; ++u) m = fmaxf(m, fabsf(v[u]));
+    }
+  }
+  red[threadIdx.x] = m;
+  __syncthreads();
+  for (int w = 128; w >= a.tcv; w >>= 1) {
+    if (int(threadIdx.x) < w) red[threadIdx.x] = fmaxf(red[threadIdx.x], red[threadIdx.x + w]);
+    __syncthreads();
+  }
+  if (int(threadIdx.x) < a.b) a.vpart[blk * 64 + threadIdx.x] = red[threadIdx.x];
 }
 
-// r2max = max(r2max, max_i ||x_i - mu||^2) over X[0:n] (non-negative float64
-// values order like their bit patterns, so an integer atomic max serves).
-__global__ void radius_max_kernel(const float* __restrict__ X, int64_t n, int D, int64_t ldx,
-                                  const double* __restrict__ mu, unsigned long long* r2max) {
+// Workgroups [0, nblk): X; [nblk, nblk + nblk2): X2; the rest: V.
+template <typename T>
+__global__ __launch_bounds__(256) void prologue_kernel(PrologueArgs a) {
+  __shared__ double red[256];
+  int blk = int(blockIdx.x);
+  if (blk == 0 && threadIdx.x == 0 && a.r2max != nullptr) *a.r2max = 0ull;
+  if (blk < a.nblk) {
+    prologue_points<T>(static_cast<const T*>(a.X), a.n, a.D, a.ldx, a.tcx, a.nblk, blk, a.part,
+                       a.flags + blk, red);
+    return;
+  }
+  blk -= a.nblk;
+  if (blk < a.nblk2) {
+    prologue_points<T>(static_cast<const T*>(a.X2), a.n2, a.D, a.ldx, a.tcx, a.nblk2, blk, nullptr,
+                       a.flags + a.nblk + blk, red);
+    return;
+  }
+  prologue_vmax(a, blk - a.nblk2, reinterpret_cast<float*>(red));
+}
+
+CentreWs carve_centre(Arena& a, int64_t n, int64_t n2) {
+  CentreWs c;
+  c.nblk = prologue_blocks(n);
+  c.nblk2 = n2 > 0 ? prologue_blocks(n2) : 0;
+  c.part = a.take<double>(size_t(c.nblk) * MAX_D);
+  c.r2max = a.take<unsigned long long>(1);
+  c.flags = a.take<int>(size_t(c.nblk) + size_t(c.nblk2));
+  return c;
+}
+
+void launch_prologue(const PrologueIn& in, CentreWs& c, FSpan vscale, hipStream_t stream) {
+  PrologueArgs a{};
+  a.X = in.X;
+  a.X2 = in.X2;
+  a.n = in.n;
+  a.n2 = in.n2;
+  a.ldx = in.ldx;
+  a.D = int(in.D);
+  a.nblk = in.X != nullptr ? prologue_blocks(in.n) : 0;
+  a.nblk2 = in.X2 != nullptr ? prologue_blocks(in.n2) : 0;
+  FD_REQUIRE(a.nblk <= c.nblk && a.nblk2 <= c.nblk2 && in.D <= MAX_D && in.b <= MAX_B,
+             FD_ERR_INVALID_ARG, "internal: prologue workspace");
+  a.tcx = a.nblk > 0 ? column_lanes(in.D) : 1;
+  a.part = in.xt == FD_F32 ? c.part : nullptr;
+  a.r2max = a.nblk > 0 ? c.r2max : nullptr;
+  a.flags = c.flags;
+  if (in.V != nullptr) {
+    check_span(vscale, VSCALE_FLOATS, "column scales");
+    a.V = in.V;
+    a.sr = in.sr;
+    a.nv = in.nv;
+    a.ldv = in.ldv;
+    a.b = int(in.b);
+    a.tcv = column_lanes(in.b);
+    a.nblkv = int(vmax_blocks(in.nv));
+    a.vpart = vscale.p + 64;
+  }
+  c.n = in.n;
+  c.used = a.nblk;
+  c.used2 = a.nblk2;
+  const dim3 grid{unsigned(a.nblk + a.nblk2 + a.nblkv)};
+  if (in.xt == FD_BF16)
+    hipLaunchKernelGGL(prologue_kernel<uint16_t>, grid, dim3(256), 0, stream, a);
+  else
+    hipLaunchKernelGGL(prologue_kernel<float>, grid, dim3(256), 0, stream, a);
+  FD_LAUNCH_CHECK();
+}
+
+// r2max = max_i ||x_i - mu||^2 over X[0:n] (raise_r2max).
+__global__ __launch_bounds__(256) void radius_max_kernel(const float* __restrict__ X, int64_t n,
+                                                         int D, int64_t ldx,
+                                                         const double* __restrict__ part, int nblk,
+                                                         unsigned long long* r2max) {
+  __shared__ double mu[MAX_D], red[128];
+  centre_means(part, nblk, D, n, mu, red);
   double best = 0.0;
   for (int64_t i = int64_t(blockIdx.x) * blockDim.x + threadIdx.x; i < n;
        i += int64_t(gridDim.x) * blockDim.x) {
@@ -98,61 +250,22 @@ __global__ void radius_max_kernel(const float* __restrict__ X, int64_t n, int D,
       const double v = double(X[i * ldx + f]) - mu[f];
       r += v * v;
     }
-    best = r > best ? r : best;  // a NaN row is skipped; the non-finite scan reports it
+    best = r > best ? r : best;  // a NaN row is skipped; the flag words report it
   }
-  for (int o = 32; o > 0; o >>= 1) best = fmax(best, __shfl_xor(best, o));
-  if ((threadIdx.x & 63) == 0 && best > 0.0)
-    atomicMax(r2max, static_cast<unsigned long long>(__double_as_longlong(best)));
+  raise_r2max(best, r2max);
 }
 
-static int centre_blocks(int64_t n) {
-  return int(std::min<int64_t>(256, std::max<int64_t>(1, ceil_div(n, 4096))));
-}
-
-CentreWs carve_centre(Arena& a, int64_t n) {
-  CentreWs c;
-  c.nblk = centre_blocks(n);
-  c.part = a.take<double>(size_t(c.nblk) * MAX_D);
-  c.mu = a.take<double>(MAX_D);
-  c.r2max = a.take<unsigned long long>(1);
-  return c;
-}
-
-void launch_centre(const void* X, fd_dtype xt, int64_t n, int64_t D, int64_t ldx,
+void launch_radius(const void* X, fd_dtype xt, int64_t n, int64_t D, int64_t ldx,
                    const CentreWs& c, hipStream_t stream) {
   if (xt != FD_F32) return;
-  FD_REQUIRE(c.part != nullptr && c.mu != nullptr && c.r2max != nullptr && D <= MAX_D &&
-                 centre_blocks(n) <= c.nblk,
-             FD_ERR_INVALID_ARG, "internal: centring workspace");
-  const int nblk = centre_blocks(n);
-  const int64_t rpb = ceil_div(n, nblk);
-  const float* Xf = static_cast<const float*>(X);
-  hipLaunchKernelGGL(centre_sum_kernel, dim3(nblk), dim3(256), 0, stream, Xf, n, int(D), ldx,
-                     rpb, c.part);
-  FD_LAUNCH_CHECK();
-  hipLaunchKernelGGL(centre_mean_kernel, dim3(1), dim3(64), 0, stream, c.part, nblk, int(D), n,
-                     c.mu, c.r2max);
-  FD_LAUNCH_CHECK();
-  launch_radius_more(X, xt, n, D, ldx, c, stream);
-}
-
-void launch_radius_more(const void* X2, fd_dtype xt, int64_t n2, int64_t D, int64_t ldx,
-                        const CentreWs& c, hipStream_t stream) {
-  if (xt != FD_F32) return;
-  const unsigned grid = unsigned(std::min<int64_t>(1024, std::max<int64_t>(1, ceil_div(n2, 256))));
+  FD_REQUIRE(c.n == n && c.used > 0, FD_ERR_INVALID_ARG, "internal: radius before the prologue");
+  const unsigned grid = unsigned(std::min<int64_t>(1024, std::max<int64_t>(1, ceil_div(n, 256))));
   hipLaunchKernelGGL(radius_max_kernel, dim3(grid), dim3(256), 0, stream,
-                     static_cast<const float*>(X2), n2, int(D), ldx, c.mu, c.r2max);
+                     static_cast<const float*>(X), n, int(D), ldx, c.part, c.used, c.r2max);
   FD_LAUNCH_CHECK();
 }
 
 // ------------------------------------------------------------------ exponent range
-
-// f2: the square of the larger coordinate scale (s or 2 beta log2(e) / s)
-__global__ void range_check_kernel(const unsigned long long* __restrict__ r2max, double bl,
-                                   double f2, int* __restrict__ flag) {
-  const double r2 = __longlong_as_double(static_cast<long long>(*r2max));
-  if (!(bl * r2 <= HX_EXP_RANGE && f2 * r2 <= HX_PIECE_MAX * HX_PIECE_MAX)) atomicOr(flag, 2);
-}
 
 static double coord_scale_sq(double beta) {
   const double s = hx_coord_scale(beta);
@@ -186,14 +299,15 @@ void require_exponent_range(fd_dtype xt, const CentreWs& c, double beta, hipStre
                     std::to_string(HX_EXP_RANGE) + ", coordinate pieces up to 65504)"};
 }
 
-void launch_range_check(fd_dtype xt, const CentreWs& c, double beta, int* flag,
-                        hipStream_t stream) {
-  if (xt != FD_F32) return;
-  FD_REQUIRE(c.r2max != nullptr && flag != nullptr, FD_ERR_INVALID_ARG,
-             "internal: range check words");
-  hipLaunchKernelGGL(range_check_kernel, dim3(1), dim3(1), 0, stream, c.r2max, beta * LOG2E,
-                     coord_scale_sq(beta), flag);
-  FD_LAUNCH_CHECK();
+PoisonGate poison_gate(fd_dtype xt, const CentreWs& c, double beta, const int* flag) {
+  PoisonGate g;
+  g.flag = flag;
+  if (xt == FD_F32) {
+    g.r2max = c.r2max;
+    g.bl = beta * LOG2E;
+    g.f2 = coord_scale_sq(beta);
+  }
+  return g;
 }
 
 // ------------------------------------------------------------------ packing
@@ -214,30 +328,14 @@ __global__ void pack_w_kernel(const float* __restrict__ w, int64_t n, int64_t nt
   wp[idx] = out;
 }
 
-// Weight pack of sr * v for a single right-hand side v (stride ldv): the
-// layout of pack_w_kernel.
-__global__ void pack_wv_kernel(const float* __restrict__ v, int64_t ldv,
-                               const float* __restrict__ sr, int64_t n, int64_t ntiles,
-                               floatx4* __restrict__ wp) {
-  const int64_t idx = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
-  if (idx >= ntiles * 64) return;
-  const int lane = int(idx & 63);
-  const int64_t jb = idx >> 6;
-  const int g = lane >> 4;
-  floatx4 out;
-#pragma unroll
-  for (int r = 0; r < 4; ++r) {
-    const int64_t j = jb * TILE + 4 * g + r;
-    out[r] = (j < n) ? (sr != nullptr ? sr[j] * v[j * ldv] : v[j * ldv]) : 0.f;
-  }
-  wp[idx] = out;
-}
-
 // Y[i] = sl[i] * t[i] (sl NULL: copy), Y with row stride ldy.
 __global__ void scale_rows_kernel(const float* __restrict__ t, const float* __restrict__ sl,
-                                  int64_t n, float* __restrict__ Y, int64_t ldy) {
+                                  int64_t n, float* __restrict__ Y, int64_t ldy,
+                                  PoisonGate poison) {
   const int64_t i = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
-  if (i < n) Y[i * ldy] = (sl != nullptr) ? sl[i] * t[i] : t[i];
+  if (i >= n) return;
+  const float y = (sl != nullptr) ? sl[i] * t[i] : t[i];
+  Y[i * ldy] = poisoned(poison) ? __builtin_nanf("") : y;
 }
 
 // 2^t clamped to [0, 1]: the exponent of a true kernel value is <= 0 and
@@ -261,96 +359,9 @@ __device__ __forceinline__ float exp2_unit(float t) {
 // form the 32-wide contraction; the pack stores, per lane (g, p), the 8 rows
 // {4g + r, 16 + 4g + r} of column 16 cb + p as hi and lo halves.
 
-// max |sr_j V[j][c]| per column as float bits (non-negative floats order like
-// their bit patterns, so an integer max is exact and order independent)
-__global__ void vmax_zero_kernel(unsigned* __restrict__ maxbits) {
-  if (threadIdx.x < 64) maxbits[threadIdx.x] = 0u;
-}
-
-// Thread (row lane rl, column c): tc = power of two >= b columns side by side
-// (consecutive addresses of a row), 256 / tc row lanes; the grid strides over
-// the rows, four at a time with their loads issued together; one integer
-// atomicMax per column and workgroup.
-__global__ __launch_bounds__(256) void vmax_kernel(const float* __restrict__ V, int64_t n, int b,
-                                                   int64_t ldv, const float* __restrict__ sr,
-                                                   int tc, unsigned* __restrict__ maxbits) {
-  __shared__ float red[256];
-  const int c = threadIdx.x % tc;
-  const int rl = threadIdx.x / tc;
-  const int nrl = 256 / tc;
-  const int64_t stride = int64_t(gridDim.x) * nrl;
-  float m = 0.f;
-  if (c < b) {
-    for (int64_t i = int64_t(blockIdx.x) * nrl + rl; i < n; i += 4 * stride) {
-      float v[4];
-#pragma unroll
-      for (int u = 0; u < 4; ++u) {
-        const int64_t r = min(i + u * stride, n - 1);
-        v[u] = V[r * ldv + c];
-        if (sr != nullptr) v[u] *= sr[r];
-      }
-#pragma unroll
-      for (int u = 0; u < 4; ++u)
-        if (i + u * stride < n) m = fmaxf(m, fabsf(v[u]));
-    }
-  }
-  red[threadIdx.x] = m;
-  __syncthreads();
-  for (int w = 128; w >= tc; w >>= 1) {
-    if (threadIdx.x < w) red[threadIdx.x] = fmaxf(red[threadIdx.x], red[threadIdx.x + w]);
-    __syncthreads();
-  }
-  if (threadIdx.x < tc) {
-    m = red[threadIdx.x];
-    if (c < b && m > 0.f) atomicMax(&maxbits[c], __float_as_uint(m));
-  }
-}
-
-__device__ __forceinline__ int vscale_exponent(unsigned bits) {
-  if (bits == 0u) return 0;
-  int e;
-  (void)frexpf(__uint_as_float(bits), &e);  // max < 2^e
-  return 14 - e;                            // scaled max < 2^14
-}
-
-__global__ void pack_v_split_kernel(const float* __restrict__ V, int64_t n, int b, int64_t ldv,
-                                    const float* __restrict__ sr, int ncb, int64_t npairs,
-                                    const unsigned* __restrict__ maxbits,
-                                    VSplit* __restrict__ vp, float* __restrict__ colscale) {
-  const int64_t idx = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
-  if (idx >= npairs * ncb * 64) return;
-  const int lane = int(idx & 63);
-  const int cb = int((idx >> 6) % ncb);
-  const int64_t jp = idx / (64 * ncb);
-  const int g = lane >> 4, p = lane & 15;
-  const int c = cb * 16 + p;
-  const int ex = (c < b) ? vscale_exponent(maxbits[c]) : 0;
-  const float scale = ldexpf(1.f, ex);
-  if (jp == 0 && g == 0 && c < b) colscale[c] = ldexpf(1.f, -ex - 15);
-  uintx4 hw, lw;
-#pragma unroll
-  for (int e = 0; e < 8; e += 2) {
-    float v[2];
-#pragma unroll
-    for (int u = 0; u < 2; ++u) {
-      const int ee = e + u;
-      const int64_t j = jp * 32 + (ee < 4 ? 4 * g + ee : 16 + 4 * g + (ee - 4));
-      float x = 0.f;
-      if (j < n && c < b) {
-        x = V[j * ldv + c];
-        if (sr != nullptr) x *= sr[j];
-      }
-      v[u] = x * scale;
-    }
-    unsigned h, l;
-    split2(v[0], v[1], h, l);
-    hw[e / 2] = h;
-    lw[e / 2] = l;
-  }
-  VSplit out;
-  out.hi = __builtin_bit_cast(halfx8, hw);
-  out.lo = __builtin_bit_cast(halfx8, lw);
-  vp[idx] = out;
+__global__ __launch_bounds__(PACK_THREADS) void pack_v_kernel(PackV a) {
+  __shared__ int ex[64];
+  pack_v_block(a, blockIdx.x, ex);
 }
 
 // Column-pair operands: exponent-contraction inputs of two 16-point tiles and
@@ -371,50 +382,89 @@ __global__ void pack_v_split_kernel(const float* __restrict__ V, int64_t n, int 
 // the 8 bfloat16 x[16 tile + p][32 c + 8 g + e], e = 0..7, as one uint4; that
 // is the A operand of the column tile and the B operand of the row tile.
 
-__global__ void norms_bf16_kernel(const uint16_t* __restrict__ X, int64_t n, int D, int64_t ldx,
-                                  float* __restrict__ ap, float* __restrict__ ar, int64_t npad) {
-  const int64_t i = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
-  if (i >= npad) return;
-  double r = 0.0;
-  if (i < n)
-    for (int k = 0; k < D; ++k) {
-      const double x = double(__uint_as_float(uint32_t(X[i * ldx + k]) << 16));
-      r += x * x;
-    }
-  // padded points: a huge negative offset makes their kernel values exactly 0
-  const float a = (i < n) ? float(-0.5 * r) : -1e30f;
-  ar[i] = a;
-  if (ap != nullptr) {
-    const int64_t tile = i / TILE;
-    const int p = int(i % TILE);
-    const int g = p >> 2, rr = p & 3;
-    float* base = ap + (tile * 64 + 16 * g) * 4 + rr;
-    for (int q = 0; q < 16; ++q) base[q * 4] = a;
+// One wave per 16-point tile: lane (g, p) holds eight features of point p per
+// chunk, sums their squares in float64 (exact products) and adds the four lanes
+// of a point.  Workgroups [0, nbr): the row pack, then the column pack, then V.
+struct PackBf16Side {
+  const uint16_t* X;
+  int64_t n, ntiles;
+  uintx4* xp;
+  float* ar;      // row side: offsets per point
+  floatx4* ap;    // column side: offsets in accumulator order
+};
+struct PackBf16Args {
+  PackBf16Side row, col;
+  int64_t ldx, nbr, nbc;
+  int D, dc, vec;
+  const int* flags;
+  int nflags;
+  int* flag;
+  PackV v;
+  unsigned long long *zero1, *zero2;
+  int64_t nzero;
+};
+__global__ __launch_bounds__(PACK_THREADS) void pack_bf16_kernel(PackBf16Args a) {
+  __shared__ int ex[64];
+  int64_t blk = blockIdx.x;
+  if (blk == 0 && a.flag != nullptr) pack_flag(a.flags, a.nflags, a.flag);
+  if (blk >= a.nbr + a.nbc) {
+    pack_v_block(a.v, blk - a.nbr - a.nbc, ex);
+    return;
   }
-}
-
-__global__ void pack_bf16_kernel(const uint16_t* __restrict__ X, int64_t n, int D, int64_t ldx,
-                                 int dc, int64_t ntiles, uintx4* __restrict__ xp) {
-  const int64_t idx = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
-  if (idx >= ntiles * dc * 64) return;
-  const int lane = int(idx & 63);
-  const int c = int((idx >> 6) % dc);
-  const int64_t tile = idx / (64 * dc);
-  const int g = lane >> 4, p = lane & 15;
+  const bool row_side = blk < a.nbr;
+  if (row_side) {
+    const int64_t z = blk * PACK_THREADS + threadIdx.x;
+    // a workgroup clears 1/nbr of the words
+    for (int64_t e = z; e < a.nzero; e += a.nbr * PACK_THREADS) {
+      if (a.zero1 != nullptr) a.zero1[e] = 0ull;
+      if (a.zero2 != nullptr) a.zero2[e] = 0ull;
+    }
+  }
+  const PackBf16Side s = row_side ? a.row : a.col;
+  if (!row_side) blk -= a.nbr;
+  const int lane = threadIdx.x & 63, g = lane >> 4, p = lane & 15;
+  const int64_t tile = blk * (PACK_THREADS / 64) + (threadIdx.x >> 6);
+  if (tile >= s.ntiles) return;
   const int64_t i = tile * TILE + p;
-  uintx4 out;
+  const bool real = i < s.n;
+  const uint16_t* xi = s.X + min(i, s.n - 1) * a.ldx;
+  double r = 0.0;
+  for (int c = 0; c < a.dc; ++c) {
+    const int k0 = 32 * c + 8 * g;
+    uintx4 out = uintx4{0u, 0u, 0u, 0u};
+    if (a.vec && k0 + 8 <= a.D) {
+      out = *reinterpret_cast<const uintx4*>(xi + k0);
+    } else {
 #pragma unroll
-  for (int w = 0; w < 4; ++w) {
-    uint32_t word = 0;
+      for (int w = 0; w < 4; ++w)
 #pragma unroll
-    for (int h = 0; h < 2; ++h) {
-      const int k = 32 * c + 8 * g + 2 * w + h;
-      const uint32_t v = (i < n && k < D) ? uint32_t(X[i * ldx + k]) : 0u;
-      word |= v << (16 * h);
+        for (int h = 0; h < 2; ++h) {
+          const int k = k0 + 2 * w + h;
+          const uint32_t v = uint32_t(xi[min(k, a.D - 1)]);
+          out[w] |= (k < a.D ? v : 0u) << (16 * h);
+        }
     }
-    out[w] = word;
+    if (!real) out = uintx4{0u, 0u, 0u, 0u};
+#pragma unroll
+    for (int w = 0; w < 4; ++w) {
+      const double lo = double(__uint_as_float(out[w] << 16));
+      const double hi = double(__uint_as_float(out[w] & 0xFFFF0000u));
+      r += lo * lo;
+      r += hi * hi;
+    }
+    s.xp[(tile * a.dc + c) * 64 + lane] = out;
   }
-  xp[idx] = out;
+  r += __shfl_xor(r, 16);
+  r += __shfl_xor(r, 32);
+  // padded points: a huge negative offset makes their kernel values exactly 0
+  const float off = real ? float(-0.5 * r) : -1e30f;
+  if (s.ar != nullptr && g == 0) s.ar[i] = off;
+  if (s.ap != nullptr) {
+    floatx4 q;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) q[e] = __shfl(off, 4 * g + e);
+    s.ap[tile * 64 + lane] = q;
+  }
 }
 
 
@@ -543,7 +593,7 @@ __attribute__((amdgpu_waves_per_eu(bf16_waves<DC, NCB, NIB>()))) void product_bf
     const uintx4* __restrict__ xb, const float* __restrict__ ar, int64_t nrt, int64_t njp,
     int64_t jp_per_split, int diag, float scale2, const float* __restrict__ colscale,
     const float* __restrict__ sl, float* __restrict__ Y, int64_t ldy, int64_t Nr, int b,
-    float* __restrict__ part, int64_t nrpad) {
+    float* __restrict__ part, int64_t nrpad, PoisonGate poison) {
   __shared__ floatx4 tot[4][NIB][NCB][64];
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -676,7 +726,7 @@ __attribute__((amdgpu_waves_per_eu(bf16_waves<DC, NCB, NIB>()))) void product_bf
           part[(split * nrpad + i) * (NCB * 16) + c] = v[e];
         } else if (i < Nr && c < b) {
           const float y = v[e] * colscale[c];
-          Y[i * ldy + c] = (sl != nullptr) ? y * sl[i] : y;
+          Y[i * ldy + c] = poisoned(poison) ? __builtin_nanf("") : (sl != nullptr) ? y * sl[i] : y;
         }
       }
     }
@@ -764,19 +814,58 @@ rowsum_bf16_kernel(
   }
 }
 
-__global__ void reduce_product_kernel(const float* __restrict__ part, int nsplit, int64_t nrpad,
-                                      int width, const float* __restrict__ colscale,
-                                      const float* __restrict__ sl, float* __restrict__ Y,
-                                      int64_t ldy, int64_t Nr, int b) {
-  const int64_t idx = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
-  if (idx >= Nr * b) return;
-  const int64_t i = idx / b;
-  const int c = int(idx % b);
-  double s = 0.0;
-  for (int k = 0; k < nsplit; ++k) s += double(part[(k * nrpad + i) * width + c]);
-  if (colscale != nullptr) s *= double(colscale[c]);
-  if (sl != nullptr) s *= double(sl[i]);
-  Y[i * ldy + c] = float(s);
+// Y = diag(sl) (sum over splits of part) diag(colscale), NaN where the call is
+// poisoned.  A thread sums four consecutive columns of a row over every
+// TEAMS-th split (float64, one 16-byte load per split); the teams are added in
+// LDS in a fixed order.  Small outputs take more teams: a chain of up to 64
+// dependent loads per thread is what their time was (6-12 us below 2^13 rows).
+template <int TEAMS>
+__global__ __launch_bounds__(256) void reduce_product_kernel(
+    const float* __restrict__ part, int nsplit, int64_t nrpad, int width,
+    const float* __restrict__ colscale, const float* __restrict__ sl, float* __restrict__ Y,
+    int64_t ldy, int64_t Nr, int b, int vec, PoisonGate poison) {
+  constexpr int OUT = 256 / TEAMS;
+  __shared__ double red[TEAMS > 1 ? TEAMS : 1][TEAMS > 1 ? OUT : 1][4];
+  const int o = int(threadIdx.x) % OUT, team = int(threadIdx.x) / OUT;
+  const int quads = (b + 3) / 4;
+  const int64_t idx = int64_t(blockIdx.x) * OUT + o;
+  const bool live = idx < Nr * quads;
+  const int64_t i = live ? idx / quads : 0;
+  const int c = live ? 4 * int(idx % quads) : 0;
+  double s[4] = {0.0, 0.0, 0.0, 0.0};
+  const float* src = part + i * width + c;
+#pragma unroll 4
+  for (int k = team; k < nsplit; k += TEAMS) {
+    const floatx4 v = *reinterpret_cast<const floatx4*>(src + int64_t(k) * nrpad * width);
+#pragma unroll
+    for (int e = 0; e < 4; ++e) s[e] += double(v[e]);
+  }
+  if constexpr (TEAMS > 1) {
+#pragma unroll
+    for (int e = 0; e < 4; ++e) red[team][o][e] = s[e];
+    __syncthreads();
+    if (team != 0) return;
+#pragma unroll
+    for (int k = 1; k < TEAMS; ++k)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) s[e] += red[k][o][e];
+  }
+  if (!live) return;
+  const bool bad = poisoned(poison);
+  floatx4 out;
+#pragma unroll
+  for (int e = 0; e < 4; ++e) {
+    double v = s[e] * double(colscale[min(c + e, b - 1)]);
+    if (sl != nullptr) v *= double(sl[i]);
+    out[e] = bad ? __builtin_nanf("") : float(v);
+  }
+  if (vec && c + 4 <= b) {
+    *reinterpret_cast<floatx4*>(Y + i * ldy + c) = out;
+    return;
+  }
+#pragma unroll
+  for (int e = 0; e < 4; ++e)
+    if (c + e < b) Y[i * ldy + c + e] = out[e];
 }
 
 __global__ void reduce_rowsum_kernel(const float* __restrict__ part, int nsplit, int64_t nrpad,
@@ -788,22 +877,29 @@ __global__ void reduce_rowsum_kernel(const float* __restrict__ part, int nsplit,
   out[i] = float(s);
 }
 
-// Symmetric row sums: out_i = sum over splits of the row partials + the
-// fixed-point column sums (colfix * 2^-F), in double, fixed order.
-__global__ void reduce_rowsum_sym_kernel(const float* __restrict__ part, int nsplit,
-                                         int64_t nrpad, const unsigned long long* __restrict__ colfix,
-                                         double inv_fix, float* __restrict__ out, int64_t Nr) {
-  const int64_t i = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
-  if (i >= Nr) return;
-  double s = 0.0;
-  for (int k = 0; k < nsplit; ++k) s += double(part[k * nrpad + i]);
-  s += double(static_cast<long long>(colfix[i])) * inv_fix;
-  out[i] = float(s);
+// Sum of v over the workgroup of 256 threads (fixed order); on thread 0.
+__device__ __forceinline__ double block_sum_256(double v, double* red) {
+  red[threadIdx.x] = v;
+  __syncthreads();
+  for (int w = 128; w > 0; w >>= 1) {
+    if (int(threadIdx.x) < w) red[threadIdx.x] += red[threadIdx.x + w];
+    __syncthreads();
+  }
+  const double s = red[0];
+  __syncthreads();
+  return s;
 }
 
-__global__ void zero_u64_kernel(unsigned long long* __restrict__ p, int64_t n) {
-  const int64_t i = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
-  if (i < n) p[i] = 0ull;
+// s_off = sum(q) - n from the partial sums of q (one workgroup of 256, fixed
+// order).
+__device__ __forceinline__ void finish_s_off(const double* __restrict__ qsum, int64_t nq,
+                                             int64_t n, double* __restrict__ s_off, bool bad,
+                                             double* red) {
+  double v = 0.0;
+#pragma unroll 4
+  for (int64_t k = threadIdx.x; k < nq; k += 256) v += qsum[k];
+  v = block_sum_256(v, red);
+  if (threadIdx.x == 0) *s_off = bad ? __builtin_nan("") : v - double(n);
 }
 
 // w = q^-alpha
@@ -814,68 +910,87 @@ __global__ void pow_neg_kernel(const float* __restrict__ q, int64_t n, double al
 }
 
 // d = w * t, s = w * d^-1/2 (w = q^-alpha recomputed in double from q)
-__global__ void degree_finish_kernel(const float* __restrict__ q, const float* __restrict__ t,
-                                     int64_t n, double alpha, float* __restrict__ d,
-                                     float* __restrict__ s) {
+__global__ __launch_bounds__(256) void degree_finish_kernel(
+    const float* __restrict__ q, const float* __restrict__ t, int64_t n, double alpha,
+    float* __restrict__ d, float* __restrict__ s, const double* __restrict__ qsum, int64_t nq,
+    double* __restrict__ s_off, PoisonGate poison) {
+  __shared__ double red[256];
+  const bool bad = poisoned(poison);
+  if (blockIdx.x == 0 && s_off != nullptr) finish_s_off(qsum, nq, n, s_off, bad, red);
   const int64_t i = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
   if (i >= n) return;
   const double w = pow(double(q[i]), -alpha);
   const double dd = w * double(t[i]);
-  if (d != nullptr) d[i] = float(dd);
-  if (s != nullptr) s[i] = float(w / sqrt(dd));
+  if (d != nullptr) d[i] = bad ? __builtin_nanf("") : float(dd);
+  if (s != nullptr) s[i] = bad ? __builtin_nanf("") : float(w / sqrt(dd));
 }
 
 // The two normalisation passes on the symmetric path with their epilogues in
 // the reductions (same arithmetic, in the same order, as reduce_rowsum_sym +
 // pow_neg + pack_w and reduce_rowsum_sym + degree_finish).  One thread per
 // padded point; each clears its fixed-point column sum for the next pass.
-// Pass 1: q_i, and if wpk is set w_i = q_i^-alpha written to the weight pack
-// (pack_w_kernel's layout: w_j in lanes 16 g + p, p = 0..15, component r of
-// tile j / 16, j % 16 = 4 g + r; 0 for padding points) for the wnpad points
-// of the column pack.
-__global__ void degree_reduce_q_kernel(const float* __restrict__ part, int nsplit, int64_t nrpad,
-                                       unsigned long long* __restrict__ colfix, double inv_fix,
-                                       float* __restrict__ q, int64_t n, int64_t npad,
-                                       double alpha, float* __restrict__ wpk, int64_t wnpad) {
-  const int64_t i = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
-  if (i >= npad) return;
-  float w = 0.f;
-  if (i < n) {
-    double sum = 0.0;
-    for (int k = 0; k < nsplit; ++k) sum += double(part[k * nrpad + i]);
-    sum += double(static_cast<long long>(colfix[i])) * inv_fix;
-    const float qi = float(sum);
-    q[i] = qi;
-    w = float(pow(double(qi), -alpha));
-  }
-  colfix[i] = 0ull;
-  if (wpk != nullptr && i < wnpad) {
-    const int64_t jb = i / TILE;
-    const int jj = int(i % TILE), g = jj / 4, r = jj % 4;
-    float* base = wpk + (jb * 64 + 16 * g) * 4 + r;
+
+// Row sum of point i: the split partials, then the fixed-point column sum.
+__device__ __forceinline__ double sym_row_total(const float* __restrict__ part, int nsplit,
+                                                int64_t nrpad, unsigned long long col,
+                                                double inv_fix, int64_t i) {
+  double sum = 0.0;
+#pragma unroll 8
+  for (int k = 0; k < nsplit; ++k) sum += double(part[k * nrpad + i]);
+  return sum + double(static_cast<long long>(col)) * inv_fix;
+}
+
+// w_j into the weight pack (pack_w_kernel's layout: w_j in lanes 16 g + p,
+// p = 0..15, component r of tile j / 16, j % 16 = 4 g + r).
+__device__ __forceinline__ void put_weight(float* __restrict__ wpk, int64_t i, float w) {
+  const int64_t jb = i / TILE;
+  const int jj = int(i % TILE), g = jj / 4, r = jj % 4;
+  float* base = wpk + (jb * 64 + 16 * g) * 4 + r;
 #pragma unroll
-    for (int p = 0; p < 16; ++p) base[4 * p] = w;
+  for (int p = 0; p < 16; ++p) base[4 * p] = w;
+}
+
+// Pass 1: q_i, and if wpk is set w_i = q_i^-alpha written to the weight pack
+// (0 for padding points) for the wnpad points of the column pack.  qsum: the
+// workgroup's sum of q.
+__global__ __launch_bounds__(256) void degree_reduce_q_kernel(
+    const float* __restrict__ part, int nsplit, int64_t nrpad,
+    unsigned long long* __restrict__ colfix, double inv_fix, float* __restrict__ q, int64_t n,
+    int64_t npad, double alpha, float* __restrict__ wpk, int64_t wnpad, double* __restrict__ qsum,
+    PoisonGate poison) {
+  __shared__ double red[256];
+  const int64_t i = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
+  float qi = 0.f, w = 0.f;
+  if (i < n) {
+    qi = float(sym_row_total(part, nsplit, nrpad, colfix[i], inv_fix, i));
+    w = float(pow(double(qi), -alpha));
+    q[i] = poisoned(poison) ? __builtin_nanf("") : qi;
   }
+  if (i < npad) colfix[i] = 0ull;
+  if (wpk != nullptr && i < wnpad) put_weight(wpk, i, w);
+  const double s = block_sum_256(double(qi), red);
+  if (threadIdx.x == 0) qsum[blockIdx.x] = s;
 }
 
 // Pass 2: t_i (the weighted row sums), then d_i = w_i t_i and
-// s_i = w_i d_i^-1/2 with w_i = q_i^-alpha in double.
-__global__ void degree_reduce_ds_kernel(const float* __restrict__ part, int nsplit, int64_t nrpad,
-                                        unsigned long long* __restrict__ colfix, double inv_fix,
-                                        const float* __restrict__ q, int64_t n, int64_t npad,
-                                        double alpha, float* __restrict__ d,
-                                        float* __restrict__ s) {
+// s_i = w_i d_i^-1/2 with w_i = q_i^-alpha in double.  The first workgroup also
+// finishes s_off.
+__global__ __launch_bounds__(256) void degree_reduce_ds_kernel(
+    const float* __restrict__ part, int nsplit, int64_t nrpad,
+    unsigned long long* __restrict__ colfix, double inv_fix, const float* __restrict__ q,
+    int64_t n, int64_t npad, double alpha, float* __restrict__ d, float* __restrict__ s,
+    const double* __restrict__ qsum, int64_t nq, double* __restrict__ s_off, PoisonGate poison) {
+  __shared__ double red[256];
+  const bool bad = poisoned(poison);
+  if (blockIdx.x == 0 && s_off != nullptr) finish_s_off(qsum, nq, n, s_off, bad, red);
   const int64_t i = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
   if (i >= npad) return;
   if (i < n) {
-    double sum = 0.0;
-    for (int k = 0; k < nsplit; ++k) sum += double(part[k * nrpad + i]);
-    sum += double(static_cast<long long>(colfix[i])) * inv_fix;
-    const float ti = float(sum);
+    const float ti = float(sym_row_total(part, nsplit, nrpad, colfix[i], inv_fix, i));
     const double w = pow(double(q[i]), -alpha);
     const double dd = w * double(ti);
-    if (d != nullptr) d[i] = float(dd);
-    if (s != nullptr) s[i] = float(w / sqrt(dd));
+    if (d != nullptr) d[i] = bad ? __builtin_nanf("") : float(dd);
+    if (s != nullptr) s[i] = bad ? __builtin_nanf("") : float(w / sqrt(dd));
   }
   colfix[i] = 0ull;
 }
@@ -884,43 +999,39 @@ __global__ void degree_reduce_ds_kernel(const float* __restrict__ part, int nspl
 // squared-kernel sums of the same pass the next level's q (K(2 beta) 1, the
 // reduction in the same order as degree_reduce_q_kernel's) with its
 // w = q^-alpha written to the weight pack as degree_reduce_q_kernel writes it.
-__global__ void degree_reduce_dsq_kernel(const float* __restrict__ part, int nsplit,
-                                         int64_t nrpad, unsigned long long* __restrict__ colfix,
-                                         double inv_fix, const float* __restrict__ q, int64_t n,
-                                         int64_t npad, double alpha, float* __restrict__ d,
-                                         float* __restrict__ s, const float* __restrict__ part2,
-                                         unsigned long long* __restrict__ colfix2,
-                                         float* __restrict__ q_next, float* __restrict__ wpk,
-                                         int64_t wnpad) {
+__global__ __launch_bounds__(256) void degree_reduce_dsq_kernel(
+    const float* __restrict__ part, int nsplit, int64_t nrpad,
+    unsigned long long* __restrict__ colfix, double inv_fix, const float* __restrict__ q,
+    int64_t n, int64_t npad, double alpha, float* __restrict__ d, float* __restrict__ s,
+    const float* __restrict__ part2, unsigned long long* __restrict__ colfix2,
+    float* __restrict__ q_next, float* __restrict__ wpk, int64_t wnpad,
+    const double* __restrict__ qsum, int64_t nq, double* __restrict__ s_off,
+    double* __restrict__ qsum_next, PoisonGate poison) {
+  __shared__ double red[256];
+  const bool bad = poisoned(poison);
+  if (blockIdx.x == 0 && s_off != nullptr) finish_s_off(qsum, nq, n, s_off, bad, red);
   const int64_t i = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
-  if (i >= npad) return;
-  float wn = 0.f;
+  float qn = 0.f, wn = 0.f;
   if (i < n) {
-    double sum = 0.0;
-    for (int k = 0; k < nsplit; ++k) sum += double(part[k * nrpad + i]);
-    sum += double(static_cast<long long>(colfix[i])) * inv_fix;
-    const float ti = float(sum);
+    const float ti = float(sym_row_total(part, nsplit, nrpad, colfix[i], inv_fix, i));
     const double w = pow(double(q[i]), -alpha);
     const double dd = w * double(ti);
-    if (d != nullptr) d[i] = float(dd);
-    if (s != nullptr) s[i] = float(w / sqrt(dd));
-    double sum2 = 0.0;
-    for (int k = 0; k < nsplit; ++k) sum2 += double(part2[k * nrpad + i]);
-    sum2 += double(static_cast<long long>(colfix2[i])) * inv_fix;
-    const float qn = float(sum2);
-    q_next[i] = qn;
+    if (d != nullptr) d[i] = bad ? __builtin_nanf("") : float(dd);
+    if (s != nullptr) s[i] = bad ? __builtin_nanf("") : float(w / sqrt(dd));
+    qn = float(sym_row_total(part2, nsplit, nrpad, colfix2[i], inv_fix, i));
+    q_next[i] = bad ? __builtin_nanf("") : qn;
     wn = float(pow(double(qn), -alpha));
   }
-  colfix[i] = 0ull;
-  colfix2[i] = 0ull;
-  if (i < wnpad) {
-    const int64_t jb = i / TILE;
-    const int jj = int(i % TILE), g = jj / 4, r = jj % 4;
-    float* base = wpk + (jb * 64 + 16 * g) * 4 + r;
-#pragma unroll
-    for (int p = 0; p < 16; ++p) base[4 * p] = wn;
+  if (i < npad) {
+    colfix[i] = 0ull;
+    colfix2[i] = 0ull;
   }
+  if (i < wnpad) put_weight(wpk, i, wn);
+  const double sq = block_sum_256(double(qn), red);
+  if (threadIdx.x == 0) qsum_next[blockIdx.x] = sq;
 }
+
+int64_t qsum_words(int64_t npad) { return ceil_div(npad, 256); }
 
 // sum(q) - n in double, one workgroup, fixed order (deterministic)
 __global__ __launch_bounds__(1024) void sum_minus_n_kernel(const float* __restrict__ q, int64_t n,
@@ -1025,43 +1136,99 @@ static inline size_t lane4_extent(int64_t tiles, int groups) {
   return size_t(tiles) * groups * 64 * 4;
 }
 
-static void pack_points_bf16(const uint16_t* X, int64_t n, int64_t D, int64_t ldx, bool row_side,
-                             PointPack& out, hipStream_t stream) {
-  const int dc = int(ceil_div(D, 32));
-  FD_REQUIRE(out.npad % TILE == 0 && out.npad >= n && dc <= 2, FD_ERR_INVALID_ARG,
+static PackBf16Side bf16_side(const void* X, PointPack& out, int dc, bool row_side) {
+  FD_REQUIRE(out.npad % TILE == 0 && out.npad >= out.n && dc <= 2, FD_ERR_INVALID_ARG,
              "internal: bad bf16 pack geometry");
   const int64_t ntiles = out.npad / TILE;
   check_span(out.xp, size_t(ntiles) * dc * 64 * 4, "bf16 point pack");
-  check_span(out.ar, size_t(out.npad), "row offsets");
-  if (!row_side) check_span(out.ap, lane4_extent(ntiles, 1), "column offsets");
-  hipLaunchKernelGGL(norms_bf16_kernel, dim3(blocks_for(out.npad, 256)), dim3(256), 0, stream, X,
-                     n, int(D), ldx, row_side ? nullptr : out.ap.p, out.ar.p, out.npad);
-  FD_LAUNCH_CHECK();
-  hipLaunchKernelGGL(pack_bf16_kernel, dim3(blocks_for(ntiles * dc * 64, 256)), dim3(256), 0,
-                     stream, X, n, int(D), ldx, dc, ntiles, reinterpret_cast<uintx4*>(out.xp.p));
-  FD_LAUNCH_CHECK();
+  if (row_side) check_span(out.ar, size_t(out.npad), "row offsets");
+  else check_span(out.ap, lane4_extent(ntiles, 1), "column offsets");
   out.bf16 = true;
   out.dc = dc;
+  out.rid = -1;
+  out.rid2 = -1;
+  out.variant = 0;
+  out.row_side = row_side;
+  return PackBf16Side{static_cast<const uint16_t*>(X), out.n, ntiles,
+                      reinterpret_cast<uintx4*>(out.xp.p), row_side ? out.ar.p : nullptr,
+                      row_side ? nullptr : reinterpret_cast<floatx4*>(out.ap.p)};
 }
 
-void launch_pack_points(const void* X, fd_dtype xt, int64_t n, int64_t D, int64_t ldx,
-                        double beta, bool row_side, PointPack& out, const CentreWs* centre,
-                        hipStream_t stream) {
-  out.beta = beta;
-  if (xt == FD_BF16) {
-    pack_points_bf16(static_cast<const uint16_t*>(X), n, D, ldx, row_side, out, stream);
-    out.rid = -1;
-    out.rid2 = -1;
-    out.variant = 0;
-    out.row_side = row_side;
+static void launch_packs_bf16(const PackIn& in, const PackV& v, PointPack& rows, PointPack& cols,
+                              const CentreWs& centre, hipStream_t stream) {
+  PackBf16Args a{};
+  const int dc = int(ceil_div(in.D, 32));
+  a.row = bf16_side(in.Xr, rows, dc, true);
+  a.col = bf16_side(in.Xc, cols, dc, false);
+  a.ldx = in.ldx;
+  a.D = int(in.D);
+  a.dc = dc;
+  // eight features at a time where every row starts on 16 bytes
+  a.vec = in.ldx % 8 == 0 && reinterpret_cast<uintptr_t>(in.Xr) % 16 == 0 &&
+          reinterpret_cast<uintptr_t>(in.Xc) % 16 == 0;
+  constexpr int TPB = PACK_THREADS / 64;
+  a.nbr = ceil_div(a.row.ntiles, TPB);
+  a.nbc = ceil_div(a.col.ntiles, TPB);
+  a.flags = centre.flags;
+  a.nflags = centre.used + centre.used2;
+  a.flag = in.flag;
+  a.v = v;
+  a.zero1 = in.zero1;
+  a.zero2 = in.zero2;
+  a.nzero = in.nzero;
+  const int64_t grid = a.nbr + a.nbc + ceil_div(pack_v_items(v), PACK_THREADS);
+  hipLaunchKernelGGL(pack_bf16_kernel, dim3(unsigned(grid)), dim3(PACK_THREADS), 0, stream, a);
+  FD_LAUNCH_CHECK();
+}
+
+// The V part of a pack: the split pack of V[0:n, 0:b] (ncb > 0) or the weight
+// pack of its one column (ncb = 0) for a column side of npad points.
+static PackV pack_v_args(const float* V, int64_t n, int64_t b, int64_t ldv, const float* sr,
+                         int ncb, int64_t npad, FSpan vp, FSpan vscale, int64_t nvmax) {
+  PackV v;
+  if (V == nullptr) return v;
+  v.V = V;
+  v.sr = sr;
+  v.n = n;
+  v.ldv = ldv;
+  v.b = int(b);
+  v.ncb = ncb;
+  if (ncb == 0) {
+    FD_REQUIRE(npad % TILE == 0 && npad >= n && b == 1, FD_ERR_INVALID_ARG,
+               "internal: bad w pack geometry");
+    v.ntiles = npad / TILE;
+    check_span(vp, lane4_extent(v.ntiles, 1), "weight pack");
+    v.wp = reinterpret_cast<floatx4*>(vp.p);
+    return v;
+  }
+  FD_REQUIRE(npad % (2 * TILE) == 0 && npad >= n && b <= ncb * 16 && b <= 64 &&
+                 nvmax <= VMAX_BLOCKS,
+             FD_ERR_INVALID_ARG, "internal: bad split V pack geometry");
+  v.npairs = npad / (2 * TILE);
+  // one VSplit (32 bytes = 8 floats) per lane per pair per column block
+  check_span(vp, size_t(v.npairs) * ncb * 64 * 8, "split V pack");
+  check_span(vscale, VSCALE_FLOATS, "column scales");
+  v.nvmax = int(nvmax);
+  v.colscale = vscale.p;
+  v.vpart = vscale.p + 64;
+  v.vp = reinterpret_cast<VSplit*>(vp.p);
+  return v;
+}
+
+void launch_packs(const PackIn& in, PointPack& rows, PointPack& cols, const CentreWs& centre,
+                  hipStream_t stream) {
+  rows.beta = cols.beta = in.beta;
+  const PackV v = pack_v_args(in.V, cols.n, in.b, in.ldv, in.sr, in.ncb, cols.npad, in.vp,
+                              in.vscale, in.nvmax);
+  if (in.xt == FD_BF16) {
+    launch_packs_bf16(in, v, rows, cols, centre, stream);
     return;
   }
-  out.bf16 = false;
-  out.dc = 0;
-  FD_REQUIRE(out.dp % 4 == 0 && D <= out.dp, FD_ERR_INVALID_ARG,
+  rows.bf16 = cols.bf16 = false;
+  rows.dc = cols.dc = 0;
+  FD_REQUIRE(rows.dp == cols.dp && rows.dp % 4 == 0 && in.D <= rows.dp, FD_ERR_INVALID_ARG,
              "internal: bad point pack geometry");
-  launch_pack_points_hx(static_cast<const float*>(X), n, D, ldx, beta, row_side, out, centre,
-                        stream);
+  launch_packs_hx(in, v, rows, cols, centre, stream);
 }
 
 void launch_pack_w(const float* w, int64_t n, int64_t npad, FSpan wp, hipStream_t stream) {
@@ -1073,20 +1240,10 @@ void launch_pack_w(const float* w, int64_t n, int64_t npad, FSpan wp, hipStream_
   FD_LAUNCH_CHECK();
 }
 
-void launch_pack_wv(const float* v, int64_t ldv, const float* sr, int64_t n, int64_t npad,
-                    FSpan wp, hipStream_t stream) {
-  FD_REQUIRE(npad % TILE == 0 && npad >= n, FD_ERR_INVALID_ARG, "internal: bad w pack geometry");
-  const int64_t ntiles = npad / TILE;
-  check_span(wp, lane4_extent(ntiles, 1), "weight pack");
-  hipLaunchKernelGGL(pack_wv_kernel, dim3(blocks_for(ntiles * 64, 256)), dim3(256), 0, stream, v,
-                     ldv, sr, n, ntiles, reinterpret_cast<floatx4*>(wp.p));
-  FD_LAUNCH_CHECK();
-}
-
 void launch_scale_rows(const float* t, const float* sl, int64_t n, float* Y, int64_t ldy,
-                       hipStream_t stream) {
+                       const PoisonGate& poison, hipStream_t stream) {
   hipLaunchKernelGGL(scale_rows_kernel, dim3(blocks_for(n, 256)), dim3(256), 0, stream, t, sl, n,
-                     Y, ldy);
+                     Y, ldy, poison);
   FD_LAUNCH_CHECK();
 }
 
@@ -1111,41 +1268,27 @@ static void check_tiles(const KVPlan& p, const PointPack& rows, const PointPack&
 
 void launch_pack_v_split(const float* V, int64_t n, int64_t b, int64_t ldv, const float* sr,
                          int ncb, int64_t npad, FSpan vp, FSpan vscale, hipStream_t stream) {
-  FD_REQUIRE(npad % (2 * TILE) == 0 && npad >= n && b <= ncb * 16 && b <= 64, FD_ERR_INVALID_ARG,
-             "internal: bad split V pack geometry");
-  const int64_t npairs = npad / (2 * TILE);
-  // one VSplit (32 bytes = 8 floats) per lane per pair per column block
-  check_span(vp, size_t(npairs) * ncb * 64 * 8, "split V pack");
-  check_span(vscale, 128, "column scales");
-  unsigned* maxbits = reinterpret_cast<unsigned*>(vscale.p);
-  float* colscale = vscale.p + 64;
-  hipLaunchKernelGGL(vmax_zero_kernel, dim3(1), dim3(64), 0, stream, maxbits);
+  if (ncb > 0) {
+    PrologueIn in;
+    in.V = V;
+    in.nv = n;
+    in.b = b;
+    in.ldv = ldv;
+    in.sr = sr;
+    CentreWs none;
+    launch_prologue(in, none, vscale, stream);
+  }
+  const PackV v = pack_v_args(V, n, b, ldv, sr, ncb, npad, vp, vscale, vmax_blocks(n));
+  hipLaunchKernelGGL(pack_v_kernel, dim3(blocks_for(pack_v_items(v), PACK_THREADS)),
+                     dim3(PACK_THREADS), 0, stream, v);
   FD_LAUNCH_CHECK();
-  int tc = 1;
-  while (tc < b) tc *= 2;
-  const int64_t nrl = 256 / tc;
-  const unsigned vgrid = unsigned(std::min<int64_t>(256, std::max<int64_t>(1, (n + 4 * nrl - 1) / (4 * nrl))));
-  hipLaunchKernelGGL(vmax_kernel, dim3(vgrid), dim3(256), 0, stream, V, n, int(b), ldv, sr, tc,
-                     maxbits);
-  FD_LAUNCH_CHECK();
-  const int64_t total = npairs * ncb * 64;
-  hipLaunchKernelGGL(pack_v_split_kernel, dim3(blocks_for(total, 256)), dim3(256), 0, stream, V,
-                     n, int(b), ldv, sr, ncb, npairs, maxbits, reinterpret_cast<VSplit*>(vp.p),
-                     colscale);
-  FD_LAUNCH_CHECK();
-}
-
-void launch_pack_v_for(const PointPack& /*rows*/, const float* V, int64_t n, int64_t b,
-                       int64_t ldv, const float* sr, int ncb, int64_t npad, FSpan vp,
-                       FSpan vscale, hipStream_t stream) {
-  // both product kinds take the split V (hi + lo float16 halves)
-  launch_pack_v_split(V, n, b, ldv, sr, ncb, npad, vp, vscale, stream);
 }
 
 template <int DC, int NCB, int NIB>
 static void product_bf16_nib(const KVPlan& p, const PointPack& rows, const PointPack& cols,
                              const float* vp, const float* colscale, bool diag, const float* sl,
-                             float* Y, int64_t ldy, int b, float* part, hipStream_t stream) {
+                             float* Y, int64_t ldy, int b, float* part,
+                             const PoisonGate& poison, hipStream_t stream) {
   const unsigned grid = unsigned(p.nrt * p.nsplit);
   const float scale2 = float(2.0 * rows.beta * LOG2E);
   ProfScope prof(FD_KERNEL_PRODUCT, stream);
@@ -1155,50 +1298,52 @@ static void product_bf16_nib(const KVPlan& p, const PointPack& rows, const Point
                      reinterpret_cast<const VSplit*>(vp),
                      reinterpret_cast<const uintx4*>(rows.xp.p), rows.ar.p, p.nrt,
                      ceil_div(p.njb, 2), p.jb_per_split / 2, int(diag), scale2, colscale, sl, Y,
-                     ldy, rows.n, b, part, rows.npad);
+                     ldy, rows.n, b, part, rows.npad, poison);
   FD_LAUNCH_CHECK();
 }
 
 template <int DC, int NCB>
 static void product_bf16_launch(const KVPlan& p, const PointPack& rows, const PointPack& cols,
                                 const float* vp, const float* cs, bool diag, const float* sl,
-                                float* Y, int64_t ldy, int b, float* part, hipStream_t stream) {
+                                float* Y, int64_t ldy, int b, float* part,
+                             const PoisonGate& poison, hipStream_t stream) {
   // eight row tiles per wave only for the shapes product_nib gives them to
   if constexpr (DC == 1 && NCB == 1) {
     if (p.nib == 8)
       return product_bf16_nib<DC, NCB, 8>(p, rows, cols, vp, cs, diag, sl, Y, ldy, b, part,
-                                          stream);
+                                          poison, stream);
   }
   FD_REQUIRE(p.nib == 2 || p.nib == 4, FD_ERR_INVALID_ARG, "internal: bf16 rows per wave");
   if (p.nib == 2)
-    product_bf16_nib<DC, NCB, 2>(p, rows, cols, vp, cs, diag, sl, Y, ldy, b, part, stream);
+    product_bf16_nib<DC, NCB, 2>(p, rows, cols, vp, cs, diag, sl, Y, ldy, b, part, poison, stream);
   else
-    product_bf16_nib<DC, NCB, 4>(p, rows, cols, vp, cs, diag, sl, Y, ldy, b, part, stream);
+    product_bf16_nib<DC, NCB, 4>(p, rows, cols, vp, cs, diag, sl, Y, ldy, b, part, poison, stream);
 }
 
 template <int DC>
 static void product_bf16_ncb(const KVPlan& p, const PointPack& rows, const PointPack& cols,
                              const float* vp, const float* cs, bool diag, const float* sl,
-                             float* Y, int64_t ldy, int b, float* part, hipStream_t stream) {
+                             float* Y, int64_t ldy, int b, float* part,
+                             const PoisonGate& poison, hipStream_t stream) {
   switch (p.ncb) {
-    case 1: return product_bf16_launch<DC, 1>(p, rows, cols, vp, cs, diag, sl, Y, ldy, b, part, stream);
-    case 2: return product_bf16_launch<DC, 2>(p, rows, cols, vp, cs, diag, sl, Y, ldy, b, part, stream);
-    case 3: return product_bf16_launch<DC, 3>(p, rows, cols, vp, cs, diag, sl, Y, ldy, b, part, stream);
-    case 4: return product_bf16_launch<DC, 4>(p, rows, cols, vp, cs, diag, sl, Y, ldy, b, part, stream);
+    case 1: return product_bf16_launch<DC, 1>(p, rows, cols, vp, cs, diag, sl, Y, ldy, b, part, poison, stream);
+    case 2: return product_bf16_launch<DC, 2>(p, rows, cols, vp, cs, diag, sl, Y, ldy, b, part, poison, stream);
+    case 3: return product_bf16_launch<DC, 3>(p, rows, cols, vp, cs, diag, sl, Y, ldy, b, part, poison, stream);
+    case 4: return product_bf16_launch<DC, 4>(p, rows, cols, vp, cs, diag, sl, Y, ldy, b, part, poison, stream);
   }
   throw Error{FD_ERR_UNSUPPORTED, "block width above 64"};
 }
 
 void launch_product(const KVPlan& p, const PointPack& rows, const PointPack& cols, FSpan vp,
                     FSpan vscale, bool diag, const float* sl, float* Y, int64_t ldy, int b,
-                    FSpan part, hipStream_t stream) {
+                    FSpan part, const PoisonGate& poison, hipStream_t stream) {
   check_tiles(p, rows, cols);
   FD_REQUIRE(b >= 1 && b <= p.ncb * 16 && (p.nib == 2 || p.nib == 4 || p.nib == 8),
              FD_ERR_INVALID_ARG, "internal: block width does not match the plan");
   FD_REQUIRE(p.jb_per_split % 2 == 0 && round_up(p.njb, 2) * TILE <= cols.npad,
              FD_ERR_INVALID_ARG, "internal: column pairs do not fit the pack");
-  check_span(vscale, 128, "column scales");
-  const float* cs = vscale.p + 64;
+  check_span(vscale, VSCALE_FLOATS, "column scales");
+  const float* cs = vscale.p;
   float* pp = nullptr;
   if (p.nsplit > 1) {
     check_span(part, size_t(p.nsplit) * rows.npad * p.ncb * 16, "partial products");
@@ -1209,17 +1354,28 @@ void launch_product(const KVPlan& p, const PointPack& rows, const PointPack& col
                "internal: mixed pack kinds");
     check_span(vp, size_t(ceil_div(p.njb, 2)) * p.ncb * 64 * 8, "split V pack");
     if (rows.dc == 1)
-      product_bf16_ncb<1>(p, rows, cols, vp.p, cs, diag, sl, Y, ldy, b, pp, stream);
+      product_bf16_ncb<1>(p, rows, cols, vp.p, cs, diag, sl, Y, ldy, b, pp, poison, stream);
     else
-      product_bf16_ncb<2>(p, rows, cols, vp.p, cs, diag, sl, Y, ldy, b, pp, stream);
+      product_bf16_ncb<2>(p, rows, cols, vp.p, cs, diag, sl, Y, ldy, b, pp, poison, stream);
   } else {
     check_span(vp, size_t(ceil_div(p.njb, 2)) * p.ncb * 64 * 8, "split V pack");
-    launch_product_hx(p, rows, cols, vp.p, cs, diag, sl, Y, ldy, b, pp, stream);
+    launch_product_hx(p, rows, cols, vp.p, cs, diag, sl, Y, ldy, b, pp, poison, stream);
   }
   if (p.nsplit > 1) {
-    const int64_t total = rows.n * b;
-    hipLaunchKernelGGL(reduce_product_kernel, dim3(blocks_for(total, 256)), dim3(256), 0, stream,
-                       pp, p.nsplit, rows.npad, p.ncb * 16, cs, sl, Y, ldy, rows.n, b);
+    // four teams of threads per output below 2^18 threads' worth of outputs
+    // (N = 2,048, b = 8, 16 splits: 6.0 -> 3 us; from there on one is as fast)
+    const int64_t total = rows.n * ceil_div(b, 4);
+    const int teams = total < (int64_t(1) << 16) && p.nsplit >= 16  ? 8
+                      : total < (int64_t(1) << 18) && p.nsplit >= 8 ? 4
+                                                                     : 1;
+    const int vec = ldy % 4 == 0 && reinterpret_cast<uintptr_t>(Y) % 16 == 0;
+    auto go = [&](auto kernel) {
+      hipLaunchKernelGGL(kernel, dim3(blocks_for(total * teams, 256)), dim3(256), 0, stream, pp,
+                         p.nsplit, rows.npad, p.ncb * 16, cs, sl, Y, ldy, rows.n, b, vec, poison);
+    };
+    if (teams == 8) go(reduce_product_kernel<8>);
+    else if (teams == 4) go(reduce_product_kernel<4>);
+    else go(reduce_product_kernel<1>);
     FD_LAUNCH_CHECK();
   }
 }
@@ -1257,8 +1413,8 @@ bool rowsum_sym_applies(const PointPack& rows, const PointPack& cols, bool diag,
 }
 
 SymPass launch_rowsum_sym_pass(const KVPlan& p, const PointPack& rows, const PointPack& cols,
-                               FSpan wp, FSpan part, unsigned long long* colfix, bool zero_colfix,
-                               hipStream_t stream, FSpan sq_part, unsigned long long* sq_colfix) {
+                               FSpan wp, FSpan part, unsigned long long* colfix, hipStream_t stream,
+                               FSpan sq_part, unsigned long long* sq_colfix) {
   check_tiles(p, rows, cols);
   FD_REQUIRE(rowsum_sym_applies(rows, cols, true, colfix), FD_ERR_INVALID_ARG,
              "internal: symmetric row sums need one float32 point set");
@@ -1268,11 +1424,6 @@ SymPass launch_rowsum_sym_pass(const KVPlan& p, const PointPack& rows, const Poi
   // fixed point with F fractional bits: the total of weights in [0, 1] over
   // npad columns stays below 2^62 / 4
   const int F = 62 - int(std::ceil(std::log2(double(rows.npad)))) - 2;
-  if (zero_colfix) {
-    hipLaunchKernelGGL(zero_u64_kernel, dim3(blocks_for(rows.npad, 256)), dim3(256), 0, stream,
-                       colfix, rows.npad);
-    FD_LAUNCH_CHECK();
-  }
   SymSquares sq;
   if (sq_part.p != nullptr) {
     FD_REQUIRE(wp.p != nullptr && sq_colfix != nullptr, FD_ERR_INVALID_ARG,
@@ -1287,22 +1438,23 @@ SymPass launch_rowsum_sym_pass(const KVPlan& p, const PointPack& rows, const Poi
 
 void launch_degree_reduce_q(const SymPass& sp, const PointPack& rows, const PointPack& cols,
                             FSpan part, unsigned long long* colfix, float* q, double alpha,
-                            FSpan wp, hipStream_t stream) {
+                            FSpan wp, double* qsum, const PoisonGate& poison, hipStream_t stream) {
   FD_REQUIRE(cols.npad % TILE == 0 && cols.npad <= rows.npad && cols.n == rows.n,
              FD_ERR_INVALID_ARG, "internal: bad weight pack geometry");
   if (wp.p != nullptr) check_span(wp, lane4_extent(cols.npad / TILE, 1), "weight pack");
   hipLaunchKernelGGL(degree_reduce_q_kernel, dim3(blocks_for(rows.npad, 256)), dim3(256), 0,
                      stream, part.p, sp.nsplit, rows.npad, colfix, sp.inv_fix, q, rows.n,
-                     rows.npad, alpha, wp.p, cols.npad);
+                     rows.npad, alpha, wp.p, cols.npad, qsum, poison);
   FD_LAUNCH_CHECK();
 }
 
 void launch_degree_reduce_ds(const SymPass& sp, const PointPack& rows, FSpan part,
                              unsigned long long* colfix, const float* q, double alpha, float* d,
-                             float* s, hipStream_t stream) {
+                             float* s, const double* qsum, double* s_off,
+                             const PoisonGate& poison, hipStream_t stream) {
   hipLaunchKernelGGL(degree_reduce_ds_kernel, dim3(blocks_for(rows.npad, 256)), dim3(256), 0,
                      stream, part.p, sp.nsplit, rows.npad, colfix, sp.inv_fix, q, rows.n,
-                     rows.npad, alpha, d, s);
+                     rows.npad, alpha, d, s, qsum, qsum_words(rows.npad), s_off, poison);
   FD_LAUNCH_CHECK();
 }
 
@@ -1310,7 +1462,8 @@ void launch_degree_reduce_dsq(const SymPass& sp, const PointPack& rows, const Po
                               FSpan part, unsigned long long* colfix, const float* q,
                               double alpha, float* d, float* s, FSpan sq_part,
                               unsigned long long* sq_colfix, float* q_next, FSpan wp,
-                              hipStream_t stream) {
+                              const double* qsum, double* s_off, double* qsum_next,
+                              const PoisonGate& poison, hipStream_t stream) {
   FD_REQUIRE(cols.npad % TILE == 0 && cols.npad <= rows.npad && cols.n == rows.n,
              FD_ERR_INVALID_ARG, "internal: bad weight pack geometry");
   check_span(wp, lane4_extent(cols.npad / TILE, 1), "weight pack");
@@ -1319,27 +1472,14 @@ void launch_degree_reduce_dsq(const SymPass& sp, const PointPack& rows, const Po
              "internal: dyadic reduction outputs");
   hipLaunchKernelGGL(degree_reduce_dsq_kernel, dim3(blocks_for(rows.npad, 256)), dim3(256), 0,
                      stream, part.p, sp.nsplit, rows.npad, colfix, sp.inv_fix, q, rows.n,
-                     rows.npad, alpha, d, s, sq_part.p, sq_colfix, q_next, wp.p, cols.npad);
-  FD_LAUNCH_CHECK();
-}
-
-void launch_zero_u64(unsigned long long* p, int64_t n, hipStream_t stream) {
-  hipLaunchKernelGGL(zero_u64_kernel, dim3(blocks_for(n, 256)), dim3(256), 0, stream, p, n);
+                     rows.npad, alpha, d, s, sq_part.p, sq_colfix, q_next, wp.p, cols.npad, qsum,
+                     qsum_words(rows.npad), s_off, qsum_next, poison);
   FD_LAUNCH_CHECK();
 }
 
 void launch_rowsum(const KVPlan& p, const PointPack& rows, const PointPack& cols, FSpan wp,
-                   bool diag, float* out, FSpan part, hipStream_t stream,
-                   unsigned long long* colfix) {
+                   bool diag, float* out, FSpan part, hipStream_t stream) {
   check_tiles(p, rows, cols);
-  if (rowsum_sym_applies(rows, cols, diag, colfix)) {
-    // one point set: each off-diagonal tile serves its rows and its columns
-    const SymPass sp = launch_rowsum_sym_pass(p, rows, cols, wp, part, colfix, true, stream);
-    hipLaunchKernelGGL(reduce_rowsum_sym_kernel, dim3(blocks_for(rows.n, 256)), dim3(256), 0,
-                       stream, part.p, sp.nsplit, rows.npad, colfix, sp.inv_fix, out, rows.n);
-    FD_LAUNCH_CHECK();
-    return;
-  }
   FD_REQUIRE(p.nib == 4 || p.nib == 8, FD_ERR_INVALID_ARG, "internal: row-sum plan");
   if (wp.p != nullptr) check_span(wp, lane4_extent(p.njb, 1), "weight pack");
   float* pp = nullptr;
@@ -1374,9 +1514,10 @@ void launch_pow_neg(const float* q, int64_t n, double alpha, float* w, hipStream
 }
 
 void launch_degree_finish(const float* q, const float* t, int64_t n, double alpha, float* d,
-                          float* s, hipStream_t stream) {
+                          float* s, const double* qsum, int64_t nqsum, double* s_off,
+                          const PoisonGate& poison, hipStream_t stream) {
   hipLaunchKernelGGL(degree_finish_kernel, dim3(blocks_for(n, 256)), dim3(256), 0, stream, q, t,
-                     n, alpha, d, s);
+                     n, alpha, d, s, qsum, nqsum, s_off, poison);
   FD_LAUNCH_CHECK();
 }
 

@@ -76,7 +76,7 @@ static SolverWs carve_solver_ws(Arena& a, int64_t N, int64_t D, int b, int mm_ca
   w.prod.rows = w.deg.rows;
   w.prod.cols = w.deg.cols;
   w.prod.vp = a.fspan(size_t(w.prod.cols.npad) * w.prod.plan.ncb * 16);
-  w.prod.vscale = a.fspan(128);
+  w.prod.vscale = a.fspan(VSCALE_FLOATS);
   w.prod.part = a.fspan(part_rows_bound(w.prod.rows.npad, N) * w.prod.plan.ncb * 16);
   w.prod.tmp = a.fspan(size_t(N));  // single-column products (block width 1)
   w.d = a.take<float>(size_t(N));
@@ -435,10 +435,20 @@ static void nystrom_extend(ContWs& c, const void* X, fd_dtype xt, int64_t D, int
   PointPack rows = pack_view(w.deg.rows, n_new, ROW_PAD);
   PointPack cols = pack_view(w.deg.cols, n_old, COL_PAD);
   // centred on the old prefix (the column set), radius over the new one
-  launch_centre(X, xt, n_old, D, ldx, w.deg.centre, st);
-  launch_radius_more(X, xt, n_new, D, ldx, w.deg.centre, st);
-  launch_pack_points(X, xt, n_new, D, ldx, beta, true, rows, &w.deg.centre, st);
-  launch_pack_points(X, xt, n_old, D, ldx, beta, false, cols, &w.deg.centre, st);
+  PrologueIn pro;
+  pro.X = X;
+  pro.xt = xt;
+  pro.n = n_old;
+  pro.D = D;
+  pro.ldx = ldx;
+  launch_prologue(pro, w.deg.centre, FSpan{}, st);
+  PackIn in;
+  in.Xr = in.Xc = X;
+  in.xt = xt;
+  in.D = D;
+  in.ldx = ldx;
+  in.beta = beta;
+  launch_packs(in, rows, cols, w.deg.centre, st);
   launch_pow_neg(q_old, n_old, alpha, c.wv, st);
   // denominators K w
   launch_pack_w(c.wv, n_old, cols.npad, w.deg.wp, st);
@@ -590,7 +600,7 @@ static FlowProbe flow_probe(FlowWs& f, const void* X, fd_dtype xt, int64_t N, in
   FlowProbe pr;
   pr.beta = beta;
   pr.role = role;
-  degree_run(f.sw.deg, X, xt, N, D, ldx, beta, alpha, nullptr, f.sw.d, f.sw.s, f.sw.s_off, true,
+  degree_run(f.sw.deg, X, xt, N, D, ldx, beta, alpha, nullptr, f.sw.d, f.sw.s, f.sw.s_off, false,
              st);
   const SolverLayout lay = solver_layout(N, b, k, o);
   Lanczos L(f.sw, product_view(f.sw.prod, f.sw.deg.rows, f.sw.deg.cols, b), st, N, b, lay.mm,
@@ -682,7 +692,14 @@ static FlowOutcome run_flow(FlowWs& f, const void* X, fd_dtype xt, int64_t N, in
                             int level, std::vector<fd_flow_probe>& out, hipStream_t st) {
   // the radius that bounds the exponent range: X's centring is the same for
   // every probe
-  launch_centre(X, xt, N, D, ldx, f.sw.deg.centre, st);
+  PrologueIn pro;
+  pro.X = X;
+  pro.xt = xt;
+  pro.n = N;
+  pro.D = D;
+  pro.ldx = ldx;
+  launch_prologue(pro, f.sw.deg.centre, FSpan{}, st);
+  launch_radius(X, xt, N, D, ldx, f.sw.deg.centre, st);
   const double r2 = exponent_radius(xt, f.sw.deg.centre, st);
   DeviceFlowDriver drv{f, X, xt, N, D, ldx, alpha, bb, kk, fp, o, level, out, st, r2};
   return logic::run_flow_logic(drv, N, beta, warm, max_probes);
@@ -743,7 +760,7 @@ fd_status fd_block_lanczos(const void* X, fd_dtype xt, int64_t N, int64_t D, int
       hipStream_t st = static_cast<hipStream_t>(stream);
       require_finite(X, xt, N, D, ldx, w.deg.flag, st);
 
-      degree_run(w.deg, X, xt, N, D, ldx, beta, alpha, nullptr, w.d, w.s, w.s_off, true, st);
+      degree_run(w.deg, X, xt, N, D, ldx, beta, alpha, nullptr, w.d, w.s, w.s_off, false, st);
       require_exponent_range(xt, w.deg.centre, beta, st);
       // the product view takes the packs as filled (kind and bandwidth)
       Lanczos L(w, product_view(w.prod, w.deg.rows, w.deg.cols, int(b)), st, N, int(b), lay.mm,
@@ -859,7 +876,7 @@ fd_status fd_continuation(const void* X, fd_dtype xt, int64_t N, int64_t D, int6
       }
       // normalisation and eigensolve on the prefix
       DegreeWs dv = degree_view(c.sw.deg, n);
-      degree_run(dv, X, xt, n, D, ldx, beta, alpha, c.q(t), c.sw.d, c.sw.s, c.sw.s_off, true, st);
+      degree_run(dv, X, xt, n, D, ldx, beta, alpha, c.q(t), c.sw.d, c.sw.s, c.sw.s_off, false, st);
       require_exponent_range(xt, dv.centre, beta, st);
       const SolverLayout lay = solver_layout(n, int(b), kk, o);
       FD_REQUIRE(lay.mm <= c.sw.mm_cap, FD_ERR_INVALID_ARG, "internal: basis wider than carved");
