@@ -78,55 +78,23 @@ __global__ void scan_nonfinite_kernel(const void* __restrict__ X, int bf16, int6
   if (bad) atomicOr(flag, 1);
 }
 
-__global__ void poison_f32_kernel(const int* __restrict__ flag, float* __restrict__ v,
-                                  int64_t rows, int64_t cols, int64_t ld) {
-  if (*flag == 0) return;
-  for (int64_t e = int64_t(blockIdx.x) * blockDim.x + threadIdx.x; e < rows * cols;
-       e += int64_t(gridDim.x) * blockDim.x)
-    v[(e / cols) * ld + e % cols] = __builtin_nanf("");
-}
-
-__global__ void poison_f64_kernel(const int* __restrict__ flag, double* __restrict__ v,
-                                  int64_t n) {
-  if (*flag == 0) return;
-  for (int64_t e = int64_t(blockIdx.x) * blockDim.x + threadIdx.x; e < n;
-       e += int64_t(gridDim.x) * blockDim.x)
-    v[e] = __builtin_nan("");
-}
-
 static unsigned stride_grid(int64_t n) {
   return unsigned(std::min<int64_t>(1024, std::max<int64_t>(1, (n + 255) / 256)));
 }
 
 void launch_scan_nonfinite(const void* X, fd_dtype xt, int64_t N, int64_t D, int64_t ldx,
-                           int* flag, bool clear, hipStream_t stream) {
+                           int* flag, hipStream_t stream) {
   FD_REQUIRE(flag != nullptr, FD_ERR_INVALID_ARG, "internal: no flag word");
-  if (clear) {
-    hipLaunchKernelGGL(clear_flag_kernel, dim3(1), dim3(1), 0, stream, flag);
-    FD_LAUNCH_CHECK();
-  }
+  hipLaunchKernelGGL(clear_flag_kernel, dim3(1), dim3(1), 0, stream, flag);
+  FD_LAUNCH_CHECK();
   hipLaunchKernelGGL(scan_nonfinite_kernel, dim3(stride_grid(N * D)), dim3(256), 0, stream, X,
                      xt == FD_BF16 ? 1 : 0, N, int(D), ldx, flag);
   FD_LAUNCH_CHECK();
 }
 
-void launch_poison(const int* flag, float* v, int64_t rows, int64_t cols, int64_t ld,
-                   hipStream_t stream) {
-  if (v == nullptr || rows * cols == 0) return;
-  hipLaunchKernelGGL(poison_f32_kernel, dim3(stride_grid(rows * cols)), dim3(256), 0, stream,
-                     flag, v, rows, cols, ld);
-  FD_LAUNCH_CHECK();
-}
-
-void launch_poison(const int* flag, double* v, int64_t n, hipStream_t stream) {
-  if (v == nullptr || n == 0) return;
-  hipLaunchKernelGGL(poison_f64_kernel, dim3(stride_grid(n)), dim3(256), 0, stream, flag, v, n);
-  FD_LAUNCH_CHECK();
-}
-
 void require_finite(const void* X, fd_dtype xt, int64_t N, int64_t D, int64_t ldx, int* flag,
                     hipStream_t stream) {
-  launch_scan_nonfinite(X, xt, N, D, ldx, flag, true, stream);
+  launch_scan_nonfinite(X, xt, N, D, ldx, flag, stream);
   int h = 0;
   FD_HIP_CHECK(hipMemcpyAsync(&h, flag, sizeof(int), hipMemcpyDeviceToHost, stream));
   FD_HIP_CHECK(hipStreamSynchronize(stream));
@@ -144,7 +112,7 @@ ProductWs carve_product(Arena& a, int64_t Nr, int64_t Nc, int64_t D, int b) {
   w.vp = a.fspan(size_t(w.cols.npad) * w.plan.ncb * 16);
   w.vscale = a.fspan(VSCALE_FLOATS);
   w.part = a.fspan(part_rows_bound(w.rows.npad, Nc) * w.plan.ncb * 16);
-  w.tmp = a.fspan(size_t(Nr));
+  if (b == 1) w.colfix = a.take<unsigned long long>(size_t(w.rows.npad));
   w.flag = a.take<int>(1);
   w.centre = carve_centre(a, Nc, Nr);
   return w;
@@ -162,9 +130,10 @@ static ProductWs carve_product_exact(Arena& a, int64_t Nr, int64_t Nc, int64_t D
   w.vscale = a.fspan(VSCALE_FLOATS);
   const KVPlan rp = plan_rowsum(Nr, Nc, dp);
   const size_t part_prod = size_t(w.plan.nsplit) * w.rows.npad * w.plan.ncb * 16;
-  const size_t part_row = size_t(rp.nsplit) * w.rows.npad;
+  const size_t part_row =
+      std::max(size_t(rp.nsplit) * w.rows.npad, sym_part_rows(w.rows.npad, SYM_NIB));
   w.part = a.fspan(b == 1 ? part_row : part_prod);
-  w.tmp = a.fspan(size_t(Nr));
+  if (b == 1) w.colfix = a.take<unsigned long long>(size_t(w.rows.npad));
   w.flag = a.take<int>(1);
   w.centre = carve_centre(a, Nc, Nr);
   return w;
@@ -235,10 +204,8 @@ static void product_run(ProductWs& w, const float* sl, int b, float* Y, int64_t 
   if (b == 1) {
     // one right-hand side: weighted row sums K (sr v) on the vector ALUs (no
     // matrix-core contraction padded to 16 columns), then the row scale
-    const KVPlan rp = plan_rowsum(w.rows.n, w.cols.n, w.rows.dp);
-    check_span(w.tmp, size_t(w.rows.n), "single-column row sums");
-    launch_rowsum(rp, w.rows, w.cols, w.vp, diag, w.tmp.p, w.part, stream);
-    launch_scale_rows(w.tmp.p, sl, w.rows.n, Y, ldy, poison, stream);
+    launch_product_column(plan_rowsum(w.rows.n, w.cols.n, w.rows.dp), w.rows, w.cols, w.vp,
+                          w.vscale, diag, sl, Y, ldy, w.part, w.colfix, poison, stream);
     return;
   }
   launch_product(w.plan, w.rows, w.cols, w.vp, w.vscale, diag, sl, Y, ldy, b, w.part, poison,
@@ -270,13 +237,11 @@ static void matmul_run(ProductWs& w, const void* Xr, const void* Xc, int64_t D, 
     pro.X2 = Xr;
     pro.n2 = w.rows.n;
   }
-  if (b > 1) {
-    pro.V = V;
-    pro.nv = w.cols.n;
-    pro.b = b;
-    pro.ldv = ldv;
-    pro.sr = sr;
-  }
+  pro.V = V;
+  pro.nv = w.cols.n;
+  pro.b = b;
+  pro.ldv = ldv;
+  pro.sr = sr;
   launch_prologue(pro, w.centre, w.vscale, st);
   PackIn in;
   in.Xr = Xr;
@@ -294,6 +259,8 @@ static void matmul_run(ProductWs& w, const void* Xr, const void* Xc, int64_t D, 
   in.vp = w.vp;
   in.vscale = w.vscale;
   in.nvmax = vmax_blocks(w.cols.n);
+  in.zero1 = w.colfix;
+  in.nzero = w.colfix != nullptr ? w.rows.npad : 0;
   launch_packs(in, w.rows, w.cols, w.centre, st);
   product_run(w, sl, b, Y, ldy, diag, poison_gate(xt, w.centre, beta, w.flag), st);
 }
@@ -308,7 +275,6 @@ DegreeWs carve_degree(Arena& a, int64_t N, int64_t D) {
   w.cols = carve_pack(a, N, dp, COL_PAD);
   w.wp = a.fspan(size_t(w.cols.npad) * 16);  // one float4 per lane per 16-point tile
   w.q = a.take<float>(size_t(N));
-  w.t = a.take<float>(size_t(N));
   w.w = a.take<float>(size_t(N));
   w.part = a.fspan(std::max(part_rows_bound(w.rows.npad, N), sym_part_rows(w.rows.npad, SYM_NIB)));
   w.colfix = a.take<unsigned long long>(size_t(w.rows.npad));
@@ -351,37 +317,20 @@ static void degree_passes(DegreeWs& w, int64_t N, double alpha, float* q, float*
                           double* s_off, const PoisonGate& poison, hipStream_t stream) {
   float* qq = q != nullptr ? q : w.q;
   const int64_t nq = qsum_words(w.rows.npad);
-  if (rowsum_sym_applies(w.rows, w.cols, true, w.colfix)) {
-    // symmetric row sums with the epilogues fused into their reductions; the
-    // first reduction leaves the column-sum words zeroed for the second pass
-    const SymPass p1 = launch_rowsum_sym_pass(w.plan, w.rows, w.cols, FSpan{}, w.part, w.colfix,
-                                              stream);
-    launch_degree_reduce_q(p1, w.rows, w.cols, w.part, w.colfix, qq, alpha,
-                           alpha == 0.0 ? FSpan{} : w.wp, w.qsum, poison, stream);
-    if (alpha == 0.0) {
-      launch_degree_finish(qq, qq, N, 0.0, d, s, w.qsum, nq, s_off, poison, stream);
-      return;
-    }
-    const SymPass p2 = launch_rowsum_sym_pass(w.plan, w.rows, w.cols, w.wp, w.part, w.colfix,
-                                              stream);
-    launch_degree_reduce_ds(p2, w.rows, w.part, w.colfix, qq, alpha, d, s, w.qsum, s_off, poison,
-                            stream);
+  // symmetric row sums with the epilogues fused into their reductions; the
+  // first reduction leaves the column-sum words zeroed for the second pass
+  const SymPass p1 = launch_rowsum_sym_pass(w.plan, w.rows, w.cols, FSpan{}, w.part, w.colfix,
+                                            stream);
+  launch_degree_reduce_q(p1, w.rows, w.cols, w.part, w.colfix, qq, alpha,
+                         alpha == 0.0 ? FSpan{} : w.wp, w.qsum, poison, stream);
+  if (alpha == 0.0) {
+    launch_degree_finish(qq, qq, N, 0.0, d, s, w.qsum, nq, s_off, poison, stream);
     return;
   }
-  launch_rowsum(w.plan, w.rows, w.cols, FSpan{}, true, qq, w.part, stream);
-  if (s_off != nullptr) launch_sum_minus_n(qq, N, s_off, stream);
-  if (alpha == 0.0) {
-    launch_degree_finish(qq, qq, N, 0.0, d, s, nullptr, 0, nullptr, poison, stream);
-  } else {
-    launch_pow_neg(qq, N, alpha, w.w, stream);
-    launch_pack_w(w.w, N, w.cols.npad, w.wp, stream);
-    launch_rowsum(w.plan, w.rows, w.cols, w.wp, true, w.t, w.part, stream);
-    launch_degree_finish(qq, w.t, N, alpha, d, s, nullptr, 0, nullptr, poison, stream);
-  }
-  if (poison.flag != nullptr) {
-    launch_poison(poison.flag, q, N, 1, 1, stream);
-    launch_poison(poison.flag, s_off, 1, stream);
-  }
+  const SymPass p2 = launch_rowsum_sym_pass(w.plan, w.rows, w.cols, w.wp, w.part, w.colfix,
+                                            stream);
+  launch_degree_reduce_ds(p2, w.rows, w.part, w.colfix, qq, alpha, d, s, w.qsum, s_off, poison,
+                          stream);
 }
 
 void degree_run(DegreeWs& w, const void* X, fd_dtype xt, int64_t N, int64_t D, int64_t ldx,
@@ -410,11 +359,11 @@ void degree_run_dyadic(DegreeWs& w, const void* X, fd_dtype xt, int64_t N, int64
   degree_packs(w, X, xt, D, ldx, beta_of(0), true, w.flag, stream);
   // the largest bandwidth decides (every level's outputs are poisoned)
   const PoisonGate poison = poison_gate(xt, w.centre, beta_of(nb - 1), w.flag);
-  if (alpha == 0.0 || !rowsum_sym_applies(w.rows, w.cols, true, w.colfix)) {
-    // no weighted pass to carry the squares (alpha = 0), or not the symmetric
-    // path: fd_degree's passes, level by level
+  if (alpha == 0.0 || xt == FD_BF16) {
+    // no weighted pass to carry the squares (alpha = 0), or bfloat16 inputs
+    // (stated level by level): fd_degree's passes
     for (int l = 0; l < nb; ++l) {
-      if (l > 0) degree_packs(w, X, xt, D, ldx, beta_of(l), false, nullptr, stream);
+      if (l > 0) degree_packs(w, X, xt, D, ldx, beta_of(l), true, nullptr, stream);
       degree_passes(w, N, alpha, at(q, l), at(d, l), at(s, l), off_at(l), poison, stream);
     }
     return;

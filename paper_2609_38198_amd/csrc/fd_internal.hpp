@@ -112,6 +112,9 @@ struct PointPack {
   int rid2 = -1;
   const unsigned long long* r2max = nullptr;
   int variant = 0;
+  // single-column products (HxGate): the device word and the case to serve
+  const float* vbad = nullptr;
+  int serves_bad = 0;
 };
 
 // Centring of a float32 point set (the kernel is translation invariant, and
@@ -236,9 +239,6 @@ struct PackIn {
 void launch_packs(const PackIn& in, PointPack& rows, PointPack& cols, const CentreWs& centre,
                   hipStream_t stream);
 void launch_pack_w(const float* w, int64_t n, int64_t npad, FSpan wp, hipStream_t stream);
-// Y[i * ldy] = sl[i] * t[i] (sl NULL: t[i]).
-void launch_scale_rows(const float* t, const float* sl, int64_t n, float* Y, int64_t ldy,
-                       const PoisonGate& poison, hipStream_t stream);
 // Split float16 pack of sr * V with per-column power-of-two scales, in two
 // launches (column maxima, pack).  vscale (VSCALE_FLOATS): 64 inverse scales,
 // then VMAX_BLOCKS x 64 partial maxima.
@@ -251,6 +251,14 @@ void launch_pack_v_split(const float* V, int64_t n, int64_t b, int64_t ldv, cons
 void launch_product(const KVPlan& p, const PointPack& rows, const PointPack& cols, FSpan vp,
                     FSpan vscale, bool diag, const float* sl, float* Y, int64_t ldy, int b,
                     FSpan part, const PoisonGate& poison, hipStream_t stream);
+// Y[:, 0] = diag(sl) K diag(sr) v for one column from its weight pack: on one
+// point set (colfix set: npad cleared words, left cleared) the symmetric row
+// sums, or the plain ones where the column holds a NaN or an infinity; else
+// the plain ones.
+void launch_product_column(const KVPlan& p, const PointPack& rows, const PointPack& cols, FSpan wp,
+                           FSpan vscale, bool diag, const float* sl, float* Y, int64_t ldy,
+                           FSpan part, unsigned long long* colfix, const PoisonGate& poison,
+                           hipStream_t stream);
 // out = K w (wp.p == NULL: w = 1).
 void launch_rowsum(const KVPlan& p, const PointPack& rows, const PointPack& cols, FSpan wp,
                    bool diag, float* out, FSpan part, hipStream_t stream);
@@ -273,7 +281,6 @@ struct SymPass {
 struct SymSquares {
   float* part = nullptr;
   unsigned long long* colfix = nullptr;
-  double fix_scale = 0.0;
 };
 bool rowsum_sym_applies(const PointPack& rows, const PointPack& cols, bool diag,
                         const unsigned long long* colfix);
@@ -312,6 +319,5 @@ void launch_degree_finish(const float* q, const float* t, int64_t n, double alph
                           float* s, const double* qsum, int64_t nqsum, double* s_off,
                           const PoisonGate& poison, hipStream_t stream);
 void launch_pow_neg(const float* q, int64_t n, double alpha, float* w, hipStream_t stream);
-void launch_sum_minus_n(const float* q, int64_t n, double* out, hipStream_t stream);
 
 }  // namespace fd

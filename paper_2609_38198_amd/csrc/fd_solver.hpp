@@ -9,7 +9,7 @@ namespace fd {
 struct ProductWs {
   PointPack rows, cols;
   FSpan vp, vscale, part;
-  FSpan tmp;  // one float per row: the single-column product's row sums
+  unsigned long long* colfix = nullptr;  // single columns: npad column-sum words
   int* flag = nullptr;  // set when a point set holds a non-finite value
   CentreWs centre;      // common centre of the row and column sets
   KVPlan plan;
@@ -20,7 +20,6 @@ struct DegreeWs {
   PointPack rows, cols;
   FSpan wp, part;
   float* q = nullptr;
-  float* t = nullptr;
   float* w = nullptr;
   unsigned long long* colfix = nullptr;  // npad words: column sums of the symmetric row sums
   double* qsum = nullptr;                // twice qsum_words(npad): partial sums of q
@@ -54,14 +53,10 @@ void degree_run_dyadic(DegreeWs& w, const void* X, fd_dtype xt, int64_t N, int64
                        int64_t ldx, double beta0, int nb, double alpha, float* q, float* d,
                        float* s, double* s_off, hipStream_t stream);
 
-// Non-finite inputs.  scan: clear *flag, then set it if any of the N x D
-// values of X is NaN or infinite.  poison: when *flag is set, fill rows x cols
-// floats of v (leading dimension ld) with NaN.  Both asynchronous.
+// Clears *flag, then sets it if any of the N x D values of X is NaN or infinite
+// (asynchronous).
 void launch_scan_nonfinite(const void* X, fd_dtype xt, int64_t N, int64_t D, int64_t ldx,
-                           int* flag, bool clear, hipStream_t stream);
-void launch_poison(const int* flag, float* v, int64_t rows, int64_t cols, int64_t ld,
-                   hipStream_t stream);
-void launch_poison(const int* flag, double* v, int64_t n, hipStream_t stream);
+                           int* flag, hipStream_t stream);
 // Synchronous check for the eigensolver entry points: FD_ERR_INVALID_ARG when
 // X holds a non-finite value.
 void require_finite(const void* X, fd_dtype xt, int64_t N, int64_t D, int64_t ldx, int* flag,

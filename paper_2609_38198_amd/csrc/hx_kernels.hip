@@ -64,6 +64,7 @@
 
 #include "fd_profile.hpp"
 #include "kv_common.hpp"
+#include "sym_rowsum.hpp"
 
 namespace fd {
 
@@ -646,11 +647,11 @@ __device__ __forceinline__ void load_hx_col(HxCol<RID>& c, const uintx4* __restr
 // first (independent chains issue back to back and the exponentials can
 // overlap their tail), then K' = 2^t summed (times the weights) on the vector
 // ALUs.
-template <int RID, int NIB, bool UNIT, bool DIAG, bool SQ = false>
+template <int RID, int NIB, bool UNIT, bool DIAG>
 __device__ __forceinline__ void hx_rowsum_tile(const HxCol<RID>& c,
                                                const uintx4 (&br)[NIB][Hx<RID>::nb],
                                                float (&acc)[NIB], int64_t jb, int64_t ib0, int g,
-                                               int p, float (*acc2)[NIB] = nullptr) {
+                                               int p) {
   floatx4 t[NIB];
 #pragma unroll
   for (int ib = 0; ib < NIB; ++ib) {
@@ -670,11 +671,6 @@ __device__ __forceinline__ void hx_rowsum_tile(const HxCol<RID>& c,
       // one FMA per entry: as many vector instructions as the unit-weight sum
 #pragma unroll
       for (int r = 0; r < 4; ++r) acc[ib] = fmaf(k[r], c.w[r], acc[ib]);
-    }
-    if constexpr (SQ) {
-      // (K')^2 = 2^30 K^2: the kernel at twice the bandwidth, unit weights
-#pragma unroll
-      for (int r = 0; r < 4; ++r) (*acc2)[ib] = fmaf(k[r], k[r], (*acc2)[ib]);
     }
   }
 }
@@ -753,345 +749,45 @@ __attribute__((amdgpu_waves_per_eu(hx_plain_waves<RID, NIB>()))) void rowsum_hx_
 }
 
 // ------------------------------------------------------------------ symmetric row sums
-//
-// When rows and columns are the same N points, K is symmetric and each
-// off-diagonal tile K_IJ can serve both sums: q_I += K_IJ w_J along its rows and
-// q_J += K_IJ^T w_I along its columns, so every kernel entry off the diagonal
-// blocks is evaluated (and exponentiated) once instead of twice.
-//
-// Points are grouped in blocks of 512 (one workgroup's 4 waves x 8 row tiles);
-// with B blocks and h = (B - 1) / 2, the workgroup of block P takes its own
-// block (row sums only, exact diagonal) and then the blocks P + 1 .. P + h
-// (mod B), plus P + B/2 when B is even and P < B/2: every unordered pair of
-// distinct blocks is then taken exactly once.  That column range is split over
-// nsplit workgroups.  Row sums go to per-split partials as in the plain kernel.
-// Column sums are reduced over the wave's 128 rows (in-lane over its row
-// tiles, then across the 16 lanes of a DPP row), converted to 64-bit fixed
-// point and added into a per-workgroup LDS array with integer LDS atomics; every
-// SYM_CHUNK column tiles the workgroup adds that array into the global
-// per-point accumulator with integer atomics.  Integer addition is exact and
-// order-free, so the result is bitwise reproducible.  (Global atomics inside
-// the tile loop would make each operand-load wait also wait for an atomic's
-// round trip, since vector memory operations retire in order.)  The
-// fixed-point scale assumes weights in [0, 1] (the normalisation weights
-// q^-alpha with q >= 1 are) and leaves a factor 4 of headroom below 2^63 for
-// the total.
 
-// Column tiles whose fixed-point column sums a workgroup gathers in LDS
-// (SYM_CHUNK x 16 x 8 bytes) before adding them into global memory; even.
-constexpr int SYM_CHUNK = 256;
-
-// Sum of v over the 16 lanes of the lane's DPP row (every lane gets the sum).
-__device__ __forceinline__ float dpp_row_sum(float v) {
-  // xor 1 and xor 2 inside quads, then mirrored quads and mirrored half-rows
-  v += __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), 0xB1,
-                                                             0xF, 0xF, false));
-  v += __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), 0x4E,
-                                                             0xF, 0xF, false));
-  v += __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), 0x141,
-                                                             0xF, 0xF, false));
-  v += __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), 0x140,
-                                                             0xF, 0xF, false));
-  return v;
-}
-
-// One pipeline step of the symmetric row sums.  t holds the exponent tiles of
-// an off-diagonal column tile J against the wave's NIB row tiles; each is
-// exponentiated and then overwritten with the exponent tile of the next column
-// tile (operands xn), so the matrix-core chain of row tile ib runs alongside
-// the vector work of row tiles ib + 1, ...  SUMS: add J's row sums into acc and
-// its column sums into the fixed-point accumulator (false for padding tiles).
-template <int RID, int NIB, bool UNIT, bool SUMS, bool SQ>
-__device__ __forceinline__ void hx_sym_step(floatx4 (&t)[NIB], const uintx4* xn,
-                                            const uintx4 (&br)[NIB][Hx<RID>::nb],
-                                            const floatx4& w, const float (&wi)[NIB],
-                                            float (&acc)[NIB], float (&acc2)[NIB], int64_t jl,
-                                            double fix_scale, double fix_scale2,
-                                            unsigned long long* lds_col,
-                                            unsigned long long* lds_col2, int g, int p) {
-  float cs[4] = {0.f, 0.f, 0.f, 0.f};
-  float cs2[4] = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-  for (int ib = 0; ib < NIB; ++ib) {
-    float k[4];
-    if (SUMS) {
-#pragma unroll
-      for (int r = 0; r < 4; ++r) k[r] = __builtin_amdgcn_exp2f(t[ib][r]);
-    }
-    t[ib] = hx_exponent<RID, false>(xn, br[ib], g, p);
-    if (SUMS) {
-      if (UNIT) {
-        acc[ib] += (k[0] + k[1]) + (k[2] + k[3]);
-#pragma unroll
-        for (int r = 0; r < 4; ++r) cs[r] += k[r];
-      } else {
-#pragma unroll
-        for (int r = 0; r < 4; ++r) {
-          acc[ib] = fmaf(k[r], w[r], acc[ib]);
-          cs[r] = fmaf(k[r], wi[ib], cs[r]);
-        }
-        if constexpr (SQ) {
-          // the squared kernel (K at twice the bandwidth) with unit weights,
-          // along the rows and along the columns of the tile
-#pragma unroll
-          for (int r = 0; r < 4; ++r) {
-            acc2[ib] = fmaf(k[r], k[r], acc2[ib]);
-            cs2[r] = fmaf(k[r], k[r], cs2[r]);
-          }
-        }
-      }
-    }
-  }
-  if (!SUMS) return;
-  // the row sums are due here (an empty statement reading them), not sunk
-  // past the column-sum atomic below, so that they interleave too
-#pragma unroll
-  for (int ib = 0; ib < NIB; ++ib) {
-    asm volatile("" ::"v"(acc[ib]));
-    if constexpr (SQ) asm volatile("" ::"v"(acc2[ib]));
-  }
-  // Interleave the contraction with the exponentials and sums (left to
-  // itself the scheduler issues the exponentials first, then the matrix
-  // instructions with little vector work between them).
-  sched_interleave<Hx<RID>::nm * NIB, 4 * NIB, SQ ? 5 : 3>();
-  // lane (g, p) holds, for column 4g + r of the tile, the sum over rows p of
-  // the wave's tiles; the 16 lanes of DPP row g hold the wave's other rows
-#pragma unroll
-  for (int r = 0; r < 4; ++r) cs[r] = dpp_row_sum(cs[r]);
-  // lane p < 4 adds column 4g + p (selects, no branches)
-  const float v01 = (p & 1) ? cs[1] : cs[0];
-  const float v23 = (p & 1) ? cs[3] : cs[2];
-  const float v = (p & 2) ? v23 : v01;
-  const long long fx = __double2ll_rn(double(v) * fix_scale);
-  if (p < 4) atomicAdd(lds_col + jl * TILE + 4 * g + p, static_cast<unsigned long long>(fx));
-  if constexpr (SQ) {
-#pragma unroll
-    for (int r = 0; r < 4; ++r) cs2[r] = dpp_row_sum(cs2[r]);
-    const float u01 = (p & 1) ? cs2[1] : cs2[0];
-    const float u23 = (p & 1) ? cs2[3] : cs2[2];
-    const float u = (p & 2) ? u23 : u01;
-    const long long fx2 = __double2ll_rn(double(u) * fix_scale2);
-    if (p < 4) atomicAdd(lds_col2 + jl * TILE + 4 * g + p, static_cast<unsigned long long>(fx2));
-  }
-}
-
-// SQ (weighted passes only): also the row and column sums of the squared
-// kernel, K^2 1 = K(2 beta) 1 (eq. kernel), into part2 / colfix2 with the scale
-// fix_scale2 per unit of (2^15 K)^2.
-template <int RID, int NIB, bool UNIT, bool SQ = false>
-__global__ __launch_bounds__(WG_THREADS)
-__attribute__((amdgpu_waves_per_eu(hx_sym_waves<RID, NIB, SQ>()))) void rowsum_sym_hx_kernel(
-    const uintx4* __restrict__ xc, const floatx4* __restrict__ wp, const uintx4* __restrict__ xr,
-    int64_t nblk, int64_t njb, int64_t jb_per_split, int64_t nsplit, float* __restrict__ part,
-    int64_t nrpad, unsigned long long* __restrict__ colfix, double fix_scale,
-    float* __restrict__ part2, unsigned long long* __restrict__ colfix2, double fix_scale2,
-    HxGate gate) {
-  static_assert(!(SQ && UNIT), "squared sums ride on a weighted pass");
-  if (hx_gate_closed(gate)) return;
-  constexpr int NB = Hx<RID>::nb;
-  constexpr int NC = Hx<RID>::nc;
-  constexpr int BT = 4 * NIB;  // tiles per block
-  const int lane = threadIdx.x & 63;
-  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const int wr = xcd_remap(blockIdx.x, gridDim.x);
-  // whole-block splits: number the workgroups by the block c their window
-  // starts at (c = P + split * blocks per split), so that consecutive ids (run
-  // together on one XCD) read the same column tiles
-  const int64_t jbk = jb_per_split / BT;
-  int64_t split, P;
-  if (jb_per_split % BT == 0) {
-    const int64_t c = wr / nsplit;
-    split = wr % nsplit;
-    P = ((c - split * jbk) % nblk + nblk) % nblk;
-  } else {
-    split = wr / nblk;
-    P = wr % nblk;
-  }
-  const int64_t ib0 = P * BT + wave * NIB;
-  const int64_t h = (nblk - 1) / 2;
-  const int64_t span = BT * (1 + h + ((nblk % 2 == 0 && 2 * P < nblk) ? 1 : 0));
-  const int64_t jj_begin = split * jb_per_split;
-  const int64_t jj_end = min(span, jj_begin + jb_per_split);
-  const int64_t ntile = nblk * BT;
-  const int g = lane >> 4, p = lane & 15;
-  // fixed-point column sums of the current chunk of SYM_CHUNK tiles
-  __shared__ unsigned long long lds_col[SYM_CHUNK * TILE];
-  __shared__ unsigned long long lds_col2[SQ ? SYM_CHUNK * TILE : 1];
-  for (int e = threadIdx.x; e < SYM_CHUNK * TILE; e += WG_THREADS) {
-    lds_col[e] = 0ull;
-    if constexpr (SQ) lds_col2[e] = 0ull;
-  }
-  __syncthreads();
-
-  uintx4 br[NIB][NB];
-  float wi[NIB];
-#pragma unroll
-  for (int ib = 0; ib < NIB; ++ib) {
-#pragma unroll
-    for (int ch = 0; ch < NB; ++ch) br[ib][ch] = xr[((ib0 + ib) * NB + ch) * 64 + lane];
-    // weight of own row 16 (ib0 + ib) + p: pack element (tile, lane 16 (p / 4), p % 4);
-    // own tiles past the column pack are padding rows (their kernel values are 0)
-    wi[ib] = 0.f;
-    if (!UNIT && ib0 + ib < njb)
-      wi[ib] = reinterpret_cast<const float*>(wp)[((ib0 + ib) * 64 + 16 * (p >> 2)) * 4 + (p & 3)];
-  }
-  float acc[NIB], tot[NIB], acc2[NIB], tot2[NIB];
-#pragma unroll
-  for (int ib = 0; ib < NIB; ++ib) acc[ib] = tot[ib] = acc2[ib] = tot2[ib] = 0.f;
-
-  // column tile of range position jj (0 <= jj < span <= ntile + BT, cyclic over
-  // the blocks); -1 for the padding tiles past the real columns
-  const int base = int(P * BT), nt32 = int(ntile), njb32 = int(njb);
-  auto tile_of = [&](int64_t jj) -> int {
-    int J = base + int(jj);
-    if (J >= nt32) J -= nt32;
-    return J < njb32 ? J : -1;
+// Tile policy of the symmetric row sums (sym_rowsum.hpp).
+template <int RID>
+struct HxTile {
+  static constexpr float ONE = 32768.f;  // 2^SHIFT
+  static constexpr int NM = Hx<RID>::nm, EXTRA = 0;
+  struct Args {
+    const uintx4* xc;
+    const uintx4* xr;
   };
-  // tile loaded for range position jj of [lo, jj_end): clamped into the range,
-  // padding tiles read tile 0, so that loads are unconditional and every path
-  // keeps the same loads in flight
-  auto load_tile = [&](int64_t jj, int64_t lo) -> int64_t {
-    const int J = tile_of(max(min(jj, jj_end - 1), lo));
-    return J < 0 ? 0 : J;
+  struct Row {
+    uintx4 b[Hx<RID>::nb];
   };
-  int chunk = 0;
-  auto row_chunk = [&](int tiles) {
-    chunk += tiles;
-    if (chunk >= CHUNK_TILES) {
-      chunk = 0;
-#pragma unroll
-      for (int ib = 0; ib < NIB; ++ib) {
-        tot[ib] += acc[ib];
-        acc[ib] = 0.f;
-        if constexpr (SQ) {
-          tot2[ib] += acc2[ib];
-          acc2[ib] = 0.f;
-        }
-      }
-    }
+  struct Col {
+    uintx4 a[Hx<RID>::nc];
   };
-
-  // The workgroup's own block (range positions below BT, in split 0 only):
-  // plain row sums, exact diagonal.  Column tiles stream through two buffers
-  // used in turn.
-  const int64_t own_end = min(jj_end, int64_t(BT));
-  if (jj_begin < own_end) {
-    auto step = [&](const HxCol<RID>& c, int64_t jj) {
-      const int J = tile_of(jj);
-      if (J < 0) return;
-      if (J >= ib0 && J < ib0 + NIB)
-        hx_rowsum_tile<RID, NIB, UNIT, true, SQ>(c, br, acc, J, ib0, g, p, &acc2);
-      else
-        hx_rowsum_tile<RID, NIB, UNIT, false, SQ>(c, br, acc, J, ib0, g, p, &acc2);
-    };
-    HxCol<RID> b0, b1;
-    b0.w = b1.w = floatx4{1.f, 1.f, 1.f, 1.f};
-    load_hx_col<RID, UNIT>(b0, xc, wp, load_tile(jj_begin, jj_begin), lane);
-    __builtin_amdgcn_sched_barrier(0);  // b0's loads ahead of b1's, as in the loop
-    load_hx_col<RID, UNIT>(b1, xc, wp, load_tile(min(jj_begin + 1, own_end - 1), jj_begin),
-                           lane);
-    for (int64_t jj = jj_begin; jj < own_end; jj += 2) {
-      step(b0, jj);
-      load_hx_col<RID, UNIT>(b0, xc, wp, load_tile(min(jj + 2, own_end - 1), jj_begin), lane);
-      if (jj + 1 < own_end) step(b1, jj + 1);
-      load_hx_col<RID, UNIT>(b1, xc, wp, load_tile(min(jj + 3, own_end - 1), jj_begin), lane);
-      row_chunk(2);
-    }
+  template <int NIB, bool SQ>
+  static constexpr int waves() {
+    return hx_sym_waves<RID, NIB, SQ>();
   }
-
-  // The other blocks: each tile serves both sums.  Two-stage pipeline over
-  // the tiles u = 0, 1, ... of [s0, jj_end): step u exponentiates and sums
-  // tile u, whose exponents the previous step made, while the matrix cores
-  // make those of tile u + 1 (hx_sym_step).  Tile v's column operands sit in
-  // slot v % 2 and are loaded two steps ahead of their contraction, its
-  // weights one step ahead of its sums.
-  const int64_t s0 = max(jj_begin, int64_t(BT));
-  const int64_t n2 = jj_end - s0;
-  if (n2 > 0) {
-    uintx4 xa[2][NC];
-    floatx4 w[2];
-    floatx4 t[NIB];
-    w[0] = w[1] = floatx4{1.f, 1.f, 1.f, 1.f};
-    auto load_xa = [&](uintx4 (&dst)[NC], int64_t u) {
-      const int64_t J = load_tile(s0 + u, s0);
+  static __device__ __forceinline__ void load_row(Row& r, const Args& a, int64_t tile, int lane) {
 #pragma unroll
-      for (int ch = 0; ch < NC; ++ch) dst[ch] = xc[(J * NC + ch) * 64 + lane];
-    };
-    auto load_w = [&](floatx4& dst, int64_t u) {
-      if (!UNIT) dst = wp[load_tile(s0 + u, s0) * 64 + lane];
-    };
-    load_xa(xa[0], 0);
-    load_w(w[0], 0);
-    __builtin_amdgcn_sched_barrier(0);
-    load_xa(xa[1], 1);
-    // consume the row operands here (an empty statement reading them): their
-    // loads complete before the loop, whose waits then only ever cover the
-    // column operands a step consumes (left to itself the compiler sinks these
-    // loads past the loop entry and every iteration waits for all loads)
-#pragma unroll
-    for (int ib = 0; ib < NIB; ++ib)
-#pragma unroll
-      for (int ch = 0; ch < NB; ++ch) asm volatile("" ::"v"(br[ib][ch]));
-    // likewise the scalar kernel argument used in the loop: with its load done
-    // here, the loop's LDS atomics (which share the counter) are never waited on
-    asm volatile("" ::"s"(fix_scale));
-#pragma unroll
-    for (int ib = 0; ib < NIB; ++ib) t[ib] = hx_exponent<RID, false>(xa[0], br[ib], g, p);
-    // step u (slot S = u % 2): operands of tile u + 2 into slot S, weights of
-    // tile u + 1 into slot S ^ 1, sums of tile u with weights from slot S,
-    // contraction of tile u + 1 from slot S ^ 1
-    auto pipe_step = [&](auto S_, int64_t u) {
-      constexpr int S = decltype(S_)::value;
-      load_xa(xa[S], u + 2);
-      load_w(w[S ^ 1], u + 1);
-      const int J = tile_of(s0 + u);
-      const int64_t jl = (s0 + u - jj_begin) % SYM_CHUNK;
-      if (J >= 0)
-        hx_sym_step<RID, NIB, UNIT, true, SQ>(t, xa[S ^ 1], br, w[S], wi, acc, acc2, jl,
-                                              fix_scale, fix_scale2, lds_col, lds_col2, g, p);
-      else
-        hx_sym_step<RID, NIB, UNIT, false, SQ>(t, xa[S ^ 1], br, w[S], wi, acc, acc2, jl,
-                                               fix_scale, fix_scale2, lds_col, lds_col2, g, p);
-      row_chunk(1);
-      // end of a chunk of column tiles (the trip count is uniform over the
-      // workgroup): add the chunk's column sums into the global accumulator
-      const int64_t done = s0 + u + 1 - jj_begin;
-      if (done % SYM_CHUNK == 0 || s0 + u + 1 >= jj_end) {
-        const int64_t c0 = jj_begin + (done - 1) / SYM_CHUNK * SYM_CHUNK;
-        __syncthreads();
-        for (int e = threadIdx.x; e < SYM_CHUNK * TILE; e += WG_THREADS) {
-          const unsigned long long v = lds_col[e];
-          const int Jc = c0 + e / TILE < jj_end ? tile_of(c0 + e / TILE) : -1;
-          if (v != 0ull && Jc >= 0) atomicAdd(colfix + int64_t(Jc) * TILE + e % TILE, v);
-          lds_col[e] = 0ull;
-          if constexpr (SQ) {
-            const unsigned long long v2 = lds_col2[e];
-            if (v2 != 0ull && Jc >= 0) atomicAdd(colfix2 + int64_t(Jc) * TILE + e % TILE, v2);
-            lds_col2[e] = 0ull;
-          }
-        }
-        __syncthreads();
-      }
-    };
-    for (int64_t u = 0; u < n2; u += 2) {
-      pipe_step(std::integral_constant<int, 0>{}, u);
-      if (u + 1 < n2) pipe_step(std::integral_constant<int, 1>{}, u + 1);
-    }
+    for (int ch = 0; ch < Hx<RID>::nb; ++ch) r.b[ch] = a.xr[(tile * Hx<RID>::nb + ch) * 64 + lane];
   }
+  static __device__ __forceinline__ void load_col(Col& c, const Args& a, int64_t tile, int lane) {
 #pragma unroll
-  for (int ib = 0; ib < NIB; ++ib) {
-    float v = (tot[ib] + acc[ib]) * 0x1p-15f;
-    v += __shfl_xor(v, 16);
-    v += __shfl_xor(v, 32);
-    if (g == 0) part[split * nrpad + (ib0 + ib) * TILE + p] = v;
-    if constexpr (SQ) {
-      float v2 = (tot2[ib] + acc2[ib]) * 0x1p-30f;
-      v2 += __shfl_xor(v2, 16);
-      v2 += __shfl_xor(v2, 32);
-      if (g == 0) part2[split * nrpad + (ib0 + ib) * TILE + p] = v2;
-    }
+    for (int ch = 0; ch < Hx<RID>::nc; ++ch) c.a[ch] = a.xc[(tile * Hx<RID>::nc + ch) * 64 + lane];
   }
-}
+  static __device__ __forceinline__ void consume(const Row& r) {
+#pragma unroll
+    for (int ch = 0; ch < Hx<RID>::nb; ++ch) asm volatile("" ::"v"(r.b[ch]));
+  }
+  static __device__ __forceinline__ floatx4 tile(const Col& c, const Row& r) {
+    return hx_exponent<RID, false>(c.a, r.b, 0, 0);
+  }
+  static __device__ __forceinline__ float value(float t, const Row&, const Args&) {
+    return __builtin_amdgcn_exp2f(t);
+  }
+};
 
 // ------------------------------------------------------------------ host dispatch
 
@@ -1171,43 +867,37 @@ void rowsum_hx_u(const KVPlan& p, const PointPack& rows, const PointPack& cols, 
 template <int RID, int NIB, bool UNIT, bool SQ>
 void rowsum_sym_hx_launch(const KVPlan& p, const PointPack& rows, const PointPack& cols,
                           const float* wp, float* part, unsigned long long* colfix,
-                          double fix_scale, const SymSquares& sq, hipStream_t stream) {
+                          int frac, const SymSquares& sq, hipStream_t stream) {
   const unsigned grid = unsigned(p.nrt * p.nsplit);
-  hipLaunchKernelGGL((rowsum_sym_hx_kernel<RID, NIB, UNIT, SQ>), dim3(grid), dim3(WG_THREADS), 0,
-                     stream, reinterpret_cast<const uintx4*>(cols.xp.p),
-                     reinterpret_cast<const floatx4*>(wp),
-                     reinterpret_cast<const uintx4*>(rows.xp.p), p.nrt, p.njb, p.jb_per_split,
-                     int64_t(p.nsplit), part, rows.npad, colfix, fix_scale, sq.part, sq.colfix,
-                     sq.fix_scale, gate_of(rows));
+  const typename HxTile<RID>::Args ta{reinterpret_cast<const uintx4*>(cols.xp.p),
+                                      reinterpret_cast<const uintx4*>(rows.xp.p)};
+  hipLaunchKernelGGL((rowsum_sym_kernel<HxTile<RID>, NIB, UNIT, SQ>), dim3(grid),
+                     dim3(WG_THREADS), 0, stream, ta, reinterpret_cast<const floatx4*>(wp), p.nrt,
+                     p.njb, p.jb_per_split,
+                     int64_t(p.nsplit), part, rows.npad, colfix,
+                     std::ldexp(1.0 / HxTile<RID>::ONE, frac), sq.part, sq.colfix,
+                     std::ldexp(1.0 / (double(HxTile<RID>::ONE) * HxTile<RID>::ONE), frac),
+                     gate_of(rows));
   FD_LAUNCH_CHECK();
 }
 
 template <int RID>
 void rowsum_sym_hx_u(const KVPlan& p, const PointPack& rows, const PointPack& cols,
-                     const float* wp, float* part, unsigned long long* colfix, double fix_scale,
+                     const float* wp, float* part, unsigned long long* colfix, int frac,
                      const SymSquares& sq, hipStream_t stream) {
   if (sq.part != nullptr) {
     // squared sums: weighted passes of the eight-tile plan only
     FD_REQUIRE(p.nib == 8 && wp != nullptr, FD_ERR_INVALID_ARG,
                "internal: squared sums need a weighted eight-tile pass");
-    rowsum_sym_hx_launch<RID, 8, false, true>(p, rows, cols, wp, part, colfix, fix_scale, sq,
+    rowsum_sym_hx_launch<RID, 8, false, true>(p, rows, cols, wp, part, colfix, frac, sq,
                                               stream);
-    return;
-  }
-  if (p.nib == 4) {
-    if (wp == nullptr)
-      rowsum_sym_hx_launch<RID, 4, true, false>(p, rows, cols, wp, part, colfix, fix_scale, sq,
-                                                stream);
-    else
-      rowsum_sym_hx_launch<RID, 4, false, false>(p, rows, cols, wp, part, colfix, fix_scale, sq,
-                                                 stream);
     return;
   }
   if (wp == nullptr)
-    rowsum_sym_hx_launch<RID, 8, true, false>(p, rows, cols, wp, part, colfix, fix_scale, sq,
+    rowsum_sym_hx_launch<RID, 8, true, false>(p, rows, cols, wp, part, colfix, frac, sq,
                                               stream);
   else
-    rowsum_sym_hx_launch<RID, 8, false, false>(p, rows, cols, wp, part, colfix, fix_scale, sq,
+    rowsum_sym_hx_launch<RID, 8, false, false>(p, rows, cols, wp, part, colfix, frac, sq,
                                                stream);
 }
 
@@ -1360,11 +1050,11 @@ void launch_product_hx(const KVPlan& p, const PointPack& rows, const PointPack& 
 
 void launch_rowsum_sym_hx(const KVPlan& p, const PointPack& rows, const PointPack& cols,
                           const float* wp, float* part, unsigned long long* colfix,
-                          double fix_scale, const SymSquares& sq, hipStream_t stream) {
+                          int frac, const SymSquares& sq, hipStream_t stream) {
   FD_REQUIRE(rows.rid >= 0 && rows.rid < HX_RECIPES && rows.rid == cols.rid && rows.row_side &&
                  !cols.row_side && rows.n == cols.n,
              FD_ERR_INVALID_ARG, "internal: symmetric row sums need one point set");
-  FD_REQUIRE((p.nib == 4 || p.nib == 8) && p.nrt * 4 * p.nib * TILE == rows.npad &&
+  FD_REQUIRE(p.nib == 8 && p.nrt * 4 * p.nib * TILE == rows.npad &&
                  p.njb == ceil_div(cols.n, TILE),
              FD_ERR_INVALID_ARG, "internal: symmetric row-sum plan");
   dual_dispatch(rows, cols, FD_KERNEL_ROWSUM, stream, [&](const PointPack& r, const PointPack& c) {
@@ -1372,13 +1062,13 @@ void launch_rowsum_sym_hx(const KVPlan& p, const PointPack& rows, const PointPac
     check_span(r.xp, size_t(r.npad / TILE) * R.nb * 64 * 4, "split row pack");
     check_span(c.xp, size_t(round_up(p.njb, 2)) * R.nc * 64 * 4, "split column pack");
     switch (r.rid) {
-      case 0: return rowsum_sym_hx_u<0>(p, r, c, wp, part, colfix, fix_scale, sq, stream);
-      case 1: return rowsum_sym_hx_u<1>(p, r, c, wp, part, colfix, fix_scale, sq, stream);
-      case 2: return rowsum_sym_hx_u<2>(p, r, c, wp, part, colfix, fix_scale, sq, stream);
-      case 3: return rowsum_sym_hx_u<3>(p, r, c, wp, part, colfix, fix_scale, sq, stream);
-      case 4: return rowsum_sym_hx_u<4>(p, r, c, wp, part, colfix, fix_scale, sq, stream);
-      case 5: return rowsum_sym_hx_u<5>(p, r, c, wp, part, colfix, fix_scale, sq, stream);
-      case 6: return rowsum_sym_hx_u<6>(p, r, c, wp, part, colfix, fix_scale, sq, stream);
+      case 0: return rowsum_sym_hx_u<0>(p, r, c, wp, part, colfix, frac, sq, stream);
+      case 1: return rowsum_sym_hx_u<1>(p, r, c, wp, part, colfix, frac, sq, stream);
+      case 2: return rowsum_sym_hx_u<2>(p, r, c, wp, part, colfix, frac, sq, stream);
+      case 3: return rowsum_sym_hx_u<3>(p, r, c, wp, part, colfix, frac, sq, stream);
+      case 4: return rowsum_sym_hx_u<4>(p, r, c, wp, part, colfix, frac, sq, stream);
+      case 5: return rowsum_sym_hx_u<5>(p, r, c, wp, part, colfix, frac, sq, stream);
+      case 6: return rowsum_sym_hx_u<6>(p, r, c, wp, part, colfix, frac, sq, stream);
     }
   });
 }

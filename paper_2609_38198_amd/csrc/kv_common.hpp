@@ -21,19 +21,30 @@ constexpr int CHUNK_TILES = 64;  // column tiles per partial accumulator
 // Which of the two layouts of a float32 pack a launch serves (PointPack):
 // every launch of such a pair reads the same device word, and the one whose
 // layout does not match the exponent budget exits before any work.
+// vbad (single-column products): whether the column holds a value that the
+// symmetric row sums cannot take; the launch serves one of the two cases.
 struct HxGate {
-  const unsigned long long* r2max;
-  double bl;    // beta log2(e) of the pack
-  int variant;  // 0: no choice, 1: short layout, 2: full-offset layout
+  const unsigned long long* r2max = nullptr;
+  double bl = 0.0;  // beta log2(e) of the pack
+  int variant = 0;  // 0: no choice, 1: short layout, 2: full-offset layout
+  const float* vbad = nullptr;
+  int serves_bad = 0;
 };
 __device__ __forceinline__ bool hx_gate_closed(const HxGate& g) {
+  if (g.vbad != nullptr && (*g.vbad != 0.f) != (g.serves_bad != 0)) return true;
   if (g.variant == 0) return false;
   const double r2 = __longlong_as_double(static_cast<long long>(*g.r2max));
   const bool wide = g.bl * r2 > EXP_BUDGET;
   return wide != (g.variant == 2);
 }
 inline HxGate gate_of(const PointPack& rows) {
-  return HxGate{rows.r2max, rows.beta * LOG2E, rows.variant};
+  HxGate g;
+  g.r2max = rows.r2max;
+  g.bl = rows.beta * LOG2E;
+  g.variant = rows.variant;
+  g.vbad = rows.vbad;
+  g.serves_bad = rows.serves_bad;
+  return g;
 }
 
 // Workgroups of one dispatch are spread over the eight XCDs round-robin by
@@ -94,7 +105,9 @@ constexpr int PACK_THREADS = 128;  // workgroup of the pack kernels
 
 // The V part of a pack launch: V (n x b, ldv) times sr, as the split pack of
 // ncb 16-column blocks over npairs pairs of 16-point tiles, or (ncb = 0) as the
-// weight pack of its one column over ntiles tiles.
+// weight pack of its one column over ntiles tiles; with nvmax that column is
+// scaled by 2^-e to below 1 (colscale[0] = e, colscale[1] = 1 where it holds a
+// NaN or an infinity, else 0).
 struct PackV {
   const float* V = nullptr;
   const float* sr = nullptr;
@@ -122,6 +135,23 @@ __device__ __forceinline__ void pack_v_block(const PackV& a, int64_t blk, int* e
   const int lane = int(threadIdx.x & 63);
   const int g = lane >> 4, p = lane & 15;
   if (a.ncb == 0) {
+    int ex1 = 0;
+    if (a.nvmax > 0) {
+      float m = 0.f, bad = 0.f;
+      for (int k = lane; k < a.nvmax; k += 64) {
+        m = fmaxf(m, a.vpart[k * 64]);
+        bad = fmaxf(bad, a.vpart[k * 64 + 1]);
+      }
+      for (int o = 32; o > 0; o >>= 1) {
+        m = fmaxf(m, __shfl_xor(m, o));
+        bad = fmaxf(bad, __shfl_xor(bad, o));
+      }
+      ex1 = bad != 0.f ? 0 : 14 - vscale_exponent(m);
+      if (idx == 0) {
+        a.colscale[0] = float(ex1);
+        a.colscale[1] = bad;
+      }
+    }
     if (idx >= a.ntiles * 64) return;
     floatx4 out;
 #pragma unroll
@@ -129,6 +159,7 @@ __device__ __forceinline__ void pack_v_block(const PackV& a, int64_t blk, int* e
       const int64_t j = (idx >> 6) * TILE + 4 * g + r;
       out[r] = 0.f;
       if (j < a.n) out[r] = a.sr != nullptr ? a.sr[j] * a.V[j * a.ldv] : a.V[j * a.ldv];
+      out[r] = ldexpf(out[r], -ex1);
     }
     a.wp[idx] = out;
     return;
@@ -245,13 +276,12 @@ void launch_rowsum_hx(const KVPlan& p, const PointPack& rows, const PointPack& c
                       const float* wp, bool diag, float* out, float* part, hipStream_t stream);
 // Symmetric row sums of one point set (rows.n == cols.n): per-split row partials
 // into part ([nsplit][rows.npad]) and column sums added into colfix (64-bit fixed
-// point, fix_scale per unit of the shifted kernel 2^15 K; weights in [0, 1]).
-// With sq.part set (weighted passes only), the unit-weight sums of the squared
-// kernel K^2 (the kernel at twice the bandwidth) go the same way into sq.part
-// and sq.colfix, sq.fix_scale per unit of (2^15 K)^2.
+// point with `frac` fractional bits; weights in [-1, 1]).  With sq.part set
+// (weighted passes only), the unit-weight sums of the squared kernel K^2 (the
+// kernel at twice the bandwidth) go the same way into sq.part and sq.colfix.
 void launch_rowsum_sym_hx(const KVPlan& p, const PointPack& rows, const PointPack& cols,
-                          const float* wp, float* part, unsigned long long* colfix,
-                          double fix_scale, const SymSquares& sq, hipStream_t stream);
+                          const float* wp, float* part, unsigned long long* colfix, int frac,
+                          const SymSquares& sq, hipStream_t stream);
 
 // Scheduling pattern for a region holding M matrix instructions and E
 // exponentials: each matrix instruction followed by its share of the

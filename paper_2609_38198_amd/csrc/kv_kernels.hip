@@ -16,6 +16,7 @@
 
 #include "fd_profile.hpp"
 #include "kv_common.hpp"
+#include "sym_rowsum.hpp"
 
 namespace fd {
 
@@ -145,6 +146,7 @@ __device__ __forceinline__ void prologue_vmax(const PrologueArgs& a, int blk, fl
   const int64_t rpb = (a.nv + a.nblkv - 1) / a.nblkv;
   const int64_t r0 = int64_t(blk) * rpb, r1 = min(a.nv, r0 + rpb);
   float m = 0.f;
+  bool ok = true;
   if (c < a.b) {
     for (int64_t i = r0 + rl; i < r1; i += 4 * nrl) {
       float v[4];
@@ -155,8 +157,16 @@ __device__ __forceinline__ void prologue_vmax(const PrologueArgs& a, int blk, fl
         if (a.sr != nullptr) v[u] *= a.sr[r];
       }
 #pragma unroll
-      for (int u = 0; u < 4; ++u) m = fmaxf(m, fabsf(v[u]));
+      for (int u = 0; u < 4; ++u) {
+        m = fmaxf(m, fabsf(v[u]));
+        ok = ok && isfinite(v[u]);
+      }
     }
+  }
+  if (a.b == 1) {
+    // one column: also whether it is finite (pack_v_block)
+    const int bad = __syncthreads_or(ok ? 0 : 1);
+    if (threadIdx.x == 0) a.vpart[blk * 64 + 1] = bad ? 1.f : 0.f;
   }
   red[threadIdx.x] = m;
   __syncthreads();
@@ -326,16 +336,6 @@ __global__ void pack_w_kernel(const float* __restrict__ w, int64_t n, int64_t nt
     out[r] = (j < n) ? w[j] : 0.f;
   }
   wp[idx] = out;
-}
-
-// Y[i] = sl[i] * t[i] (sl NULL: copy), Y with row stride ldy.
-__global__ void scale_rows_kernel(const float* __restrict__ t, const float* __restrict__ sl,
-                                  int64_t n, float* __restrict__ Y, int64_t ldy,
-                                  PoisonGate poison) {
-  const int64_t i = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
-  if (i >= n) return;
-  const float y = (sl != nullptr) ? sl[i] * t[i] : t[i];
-  Y[i * ldy] = poisoned(poison) ? __builtin_nanf("") : y;
 }
 
 // 2^t clamped to [0, 1]: the exponent of a true kernel value is <= 0 and
@@ -744,7 +744,8 @@ rowsum_bf16_kernel(
     const uintx4* __restrict__ xa, const floatx4* __restrict__ aj, const floatx4* __restrict__ wp,
     const uintx4* __restrict__ xb, const float* __restrict__ ar, int64_t nrt, int64_t njb,
     int64_t jb_per_split, int diag, float scale2, float* __restrict__ out, int64_t Nr,
-    float* __restrict__ part, int64_t nrpad) {
+    float* __restrict__ part, int64_t nrpad, HxGate gate) {
+  if (hx_gate_closed(gate)) return;
   const int lane = threadIdx.x & 63;
   const int wave = threadIdx.x >> 6;
   const int wr = xcd_remap(blockIdx.x, gridDim.x);
@@ -812,6 +813,85 @@ rowsum_bf16_kernel(
         out[i] = v;
     }
   }
+}
+
+// Tile policy of the symmetric row sums (sym_rowsum.hpp).  fd_degree plus a
+// 64-column product at N = 131,072, D = 64 takes 10.3 ms with it and 14.0 ms
+// with the plain sums (each entry evaluated twice).  The accumulator
+// starts at the column offsets -r_j / 2, and K = 2^(scale2 u + c_i) with
+// c_i = -scale2 r_i / 2 per row (one FMA per entry), clamped to [0, 1].
+template <int DC>
+struct Bf16Tile {
+  static constexpr float ONE = 1.f;
+  static constexpr int NM = DC, EXTRA = 3;
+  struct Args {
+    const uintx4* xa;
+    const floatx4* aj;
+    const uintx4* xb;
+    const float* ar;
+    float scale2;
+  };
+  struct Row {
+    uintx4 b[DC];
+    float c;
+  };
+  struct Col {
+    uintx4 a[DC];
+    floatx4 off;
+  };
+  template <int NIB, bool SQ>
+  static constexpr int waves() {
+    return 2;
+  }
+  static __device__ __forceinline__ void load_row(Row& r, const Args& a, int64_t tile, int lane) {
+#pragma unroll
+    for (int c = 0; c < DC; ++c) r.b[c] = a.xb[(tile * DC + c) * 64 + lane];
+    r.c = a.scale2 * a.ar[tile * TILE + (lane & 15)];
+  }
+  static __device__ __forceinline__ void load_col(Col& c, const Args& a, int64_t tile, int lane) {
+#pragma unroll
+    for (int k = 0; k < DC; ++k) c.a[k] = a.xa[(tile * DC + k) * 64 + lane];
+    c.off = a.aj[tile * 64 + lane];
+  }
+  static __device__ __forceinline__ void consume(const Row& r) {
+#pragma unroll
+    for (int c = 0; c < DC; ++c) asm volatile("" ::"v"(r.b[c]));
+    asm volatile("" ::"v"(r.c));
+  }
+  static __device__ __forceinline__ floatx4 tile(const Col& c, const Row& r) {
+    floatx4 t = c.off;
+#pragma unroll
+    for (int k = 0; k < DC; ++k)
+      t = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, c.a[k]),
+                                                  __builtin_bit_cast(bf16x8, r.b[k]), t, 0, 0, 0);
+    return t;
+  }
+  static __device__ __forceinline__ float value(float t, const Row& r, const Args& a) {
+    return exp2_unit(fmaf(t, a.scale2, r.c));
+  }
+};
+
+// One column on one point set: Y_i = sl_i 2^e (row partials + fixed-point column
+// sums), which are left cleared; where the column was not finite (bad != 0) from
+// the plain row sums' partials instead.
+__global__ __launch_bounds__(256) void column_finish_kernel(
+    const float* __restrict__ part, int nsplit_plain, int nsplit_sym, int64_t nrpad,
+    unsigned long long* __restrict__ colfix, double inv_fix, const float* __restrict__ colscale,
+    const float* __restrict__ sl, int64_t n, int64_t npad, float* __restrict__ Y, int64_t ldy,
+    PoisonGate poison) {
+  const int64_t i = int64_t(blockIdx.x) * 256 + threadIdx.x;
+  const bool sym = colfix != nullptr && colscale[1] == 0.f;
+  if (i < n) {
+    const int ns = sym ? nsplit_sym : nsplit_plain;
+    double s = 0.0;
+#pragma unroll 8
+    for (int k = 0; k < ns; ++k) s += double(part[k * nrpad + i]);
+    if (sym) s += double(static_cast<long long>(colfix[i])) * inv_fix;
+    float y = float(ldexp(s, int(colscale[0])));
+    if (sl != nullptr) y = sl[i] * y;
+    Y[i * ldy] = poisoned(poison) ? __builtin_nanf("") : y;
+  }
+  if (colfix != nullptr && i < npad) colfix[i] = 0ull;
 }
 
 // Y = diag(sl) (sum over splits of part) diag(colscale), NaN where the call is
@@ -1033,28 +1113,6 @@ __global__ __launch_bounds__(256) void degree_reduce_dsq_kernel(
 
 int64_t qsum_words(int64_t npad) { return ceil_div(npad, 256); }
 
-// sum(q) - n in double, one workgroup, fixed order (deterministic)
-__global__ __launch_bounds__(1024) void sum_minus_n_kernel(const float* __restrict__ q, int64_t n,
-                                                            double* __restrict__ out) {
-  __shared__ double red[1024];
-  // four independent partial sums per thread, each over a fixed index set
-  double s4[4] = {0.0, 0.0, 0.0, 0.0};
-  int64_t i = threadIdx.x;
-  for (; i + 3 * 1024 < n; i += 4 * 1024) {
-#pragma unroll
-    for (int u = 0; u < 4; ++u) s4[u] += double(q[i + u * 1024]);
-  }
-  for (; i < n; i += 1024) s4[0] += double(q[i]);
-  double s = (s4[0] + s4[1]) + (s4[2] + s4[3]);
-  red[threadIdx.x] = s;
-  __syncthreads();
-  for (int w = 512; w > 0; w >>= 1) {
-    if (int(threadIdx.x) < w) red[threadIdx.x] += red[threadIdx.x + w];
-    __syncthreads();
-  }
-  if (threadIdx.x == 0) *out = red[0] - double(n);
-}
-
 // ------------------------------------------------------------------ host side
 
 KVPlan plan_tiles(int64_t Nr, int64_t Nc, int dp, int b, int nib) {
@@ -1199,6 +1257,12 @@ static PackV pack_v_args(const float* V, int64_t n, int64_t b, int64_t ldv, cons
     v.ntiles = npad / TILE;
     check_span(vp, lane4_extent(v.ntiles, 1), "weight pack");
     v.wp = reinterpret_cast<floatx4*>(vp.p);
+    if (nvmax > 0) {
+      check_span(vscale, VSCALE_FLOATS, "column scales");
+      v.nvmax = int(nvmax);
+      v.colscale = vscale.p;
+      v.vpart = vscale.p + 64;
+    }
     return v;
   }
   FD_REQUIRE(npad % (2 * TILE) == 0 && npad >= n && b <= ncb * 16 && b <= 64 &&
@@ -1240,13 +1304,6 @@ void launch_pack_w(const float* w, int64_t n, int64_t npad, FSpan wp, hipStream_
   FD_LAUNCH_CHECK();
 }
 
-void launch_scale_rows(const float* t, const float* sl, int64_t n, float* Y, int64_t ldy,
-                       const PoisonGate& poison, hipStream_t stream) {
-  hipLaunchKernelGGL(scale_rows_kernel, dim3(blocks_for(n, 256)), dim3(256), 0, stream, t, sl, n,
-                     Y, ldy, poison);
-  FD_LAUNCH_CHECK();
-}
-
 // Geometry shared by the product and row-sum launches.
 static void check_tiles(const KVPlan& p, const PointPack& rows, const PointPack& cols) {
   const int64_t row_tiles = p.nrt * 4 * p.nib;  // 16-row tiles the grid reads
@@ -1268,7 +1325,7 @@ static void check_tiles(const KVPlan& p, const PointPack& rows, const PointPack&
 
 void launch_pack_v_split(const float* V, int64_t n, int64_t b, int64_t ldv, const float* sr,
                          int ncb, int64_t npad, FSpan vp, FSpan vscale, hipStream_t stream) {
-  if (ncb > 0) {
+  {
     PrologueIn in;
     in.V = V;
     in.nv = n;
@@ -1392,7 +1449,7 @@ static void rowsum_bf16_nib(const KVPlan& p, const PointPack& rows, const PointP
                      reinterpret_cast<const floatx4*>(cols.ap.p),
                      reinterpret_cast<const floatx4*>(wp),
                      reinterpret_cast<const uintx4*>(rows.xp.p), rows.ar.p, p.nrt, p.njb,
-                     p.jb_per_split, int(diag), scale2, out, rows.n, part, rows.npad);
+                     p.jb_per_split, int(diag), scale2, out, rows.n, part, rows.npad, gate_of(rows));
   FD_LAUNCH_CHECK();
 }
 
@@ -1409,7 +1466,24 @@ static void rowsum_bf16_launch(const KVPlan& p, const PointPack& rows, const Poi
 
 bool rowsum_sym_applies(const PointPack& rows, const PointPack& cols, bool diag,
                         const unsigned long long* colfix) {
-  return colfix != nullptr && diag && !rows.bf16 && !cols.bf16 && rows.n == cols.n;
+  return colfix != nullptr && diag && rows.bf16 == cols.bf16 && rows.n == cols.n;
+}
+
+template <int DC, bool UNIT>
+static void rowsum_sym_bf16(const KVPlan& p, const PointPack& rows, const PointPack& cols,
+                            const float* wp, float* part, unsigned long long* colfix, int frac,
+                            hipStream_t stream) {
+  using T = Bf16Tile<DC>;
+  const typename T::Args ta{reinterpret_cast<const uintx4*>(cols.xp.p),
+                            reinterpret_cast<const floatx4*>(cols.ap.p),
+                            reinterpret_cast<const uintx4*>(rows.xp.p), rows.ar.p,
+                            float(2.0 * rows.beta * LOG2E)};
+  ProfScope prof(FD_KERNEL_ROWSUM, stream);
+  hipLaunchKernelGGL((rowsum_sym_kernel<T, 8, UNIT>), dim3(unsigned(p.nrt * p.nsplit)),
+                     dim3(WG_THREADS), 0, stream, ta, reinterpret_cast<const floatx4*>(wp), p.nrt,
+                     p.njb, p.jb_per_split, int64_t(p.nsplit), part, rows.npad, colfix,
+                     std::ldexp(1.0, frac), nullptr, nullptr, 0.0, gate_of(rows));
+  FD_LAUNCH_CHECK();
 }
 
 SymPass launch_rowsum_sym_pass(const KVPlan& p, const PointPack& rows, const PointPack& cols,
@@ -1417,22 +1491,33 @@ SymPass launch_rowsum_sym_pass(const KVPlan& p, const PointPack& rows, const Poi
                                FSpan sq_part, unsigned long long* sq_colfix) {
   check_tiles(p, rows, cols);
   FD_REQUIRE(rowsum_sym_applies(rows, cols, true, colfix), FD_ERR_INVALID_ARG,
-             "internal: symmetric row sums need one float32 point set");
+             "internal: symmetric row sums need one point set");
   const KVPlan sp = plan_rowsum_sym(rows.n, rows.npad, p.dp, SYM_NIB);
   if (wp.p != nullptr) check_span(wp, lane4_extent(sp.njb, 1), "weight pack");
   check_span(part, size_t(sp.nsplit) * rows.npad, "partial row sums");
-  // fixed point with F fractional bits: the total of weights in [0, 1] over
-  // npad columns stays below 2^62 / 4
+  // fixed point with F fractional bits: the total of weights in [-1, 1] over
+  // npad columns stays below 2^62 / 4 (and so does that of K^2 <= 1)
   const int F = 62 - int(std::ceil(std::log2(double(rows.npad)))) - 2;
   SymSquares sq;
   if (sq_part.p != nullptr) {
     FD_REQUIRE(wp.p != nullptr && sq_colfix != nullptr, FD_ERR_INVALID_ARG,
                "internal: squared sums ride on a weighted pass");
     check_span(sq_part, size_t(sp.nsplit) * rows.npad, "partial squared row sums");
-    // (2^15 K)^2 per unit: K^2 <= 1 keeps the same headroom as the weights
-    sq = SymSquares{sq_part.p, sq_colfix, std::ldexp(1.0, F - 30)};
+    sq = SymSquares{sq_part.p, sq_colfix};
   }
-  launch_rowsum_sym_hx(sp, rows, cols, wp.p, part.p, colfix, std::ldexp(1.0, F - 15), sq, stream);
+  if (rows.bf16) {
+    FD_REQUIRE(rows.dc == cols.dc && sq.part == nullptr && sp.nrt * 4 * sp.nib * TILE == rows.npad, FD_ERR_INVALID_ARG,
+               "internal: symmetric row-sum plan");
+    const bool unit = wp.p == nullptr;
+    if (rows.dc == 1)
+      unit ? rowsum_sym_bf16<1, true>(sp, rows, cols, wp.p, part.p, colfix, F, stream)
+           : rowsum_sym_bf16<1, false>(sp, rows, cols, wp.p, part.p, colfix, F, stream);
+    else
+      unit ? rowsum_sym_bf16<2, true>(sp, rows, cols, wp.p, part.p, colfix, F, stream)
+           : rowsum_sym_bf16<2, false>(sp, rows, cols, wp.p, part.p, colfix, F, stream);
+  } else {
+    launch_rowsum_sym_hx(sp, rows, cols, wp.p, part.p, colfix, F, sq, stream);
+  }
   return SymPass{int(sp.nsplit), std::ldexp(1.0, -F)};
 }
 
@@ -1477,16 +1562,11 @@ void launch_degree_reduce_dsq(const SymPass& sp, const PointPack& rows, const Po
   FD_LAUNCH_CHECK();
 }
 
-void launch_rowsum(const KVPlan& p, const PointPack& rows, const PointPack& cols, FSpan wp,
-                   bool diag, float* out, FSpan part, hipStream_t stream) {
-  check_tiles(p, rows, cols);
+// The plain row-sum kernel: partials into pp, or (pp NULL, one split) out.
+static void launch_rowsum_pass(const KVPlan& p, const PointPack& rows, const PointPack& cols,
+                               FSpan wp, bool diag, float* out, float* pp, hipStream_t stream) {
   FD_REQUIRE(p.nib == 4 || p.nib == 8, FD_ERR_INVALID_ARG, "internal: row-sum plan");
   if (wp.p != nullptr) check_span(wp, lane4_extent(p.njb, 1), "weight pack");
-  float* pp = nullptr;
-  if (p.nsplit > 1) {
-    check_span(part, size_t(p.nsplit) * rows.npad, "partial row sums");
-    pp = part.p;
-  }
   if (rows.bf16 || cols.bf16) {
     FD_REQUIRE(rows.bf16 && cols.bf16 && rows.dc == cols.dc, FD_ERR_INVALID_ARG,
                "internal: mixed pack kinds");
@@ -1500,11 +1580,50 @@ void launch_rowsum(const KVPlan& p, const PointPack& rows, const PointPack& cols
   } else {
     launch_rowsum_hx(p, rows, cols, wp.p, diag, out, pp, stream);
   }
+}
+
+void launch_rowsum(const KVPlan& p, const PointPack& rows, const PointPack& cols, FSpan wp,
+                   bool diag, float* out, FSpan part, hipStream_t stream) {
+  check_tiles(p, rows, cols);
+  float* pp = nullptr;
+  if (p.nsplit > 1) {
+    check_span(part, size_t(p.nsplit) * rows.npad, "partial row sums");
+    pp = part.p;
+  }
+  launch_rowsum_pass(p, rows, cols, wp, diag, out, pp, stream);
   if (p.nsplit > 1) {
     hipLaunchKernelGGL(reduce_rowsum_kernel, dim3(blocks_for(rows.n, 256)), dim3(256), 0, stream,
                        pp, p.nsplit, rows.npad, out, rows.n);
     FD_LAUNCH_CHECK();
   }
+}
+
+void launch_product_column(const KVPlan& p, const PointPack& rows, const PointPack& cols, FSpan wp,
+                           FSpan vscale, bool diag, const float* sl, float* Y, int64_t ldy,
+                           FSpan part, unsigned long long* colfix, const PoisonGate& poison,
+                           hipStream_t stream) {
+  check_tiles(p, rows, cols);
+  check_span(part, size_t(p.nsplit) * rows.npad, "partial row sums");
+  check_span(vscale, VSCALE_FLOATS, "column scales");
+  SymPass sp;
+  if (rowsum_sym_applies(rows, cols, diag, colfix)) {
+    // K is symmetric: each tile off the diagonal blocks once (the whole call on
+    // the 6-torus set-up, N = 65,536, D = 32: 762 -> 596 us).  Column sums are
+    // fixed point, so a NaN or an infinity among the weights takes the plain
+    // sums: both are launched, and the column's flag closes one of them.
+    PointPack r = rows, c = cols;
+    r.vbad = c.vbad = vscale.p + 1;
+    sp = launch_rowsum_sym_pass(p, r, c, wp, part, colfix, stream);
+    r.serves_bad = c.serves_bad = 1;
+    launch_rowsum_pass(p, r, c, wp, diag, nullptr, part.p, stream);
+  } else {
+    colfix = nullptr;
+    launch_rowsum_pass(p, rows, cols, wp, diag, nullptr, part.p, stream);
+  }
+  hipLaunchKernelGGL(column_finish_kernel, dim3(blocks_for(rows.npad, 256)), dim3(256), 0, stream,
+                     part.p, p.nsplit, sp.nsplit, rows.npad, colfix, sp.inv_fix, vscale.p, sl,
+                     rows.n, rows.npad, Y, ldy, poison);
+  FD_LAUNCH_CHECK();
 }
 
 void launch_pow_neg(const float* q, int64_t n, double alpha, float* w, hipStream_t stream) {
@@ -1518,11 +1637,6 @@ void launch_degree_finish(const float* q, const float* t, int64_t n, double alph
                           const PoisonGate& poison, hipStream_t stream) {
   hipLaunchKernelGGL(degree_finish_kernel, dim3(blocks_for(n, 256)), dim3(256), 0, stream, q, t,
                      n, alpha, d, s, qsum, nqsum, s_off, poison);
-  FD_LAUNCH_CHECK();
-}
-
-void launch_sum_minus_n(const float* q, int64_t n, double* out, hipStream_t stream) {
-  hipLaunchKernelGGL(sum_minus_n_kernel, dim3(1), dim3(1024), 0, stream, q, n, out);
   FD_LAUNCH_CHECK();
 }
 

@@ -78,7 +78,7 @@ static SolverWs carve_solver_ws(Arena& a, int64_t N, int64_t D, int b, int mm_ca
   w.prod.vp = a.fspan(size_t(w.prod.cols.npad) * w.prod.plan.ncb * 16);
   w.prod.vscale = a.fspan(VSCALE_FLOATS);
   w.prod.part = a.fspan(part_rows_bound(w.prod.rows.npad, N) * w.prod.plan.ncb * 16);
-  w.prod.tmp = a.fspan(size_t(N));  // single-column products (block width 1)
+  w.prod.colfix = w.deg.colfix;  // single-column products: cleared by the degree passes
   w.d = a.take<float>(size_t(N));
   w.s = a.take<float>(size_t(N));
   w.s_off = a.take<double>(1);

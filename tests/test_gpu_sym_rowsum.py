@@ -1,0 +1,99 @@
+"""The symmetric row sums over their two other users: bfloat16 points and a
+single right-hand side.
+
+They pair blocks of 512 points, each unordered pair of blocks evaluated once, so
+the sizes here are one block and its edges, an even and an odd number of
+blocks, and 64 blocks and more, where column splits become whole blocks.
+Tolerances: the vectors of fd_degree and one float32 column to 1e-5 (the
+stated tolerance of float32 arithmetic); bfloat16 points enter exactly, so
+their sums keep that bar.  One column's sums along the columns are fixed point
+with at least 42 fractional bits against the largest weight: a column spread
+over 2^16 keeps 2^-26 of its smallest entries.
+"""
+import numpy as np
+import pytest
+import torch
+
+from gpu_util import TOL_F32, case, device, rel_fro, to_np
+from oracle import kernel as ok
+from oracle import normalise as on
+from paper_2609_38198_amd import _lib as fd
+
+pytestmark = pytest.mark.gpu
+
+SIZES = [(5, 3), (511, 12), (512, 40), (513, 64), (1024, 7), (1536, 33), (2049, 64), (5000, 30)]
+
+
+def _points(n, d, dtype):
+    x = torch.randn(n, d, generator=torch.Generator().manual_seed(n + d)) * 0.5
+    x = x.to(dtype).to(device())
+    return x, x.double().cpu().numpy()
+
+
+@pytest.mark.parametrize("n, d", SIZES)
+@pytest.mark.parametrize("alpha", [0.0, 0.5])
+def test_bfloat16_normalisation(n, d, alpha):
+    case(f"degree bf16 n={n} d={d} alpha={alpha}")
+    x, x64 = _points(n, d, torch.bfloat16)
+    deg = fd.fd_degree(x, 1.0 / d, alpha)
+    ref = on.normalise(x64, float(np.float32(1.0 / d)), alpha)
+    for name in ("q", "d", "s"):
+        assert rel_fro(to_np(getattr(deg, name)), getattr(ref, name)) <= TOL_F32
+    assert abs(float(to_np(deg.s_off)[0]) - ref.s_off) <= TOL_F32 * float(ref.q.sum())
+
+
+def test_bfloat16_normalisation_with_whole_block_splits_and_dyadic_levels():
+    n, d = 40000, 20
+    case(f"degree bf16 n={n} d={d}, dyadic")
+    x, x64 = _points(n, d, torch.bfloat16)
+    lev = fd.fd_degree_dyadic(x, 0.25 / d, 3, 0.5)
+    again = fd.fd_degree_dyadic(x, 0.25 / d, 3, 0.5)
+    assert torch.equal(lev.q, again.q) and torch.equal(lev.s, again.s)
+    rows = np.linspace(0, n - 1, 50).astype(int)
+    beta0 = float(np.float32(0.25 / d))
+    for l in range(3):
+        beta = beta0 * 2 ** l
+        q = ok.kernel_matmul(x64[rows], x64, beta, np.ones((n, 1)))[:, 0]
+        assert rel_fro(to_np(lev.q)[l][rows], q) <= TOL_F32
+        w = to_np(lev.q)[l] ** -0.5
+        dd = w[rows] * ok.kernel_matmul(x64[rows], x64, beta, w[:, None])[:, 0]
+        assert rel_fro(to_np(lev.d)[l][rows], dd) <= TOL_F32
+
+
+@pytest.mark.parametrize("n, d", SIZES + [(40001, 12)])
+@pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
+def test_one_column(n, d, dtype):
+    case(f"one column n={n} d={d} {dtype}")
+    x, x64 = _points(n, d, dtype)
+    g = torch.Generator().manual_seed(3)
+    v = torch.randn(n, 1, generator=g) * torch.exp2(16 * torch.rand(n, 1, generator=g) - 40)
+    sl, sr = torch.rand(n, generator=g) + 0.5, torch.rand(n, generator=g) + 0.5
+    V, SL, SR = v.to(device()), sl.to(device()), sr.to(device())
+    beta = float(np.float32(1.0 / d))
+    rows = np.unique(np.linspace(0, n - 1, 60).astype(int))
+    Y = fd.fd_kernel_matmul(x, None, beta, V, sl=SL, sr=SR)
+    ref = sl.double().numpy()[rows, None] * ok.kernel_matmul(
+        x64[rows], x64, beta, (sr.double()[:, None] * v.double()).numpy())
+    assert rel_fro(to_np(Y)[rows], ref) <= TOL_F32
+    assert torch.equal(Y, fd.fd_kernel_matmul(x, None, beta, V, sl=SL, sr=SR))
+    out = torch.empty_like(Y)
+    fd.fd_kernel_matmul_noalloc(x, None, beta, V, out, sl=SL, sr=SR)
+    assert torch.equal(Y, out)
+    # a NaN reaches every row, an infinity every row whose kernel value is not 0
+    for bad in (float("nan"), float("inf")):
+        W = V.clone()
+        W[n // 2, 0] = bad
+        got = to_np(fd.fd_kernel_matmul(x, None, beta, W, sl=SL, sr=SR))
+        assert not np.isfinite(got).any()
+        assert np.isnan(got).all() == np.isnan(bad)
+    assert torch.equal(Y, fd.fd_kernel_matmul(x, None, beta, V, sl=SL, sr=SR))
+
+
+def test_one_column_eigensolve_matches_a_wider_one():
+    """Block width 1 runs its products as single columns."""
+    n = 1500
+    case("eigensolve with one column per block")
+    x, _ = _points(n, 3, torch.float32)
+    a = fd.fd_block_lanczos(x, 0.5, 2, 1)
+    b = fd.fd_block_lanczos(x, 0.5, 2, 4)
+    assert np.allclose(a.evals[:2], b.evals[:2], rtol=0, atol=1e-6)
