@@ -9,9 +9,9 @@
 //     Rayleigh-Ritz step and the residuals ||M y - theta y|| are true values
 //     for any starting subspace (also a warm start that is not a Krylov block);
 //   * expansion: the images of the newest block are orthogonalised against the
-//     whole basis twice (classical Gram-Schmidt, twice) and orthonormalised by
-//     Cholesky QR with dependent columns replaced by random ones; one fused
-//     product gives their images;
+//     whole basis (classical Gram-Schmidt, twice), orthonormalised by Cholesky
+//     QR with dependent columns replaced by random ones, and taken through one
+//     more pass of both; one fused product gives their images;
 //   * restart (basis full): Rayleigh-Ritz on T (float64 Jacobi on the device),
 //     the leading kk Ritz vectors and their images are kept, and the next block
 //     is spanned by the residuals of the leading unconverged Ritz pairs (for a
@@ -144,18 +144,12 @@ struct Lanczos {
 
   // Z[:, 0:nb] (ld mm) <- orthonormal, orthogonal to Q[:, 0:m]
   void cgs2(float* Z, int nb, int m) {
-    if (m == 0) return;
-    for (int pass = 0; pass < 2; ++pass) {
-      gemm_tn(w.Q, mm, m, Z, mm, nb, N, w.part, nullptr, w.C32, st);
-      gemm_nn(w.Q, mm, m, w.C32, nb, Z, mm, N, -1.f, 1.f, st);
-    }
+    for (int pass = 0; pass < 2 && m > 0; ++pass) project_out(Z, mm, nb, m);
   }
-  void cgs2_t(float* Z, int64_t ldz, int nb, int m) {
-    if (m == 0) return;
-    for (int pass = 0; pass < 2; ++pass) {
-      gemm_tn(w.Q, mm, m, Z, ldz, nb, N, w.part, nullptr, w.C32, st);
-      gemm_nn(w.Q, mm, m, w.C32, nb, Z, ldz, N, -1.f, 1.f, st);
-    }
+  // Z -= Q Q^T Z against Q[:, 0:m]
+  void project_out(float* Z, int64_t ldz, int nb, int m) {
+    gemm_tn(w.Q, mm, m, Z, ldz, nb, N, w.part, nullptr, w.C32, st);
+    gemm_nn(w.Q, mm, m, w.C32, nb, Z, ldz, N, -1.f, 1.f, st);
   }
   void orth_block(float* Z, int nb, int m) {
     cgs2(Z, nb, m);
@@ -163,7 +157,10 @@ struct Lanczos {
     chol_rinv(w.G, nb, 1e-4, w.Rinv, w.flags, st);
     gemm_nn(Z, mm, nb, w.Rinv, nb, w.Zt, nb, N, 1.f, 0.f, st);
     fill_normal(w.Zt, nb, N, nb, w.flags, seed, rng_stream++, st);
-    cgs2_t(w.Zt, nb, nb, m);
+    // once more against the basis: the triangular factor has enlarged what the
+    // two passes left by at most the pivot bound (1e4), and replaced columns
+    // are random, so one pass takes both to rounding
+    if (m > 0) project_out(w.Zt, nb, nb, m);
     gemm_tn(w.Zt, nb, nb, w.Zt, nb, nb, N, w.part, w.G, nullptr, st);
     chol_rinv(w.G, nb, 1e-4, w.Rinv, w.flags, st);
     gemm_nn(w.Zt, nb, nb, w.Rinv, nb, Z, mm, N, 1.f, 0.f, st);

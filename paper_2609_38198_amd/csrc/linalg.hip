@@ -760,7 +760,11 @@ __global__ __launch_bounds__(256) void jacobi_permute_kernel(const double* __res
 // (rows are independent under column rotations), one workgroup per group of
 // rows held in LDS.
 
-constexpr int JL_MAX = 192;   // largest m on the one-workgroup path
+// Largest m on the one-workgroup path.  Whole eigensolves, this path against the
+// block path (ms): m = 33 0.31 / 0.46, 48 0.42 / 0.45, 64 0.62 / 0.52, 96 1.25 /
+// 0.69, 128 2.31 / 0.91, 192 5.57 / 1.40: one workgroup's rounds are serial,
+// and their number and their length both grow with m.
+constexpr int JL_MAX = 56;
 constexpr int JL_SWEEPS = 4;  // sweeps per launch (the log holds this many)
 constexpr int JL_BATCH = 32;  // rounds of the log staged in LDS at a time by the replay
 
@@ -1509,14 +1513,15 @@ int jacobi_eig(double* A, double* A2, int m, int lda, double* Vw, double* theta,
     }
   } else if (m > 1) {
     FD_REQUIRE(lda >= m && A2 != nullptr, FD_ERR_INVALID_ARG, "internal: block jacobi buffers");
-    // Stop at off(A) <= 1e-10 |A|_F.  A Ritz pair (theta_i, S e_i) of T then
+    // Above 192 columns: stop at off(A) <= 1e-10 |A|_F.  A Ritz pair (theta_i, S e_i) of T then
     // has residual |T s - theta s| <= off(A), about 3e-9 for the Markov
     // operators here (|T|_F <= sqrt(m)), and theta_i moves by no more; the
     // solver accepts pairs only on their explicitly computed residuals
     // |W s - theta Q s| (tolerance 1e-5), and the kept block of T is
     // re-projected at every restart, so the last sweeps of a 1e-13 stop
     // (one or two of about eight) bought nothing the caller sees.
-    constexpr double TOL_BLOCK = 1e-10;
+    // Up to 192 columns a sweep is cheap and the stop stays at 1e-13.
+    const double tol_block = m <= 192 ? TOL : 1e-10;
     check_span_d(log, bj_doubles(m), "block jacobi scratch");
     const int nbk = bj_blocks(m), P = nbk / 2;
     // a solve of round r + 1 sits in another pair than in round r only when a
@@ -1539,11 +1544,15 @@ int jacobi_eig(double* A, double* A2, int m, int lda, double* Vw, double* theta,
       double h[2] = {0.0, 0.0};
       FD_HIP_CHECK(hipMemcpyAsync(h, norms, sizeof(h), hipMemcpyDeviceToHost, stream));
       FD_HIP_CHECK(hipStreamSynchronize(stream));
-      return h[0] <= TOL_BLOCK * TOL_BLOCK * h[1];
+      return h[0] <= tol_block * tol_block * h[1];
     };
     hipLaunchKernelGGL(offnorm_partial_kernel, dim3(BJ_PART), dim3(256), 0, stream, cur, m, lda,
                        part);
     FD_LAUNCH_CHECK();
+    // a matrix that was not converged at the start is not after two sweeps (6 to
+    // 10 are usual): the host looks from the third on (a look is a launch, a
+    // copy and an idle GPU, about 25 us against 42 us for a sweep at m = 64)
+    constexpr int FIRST_LOOK = 3;
     if (!check(BJ_PART)) {
       // round 0 solved alone, then per launch: apply round r, solve round r + 1
       // (round 0 of the next sweep after the last round)
@@ -1557,13 +1566,13 @@ int jacobi_eig(double* A, double* A2, int m, int lda, double* Vw, double* theta,
           const int rn = last ? 0 : r + 1;
           hipLaunchKernelGGL(bj_round_kernel, dim3(P + ntile_a + ntile_v), dim3(256), 0, stream,
                              cur, nxt, Vw, lda, m, nbk, r, U[slot], F[slot], rn, U[slot ^ 1],
-                             F[slot ^ 1], P, ntile_a, last ? part : nullptr);
+                             F[slot ^ 1], P, ntile_a,
+                             last && sweeps + 1 >= FIRST_LOOK ? part : nullptr);
           FD_LAUNCH_CHECK();
           std::swap(cur, nxt);
           slot ^= 1;
         }
-        ++sweeps;
-        if (check(ntile_a)) break;
+        if (++sweeps >= FIRST_LOOK && check(ntile_a)) break;
       }
     }
   }
