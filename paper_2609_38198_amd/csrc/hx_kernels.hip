@@ -246,21 +246,19 @@ struct Hx {
   static constexpr int nm = HX_TABLE[RID].nm;
 };
 
-// Minimum waves per SIMD asked of the compiler.  At 2 a wave has at most 256
-// registers and the matrix instructions then accumulate in ordinary VGPRs, so
-// the vector ALUs read the exponent tiles without copies out of the
-// accumulation registers.  The variants listed take 1 (accumulation
-// registers, up to 512 per wave): their operands and accumulators do not fit
-// in 256 registers (they spill at 2, checked per instantiation).  Moving the
-// others to 2 left the results bitwise equal and took 7-23% off the products
-// at b = 48 (D <= 30), b = 64 (D <= 8) and D > 32 (b <= 32).
+// Every product asks for two waves per SIMD: at most 256 registers, and matrix
+// instructions that accumulate in ordinary VGPRs.  Where the operands,
+// accumulators and two column buffers do not fit (they spill, checked per
+// instantiation) the columns stream through one buffer each for the exponent
+// operands and for V.  N = 65,536, against one wave per SIMD with two buffers
+// (ms): D = 12, b = 64 2.25 -> 1.81; D = 30, b = 64 2.42 -> 1.95; D = 32, b = 48
+// 2.39 -> 1.81; D = 62, b = 64 3.09 -> 2.40; D = 64, b = 32 2.62 -> 1.98, b = 64
+// 3.23 -> 2.56 (four registers still spill there; one wave with one buffer takes
+// 3.12).  Where two buffers fit they stay: one buffer is 1-4% slower there
+// (D = 4, b = 64 1.57 against 1.61; D = 12, b = 48 1.46 against 1.50).
 template <int RID, int NCB, int NIB>
-constexpr int hx_waves() {
-  const bool big = (NIB == 2 && RID == 6 && NCB == 4) ||
-                   (NIB == 4 && ((NCB == 4 && RID >= 2) || (NCB == 3 && RID >= 4) ||
-                                 (NCB == 2 && RID >= 6))) ||
-                   (NIB == 8 && NCB >= 2 && RID >= 2);
-  return big ? 1 : 2;
+constexpr bool hx_single() {
+  return NIB == 4 && ((NCB == 4 && RID >= 2) || (NCB == 3 && RID >= 4) || (NCB == 2 && RID >= 6));
 }
 
 // Waves per SIMD for the symmetric row sums: two wherever the variant fits
@@ -469,9 +467,8 @@ struct HxPair {
 };
 
 template <int RID, int NCB>
-__device__ __forceinline__ void load_hx_pair(HxPair<RID, NCB>& c, const uintx4* __restrict__ xc,
-                                             const VSplit* __restrict__ vp, int64_t jp,
-                                             int lane) {
+__device__ __forceinline__ void load_hx_xa(HxPair<RID, NCB>& c, const uintx4* __restrict__ xc,
+                                           int64_t jp, int lane) {
   constexpr int NC = Hx<RID>::nc;
 #pragma unroll
   for (int t = 0; t < 2; ++t) {
@@ -479,8 +476,70 @@ __device__ __forceinline__ void load_hx_pair(HxPair<RID, NCB>& c, const uintx4* 
 #pragma unroll
     for (int ch = 0; ch < NC; ++ch) c.xa[t][ch] = xc[(jb * NC + ch) * 64 + lane];
   }
+}
+template <int RID, int NCB>
+__device__ __forceinline__ void load_hx_v(HxPair<RID, NCB>& c, const VSplit* __restrict__ vp,
+                                          int64_t jp, int lane) {
 #pragma unroll
   for (int cb = 0; cb < NCB; ++cb) c.v[cb] = vp[(jp * NCB + cb) * 64 + lane];
+}
+template <int RID, int NCB>
+__device__ __forceinline__ void load_hx_pair(HxPair<RID, NCB>& c, const uintx4* __restrict__ xc,
+                                             const VSplit* __restrict__ vp, int64_t jp,
+                                             int lane) {
+  load_hx_xa(c, xc, jp, lane);
+  load_hx_v(c, vp, jp, lane);
+}
+
+// K' = 2^t (the shift in t: K' <= 2^15 up to rounding) of a pair of exponent
+// tiles, split into float16 halves: components 2 u, 2 u + 1 hold tile u.
+__device__ __forceinline__ void hx_split(const floatx4 (&t)[2], float m1, uintx4& hw, uintx4& lw) {
+#pragma unroll
+  for (int u = 0; u < 2; ++u)
+#pragma unroll
+    for (int r = 0; r < 4; r += 2) {
+      const float k0 = __builtin_amdgcn_exp2f(t[u][r]);
+      const float k1 = __builtin_amdgcn_exp2f(t[u][r + 1]);
+      unsigned hh, ll;
+      split2m(k0, k1, m1, hh, ll);
+      hw[2 * u + r / 2] = hh;
+      lw[2 * u + r / 2] = ll;
+    }
+}
+
+// acc += K' V' from the split operands (Kh Vh + Kh Vl + Kl Vh per 16 columns).
+template <int NCB>
+__device__ __forceinline__ void hx_kv(const uintx4& hw, const uintx4& lw, const VSplit (&v)[NCB],
+                                      floatx4 (&acc)[NCB]) {
+  const halfx8 khi = __builtin_bit_cast(halfx8, hw);
+  const halfx8 klo = __builtin_bit_cast(halfx8, lw);
+#pragma unroll
+  for (int cb = 0; cb < NCB; ++cb) {
+    acc[cb] = __builtin_amdgcn_mfma_f32_16x16x32_f16(khi, v[cb].hi, acc[cb], 0, 0, 0);
+    acc[cb] = __builtin_amdgcn_mfma_f32_16x16x32_f16(khi, v[cb].lo, acc[cb], 0, 0, 0);
+    acc[cb] = __builtin_amdgcn_mfma_f32_16x16x32_f16(klo, v[cb].hi, acc[cb], 0, 0, 0);
+  }
+}
+
+// Split kernel values of a pair of column tiles against the wave's row tiles.
+template <int RID, int NCB, int NIB, bool DIAG>
+__device__ __forceinline__ void hx_kernel_values(const HxPair<RID, NCB>& c,
+                                                 const uintx4 (&br)[NIB][Hx<RID>::nb],
+                                                 uintx4 (&hw)[NIB], uintx4 (&lw)[NIB], int64_t jp,
+                                                 int64_t ib0, float m1, int g, int p) {
+#pragma unroll
+  for (int ib = 0; ib < NIB; ++ib) {
+    floatx4 t[2];
+#pragma unroll
+    for (int u = 0; u < 2; ++u) {
+      if (DIAG && 2 * jp + u == ib0 + ib)
+        t[u] = hx_exponent<RID, true>(c.xa[u], br[ib], g, p);
+      else
+        t[u] = hx_exponent<RID, false>(c.xa[u], br[ib], g, p);
+    }
+    hx_split(t, m1, hw[ib], lw[ib]);
+  }
+  sched_interleave<NIB * 2 * Hx<RID>::nm, 8 * NIB, 4>();
 }
 
 // One pair of column tiles against the wave's NIB row tiles.  From the two
@@ -503,26 +562,8 @@ __device__ __forceinline__ void hx_pair(const HxPair<RID, NCB>& c,
         t[u] = hx_exponent<RID, false>(c.xa[u], br[ib], g, p);
     }
     uintx4 hw, lw;
-#pragma unroll
-    for (int u = 0; u < 2; ++u)
-#pragma unroll
-      for (int r = 0; r < 4; r += 2) {
-        // K' = 2^t with the shift in t: K' <= 2^15 (up to rounding)
-        const float k0 = __builtin_amdgcn_exp2f(t[u][r]);
-        const float k1 = __builtin_amdgcn_exp2f(t[u][r + 1]);
-        unsigned hh, ll;
-        split2m(k0, k1, m1, hh, ll);
-        hw[2 * u + r / 2] = hh;
-        lw[2 * u + r / 2] = ll;
-      }
-    const halfx8 khi = __builtin_bit_cast(halfx8, hw);
-    const halfx8 klo = __builtin_bit_cast(halfx8, lw);
-#pragma unroll
-    for (int cb = 0; cb < NCB; ++cb) {
-      acc[ib][cb] = __builtin_amdgcn_mfma_f32_16x16x32_f16(khi, c.v[cb].hi, acc[ib][cb], 0, 0, 0);
-      acc[ib][cb] = __builtin_amdgcn_mfma_f32_16x16x32_f16(khi, c.v[cb].lo, acc[ib][cb], 0, 0, 0);
-      acc[ib][cb] = __builtin_amdgcn_mfma_f32_16x16x32_f16(klo, c.v[cb].hi, acc[ib][cb], 0, 0, 0);
-    }
+    hx_split(t, m1, hw, lw);
+    hx_kv<NCB>(hw, lw, c.v, acc[ib]);
   }
   // one matrix instruction, then its share of the exponentials and three
   // other vector instructions (3.5% faster at D = 30, b = 32; unchanged at
@@ -538,7 +579,7 @@ __device__ __forceinline__ void hx_pair(const HxPair<RID, NCB>& c,
 // m1 = -1 (see split2m).
 template <int RID, int NCB, int NIB>
 __global__ __launch_bounds__(WG_THREADS)
-__attribute__((amdgpu_waves_per_eu(hx_waves<RID, NCB, NIB>()))) void product_hx_kernel(
+__attribute__((amdgpu_waves_per_eu(2))) void product_hx_kernel(
     const uintx4* __restrict__ xc, const VSplit* __restrict__ vp, const uintx4* __restrict__ xr,
     int64_t nrt, int64_t njp, int64_t jp_per_split, int diag, float m1,
     const float* __restrict__ colscale, const float* __restrict__ sl, float* __restrict__ Y,
@@ -573,6 +614,44 @@ __attribute__((amdgpu_waves_per_eu(hx_waves<RID, NCB, NIB>()))) void product_hx_
       tot[wave][ib][cb][lane] = floatx4{0.f, 0.f, 0.f, 0.f};
     }
 
+  int chunk = 0;
+  auto fold = [&](int pairs) {
+    chunk += pairs;
+    if (chunk < CHUNK_TILES / 2) return;
+    chunk = 0;
+#pragma unroll
+    for (int ib = 0; ib < NIB; ++ib)
+#pragma unroll
+      for (int cb = 0; cb < NCB; ++cb) {
+        tot[wave][ib][cb][lane] += acc[ib][cb];
+        acc[ib][cb] = floatx4{0.f, 0.f, 0.f, 0.f};
+      }
+  };
+  if constexpr (hx_single<RID, NCB, NIB>()) {
+    // a step first forms K' of all the wave's row tiles, refills the exponent
+    // operands, multiplies K' into V and refills V: each load has the other
+    // phase's work to land
+    HxPair<RID, NCB> c;
+    load_hx_xa(c, xc, jp_begin, lane);
+    load_hx_v(c, vp, jp_begin, lane);
+#pragma unroll
+    for (int ib = 0; ib < NIB; ++ib)
+#pragma unroll
+      for (int ch = 0; ch < NB; ++ch) asm volatile("" ::"v"(br[ib][ch]));
+    for (int64_t jp = jp_begin; jp < jp_end; ++jp) {
+      const int64_t jn = min(jp + 1, jp_end - 1);
+      uintx4 hw[NIB], lw[NIB];
+      if (diag && 2 * jp + 1 >= ib0 && 2 * jp < ib0 + NIB)
+        hx_kernel_values<RID, NCB, NIB, true>(c, br, hw, lw, jp, ib0, m1, g, p);
+      else
+        hx_kernel_values<RID, NCB, NIB, false>(c, br, hw, lw, jp, ib0, m1, g, p);
+      load_hx_xa(c, xc, jn, lane);
+#pragma unroll
+      for (int ib = 0; ib < NIB; ++ib) hx_kv<NCB>(hw[ib], lw[ib], c.v, acc[ib]);
+      load_hx_v(c, vp, jn, lane);
+      fold(1);
+    }
+  } else {
   auto step = [&](const HxPair<RID, NCB>& c, int64_t jp) {
     if (diag && 2 * jp + 1 >= ib0 && 2 * jp < ib0 + NIB)
       hx_pair<RID, NCB, NIB, true>(c, br, acc, jp, ib0, m1, g, p);
@@ -585,7 +664,6 @@ __attribute__((amdgpu_waves_per_eu(hx_waves<RID, NCB, NIB>()))) void product_hx_
   // before each step then only covers the buffer it consumes
   __builtin_amdgcn_sched_barrier(0);
   load_hx_pair(b1, xc, vp, min(jp_begin + 1, jp_end - 1), lane);
-  int chunk = 0;
   for (int64_t jp = jp_begin; jp < jp_end; jp += 2) {
     step(b0, jp);
     load_hx_pair(b0, xc, vp, min(jp + 2, jp_end - 1), lane);
@@ -593,17 +671,8 @@ __attribute__((amdgpu_waves_per_eu(hx_waves<RID, NCB, NIB>()))) void product_hx_
     // in flight at the top of the loop is the same on every path
     if (jp + 1 < jp_end) step(b1, jp + 1);
     load_hx_pair(b1, xc, vp, min(jp + 3, jp_end - 1), lane);
-    chunk += 2;
-    if (chunk >= CHUNK_TILES / 2) {
-      chunk = 0;
-#pragma unroll
-      for (int ib = 0; ib < NIB; ++ib)
-#pragma unroll
-        for (int cb = 0; cb < NCB; ++cb) {
-          tot[wave][ib][cb][lane] += acc[ib][cb];
-          acc[ib][cb] = floatx4{0.f, 0.f, 0.f, 0.f};
-        }
-    }
+    fold(2);
+  }
   }
 
 #pragma unroll
@@ -811,13 +880,12 @@ void product_hx_nib(const KVPlan& p, const PointPack& rows, const PointPack& col
                     const float* vp, const float* cs, bool diag, const float* sl, float* Y,
                     int64_t ldy, int b, float* part, const PoisonGate& poison,
                     hipStream_t stream) {
-  switch (p.nib) {
-    case 2: return product_hx_launch<RID, NCB, 2>(p, rows, cols, vp, cs, diag, sl, Y, ldy, b, part, poison, stream);
-    case 4: return product_hx_launch<RID, NCB, 4>(p, rows, cols, vp, cs, diag, sl, Y, ldy, b, part, poison, stream);
-    case 8:
-      if constexpr (RID <= 3 && NCB <= 2)
-        return product_hx_launch<RID, NCB, 8>(p, rows, cols, vp, cs, diag, sl, Y, ldy, b, part, poison, stream);
-      break;
+  if (p.nib == 4)
+    return product_hx_launch<RID, NCB, 4>(p, rows, cols, vp, cs, diag, sl, Y, ldy, b, part, poison, stream);
+  // eight row tiles per wave only for the shapes product_nib gives them to
+  if constexpr (RID <= 2 && NCB == 1) {
+    if (p.nib == 8)
+      return product_hx_launch<RID, NCB, 8>(p, rows, cols, vp, cs, diag, sl, Y, ldy, b, part, poison, stream);
   }
   throw Error{FD_ERR_INVALID_ARG, "internal: unsupported rows per wave"};
 }

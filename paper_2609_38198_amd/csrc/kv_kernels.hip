@@ -1370,11 +1370,8 @@ static void product_bf16_launch(const KVPlan& p, const PointPack& rows, const Po
       return product_bf16_nib<DC, NCB, 8>(p, rows, cols, vp, cs, diag, sl, Y, ldy, b, part,
                                           poison, stream);
   }
-  FD_REQUIRE(p.nib == 2 || p.nib == 4, FD_ERR_INVALID_ARG, "internal: bf16 rows per wave");
-  if (p.nib == 2)
-    product_bf16_nib<DC, NCB, 2>(p, rows, cols, vp, cs, diag, sl, Y, ldy, b, part, poison, stream);
-  else
-    product_bf16_nib<DC, NCB, 4>(p, rows, cols, vp, cs, diag, sl, Y, ldy, b, part, poison, stream);
+  FD_REQUIRE(p.nib == 4, FD_ERR_INVALID_ARG, "internal: bf16 rows per wave");
+  product_bf16_nib<DC, NCB, 4>(p, rows, cols, vp, cs, diag, sl, Y, ldy, b, part, poison, stream);
 }
 
 template <int DC>
@@ -1395,7 +1392,7 @@ void launch_product(const KVPlan& p, const PointPack& rows, const PointPack& col
                     FSpan vscale, bool diag, const float* sl, float* Y, int64_t ldy, int b,
                     FSpan part, const PoisonGate& poison, hipStream_t stream) {
   check_tiles(p, rows, cols);
-  FD_REQUIRE(b >= 1 && b <= p.ncb * 16 && (p.nib == 2 || p.nib == 4 || p.nib == 8),
+  FD_REQUIRE(b >= 1 && b <= p.ncb * 16 && (p.nib == 4 || p.nib == 8),
              FD_ERR_INVALID_ARG, "internal: block width does not match the plan");
   FD_REQUIRE(p.jb_per_split % 2 == 0 && round_up(p.njb, 2) * TILE <= cols.npad,
              FD_ERR_INVALID_ARG, "internal: column pairs do not fit the pack");
