@@ -207,8 +207,6 @@ struct KVPlan {
 };
 
 // Tiling of a fused product (rows per wave tuned by shape) and of a row sum.
-KVPlan plan_tiles(int64_t Nr, int64_t Nc, int dp, int b, int nib);
-int product_nib(int dp, int ncb);
 KVPlan plan_product(int64_t Nr, int64_t Nc, int dp, int b);
 KVPlan plan_rowsum(int64_t Nr, int64_t Nc, int dp);
 

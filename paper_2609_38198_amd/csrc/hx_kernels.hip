@@ -882,7 +882,7 @@ void product_hx_nib(const KVPlan& p, const PointPack& rows, const PointPack& col
                     hipStream_t stream) {
   if (p.nib == 4)
     return product_hx_launch<RID, NCB, 4>(p, rows, cols, vp, cs, diag, sl, Y, ldy, b, part, poison, stream);
-  // eight row tiles per wave only for the shapes product_nib gives them to
+  // eight row tiles per wave only for the shapes plan_product gives them to
   if constexpr (RID <= 2 && NCB == 1) {
     if (p.nib == 8)
       return product_hx_launch<RID, NCB, 8>(p, rows, cols, vp, cs, diag, sl, Y, ldy, b, part, poison, stream);
