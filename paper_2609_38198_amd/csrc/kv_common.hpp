@@ -103,11 +103,18 @@ __device__ __forceinline__ bool poisoned(const PoisonGate& g) {
 
 constexpr int PACK_THREADS = 128;  // workgroup of the pack kernels
 
+// Widest column (largest over smallest |sr v|) that a single-column product takes
+// through the fixed-point column sums.  They resolve 2^-44 of the largest
+// weight at N = 65,536; a sum holds its own point's weight (K_ii = 1), so within
+// this range it keeps about 2^-20 of itself.  Sparse or decaying columns go to
+// the float32 sums, which keep far smaller results too.
+constexpr float COLUMN_RANGE = 16777216.f;  // 2^24
+
 // The V part of a pack launch: V (n x b, ldv) times sr, as the split pack of
 // ncb 16-column blocks over npairs pairs of 16-point tiles, or (ncb = 0) as the
 // weight pack of its one column over ntiles tiles; with nvmax that column is
 // scaled by 2^-e to below 1 (colscale[0] = e, colscale[1] = 1 where it holds a
-// NaN or an infinity, else 0).
+// NaN or an infinity or spans more than COLUMN_RANGE, else 0).
 struct PackV {
   const float* V = nullptr;
   const float* sr = nullptr;
@@ -137,15 +144,18 @@ __device__ __forceinline__ void pack_v_block(const PackV& a, int64_t blk, int* e
   if (a.ncb == 0) {
     int ex1 = 0;
     if (a.nvmax > 0) {
-      float m = 0.f, bad = 0.f;
+      float m = 0.f, bad = 0.f, mn = __builtin_inff();
       for (int k = lane; k < a.nvmax; k += 64) {
         m = fmaxf(m, a.vpart[k * 64]);
         bad = fmaxf(bad, a.vpart[k * 64 + 1]);
+        mn = fminf(mn, a.vpart[k * 64 + 2]);
       }
       for (int o = 32; o > 0; o >>= 1) {
         m = fmaxf(m, __shfl_xor(m, o));
         bad = fmaxf(bad, __shfl_xor(bad, o));
+        mn = fminf(mn, __shfl_xor(mn, o));
       }
+      if (mn * COLUMN_RANGE < m) bad = 1.f;
       ex1 = bad != 0.f ? 0 : 14 - vscale_exponent(m);
       if (idx == 0) {
         a.colscale[0] = float(ex1);

@@ -145,7 +145,7 @@ __device__ __forceinline__ void prologue_vmax(const PrologueArgs& a, int blk, fl
   const int c = int(threadIdx.x) % a.tcv, rl = int(threadIdx.x) / a.tcv, nrl = 256 / a.tcv;
   const int64_t rpb = (a.nv + a.nblkv - 1) / a.nblkv;
   const int64_t r0 = int64_t(blk) * rpb, r1 = min(a.nv, r0 + rpb);
-  float m = 0.f;
+  float m = 0.f, mn = __builtin_inff();
   bool ok = true;
   if (c < a.b) {
     for (int64_t i = r0 + rl; i < r1; i += 4 * nrl) {
@@ -159,14 +159,25 @@ __device__ __forceinline__ void prologue_vmax(const PrologueArgs& a, int blk, fl
 #pragma unroll
       for (int u = 0; u < 4; ++u) {
         m = fmaxf(m, fabsf(v[u]));
+        mn = fminf(mn, fabsf(v[u]));
         ok = ok && isfinite(v[u]);
       }
     }
   }
   if (a.b == 1) {
-    // one column: also whether it is finite (pack_v_block)
+    // one column: also whether it is finite and its smallest value (pack_v_block)
     const int bad = __syncthreads_or(ok ? 0 : 1);
-    if (threadIdx.x == 0) a.vpart[blk * 64 + 1] = bad ? 1.f : 0.f;
+    red[threadIdx.x] = mn;
+    __syncthreads();
+    for (int w = 128; w >= 1; w >>= 1) {
+      if (int(threadIdx.x) < w) red[threadIdx.x] = fminf(red[threadIdx.x], red[threadIdx.x + w]);
+      __syncthreads();
+    }
+    if (threadIdx.x == 0) {
+      a.vpart[blk * 64 + 1] = bad ? 1.f : 0.f;
+      a.vpart[blk * 64 + 2] = red[0];
+    }
+    __syncthreads();
   }
   red[threadIdx.x] = m;
   __syncthreads();
@@ -1635,8 +1646,9 @@ void launch_product_column(const KVPlan& p, const PointPack& rows, const PointPa
   if (rowsum_sym_applies(rows, cols, diag, colfix)) {
     // K is symmetric: each tile off the diagonal blocks once (the whole call on
     // the 6-torus set-up, N = 65,536, D = 32: 762 -> 596 us).  Column sums are
-    // fixed point, so a NaN or an infinity among the weights takes the plain
-    // sums: both are launched, and the column's flag closes one of them.
+    // fixed point against the column's largest weight, so a NaN, an infinity or
+    // a wide range (zeros among others, COLUMN_RANGE) takes the plain sums: both
+    // are launched, and the column's flag closes one of them.
     PointPack r = rows, c = cols;
     r.vbad = c.vbad = vscale.p + 1;
     sp = launch_rowsum_sym_pass(p, r, c, wp, part, colfix, stream);

@@ -89,6 +89,34 @@ def test_one_column(n, d, dtype):
     assert torch.equal(Y, fd.fd_kernel_matmul(x, None, beta, V, sl=SL, sr=SR))
 
 
+@pytest.mark.parametrize("n", [513, 5000])
+@pytest.mark.parametrize("kind", ["one point", "decaying", "normal"])
+def test_one_column_keeps_small_results(n, kind):
+    """Each result by itself: sums far below the column's largest value too.
+
+    The exponent carries a few units of 2^-22 of B = beta log2(e) max|x|^2 < 100
+    here (1e-4 of a kernel value); a normal column has results near zero by
+    cancellation, so it is compared against its sums without signs.
+    """
+    case(f"one column n={n} {kind}")
+    x, x64 = _points(n, 12, torch.float32)
+    g = torch.Generator().manual_seed(5)
+    v = torch.randn(n, 1, generator=g)
+    if kind == "one point":
+        v = torch.zeros(n, 1)
+        v[n // 3] = 3.0
+    elif kind == "decaying":
+        v = torch.exp2(-60 * torch.rand(n, 1, generator=g))
+    beta = 4.0
+    assert beta * 1.4427 * float(np.square(x64 - x64.mean(0)).sum(1).max()) < 100
+    Y = to_np(fd.fd_kernel_matmul(x, None, beta, v.to(device())))
+    ref = ok.kernel_matmul(x64, x64, beta, v.double().numpy())
+    size = ok.kernel_matmul(x64, x64, beta, v.double().abs().numpy())
+    seen = size > 1e-30
+    assert seen.sum() > n // 2
+    assert (np.abs(Y - ref) <= 1e-4 * size)[seen].all()
+
+
 def test_one_column_eigensolve_matches_a_wider_one():
     """Block width 1 runs its products as single columns."""
     n = 1500
