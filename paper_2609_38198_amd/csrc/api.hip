@@ -57,50 +57,6 @@ void check_workspace(const void* ws, size_t ws_bytes, size_t need) {
              "workspace must be 256-byte aligned");
 }
 
-// ---------------------------------------------------------------- non-finite inputs
-
-__global__ void clear_flag_kernel(int* flag) { *flag = 0; }
-
-__global__ void scan_nonfinite_kernel(const void* __restrict__ X, int bf16, int64_t n, int D,
-                                      int64_t ldx, int* __restrict__ flag) {
-  const int64_t total = n * D;
-  bool bad = false;
-  for (int64_t e = int64_t(blockIdx.x) * blockDim.x + threadIdx.x; e < total;
-       e += int64_t(gridDim.x) * blockDim.x) {
-    const int64_t i = e / D, f = e % D;
-    if (bf16) {
-      const uint16_t v = static_cast<const uint16_t*>(X)[i * ldx + f];
-      bad = bad || (v & 0x7F80u) == 0x7F80u;
-    } else {
-      bad = bad || !isfinite(static_cast<const float*>(X)[i * ldx + f]);
-    }
-  }
-  if (bad) atomicOr(flag, 1);
-}
-
-static unsigned stride_grid(int64_t n) {
-  return unsigned(std::min<int64_t>(1024, std::max<int64_t>(1, (n + 255) / 256)));
-}
-
-void launch_scan_nonfinite(const void* X, fd_dtype xt, int64_t N, int64_t D, int64_t ldx,
-                           int* flag, hipStream_t stream) {
-  FD_REQUIRE(flag != nullptr, FD_ERR_INVALID_ARG, "internal: no flag word");
-  hipLaunchKernelGGL(clear_flag_kernel, dim3(1), dim3(1), 0, stream, flag);
-  FD_LAUNCH_CHECK();
-  hipLaunchKernelGGL(scan_nonfinite_kernel, dim3(stride_grid(N * D)), dim3(256), 0, stream, X,
-                     xt == FD_BF16 ? 1 : 0, N, int(D), ldx, flag);
-  FD_LAUNCH_CHECK();
-}
-
-void require_finite(const void* X, fd_dtype xt, int64_t N, int64_t D, int64_t ldx, int* flag,
-                    hipStream_t stream) {
-  launch_scan_nonfinite(X, xt, N, D, ldx, flag, stream);
-  int h = 0;
-  FD_HIP_CHECK(hipMemcpyAsync(&h, flag, sizeof(int), hipMemcpyDeviceToHost, stream));
-  FD_HIP_CHECK(hipStreamSynchronize(stream));
-  FD_REQUIRE(h == 0, FD_ERR_INVALID_ARG, "X holds a NaN or infinite value");
-}
-
 // ---------------------------------------------------------------- products
 
 ProductWs carve_product(Arena& a, int64_t Nr, int64_t Nc, int64_t D, int b) {

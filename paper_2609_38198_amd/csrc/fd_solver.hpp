@@ -53,15 +53,6 @@ void degree_run_dyadic(DegreeWs& w, const void* X, fd_dtype xt, int64_t N, int64
                        int64_t ldx, double beta0, int nb, double alpha, float* q, float* d,
                        float* s, double* s_off, hipStream_t stream);
 
-// Clears *flag, then sets it if any of the N x D values of X is NaN or infinite
-// (asynchronous).
-void launch_scan_nonfinite(const void* X, fd_dtype xt, int64_t N, int64_t D, int64_t ldx,
-                           int* flag, hipStream_t stream);
-// Synchronous check for the eigensolver entry points: FD_ERR_INVALID_ARG when
-// X holds a non-finite value.
-void require_finite(const void* X, fd_dtype xt, int64_t N, int64_t D, int64_t ldx, int* flag,
-                    hipStream_t stream);
-
 // Row slots of a partial-sum buffer large enough for every plan with at most
 // npad rows and nc columns (see plan_product).
 size_t part_rows_bound(int64_t npad, int64_t nc);
