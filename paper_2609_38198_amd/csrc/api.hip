@@ -123,13 +123,6 @@ static char* scratch_on_current_device() {
   return ptrs[size_t(dev)];
 }
 
-// Every plan has nsplit <= max(ceil(2048 / row blocks), ceil(column tiles /
-// SPLIT_SPAN_TILES)), so the partial buffers of any problem with at most npad
-// rows and nc columns fit in this many row slots.
-size_t part_rows_bound(int64_t npad, int64_t nc) {
-  return size_t(2048) * ROW_PAD + size_t(npad) * size_t(1 + ceil_div(ceil_div(nc, TILE), SPLIT_SPAN_TILES));
-}
-
 PointPack pack_view(const PointPack& big, int64_t n, int64_t pad) {
   PointPack p = big;
   p.n = n;
@@ -223,7 +216,7 @@ static void matmul_run(ProductWs& w, const void* Xr, const void* Xc, int64_t D, 
 
 // ---------------------------------------------------------------- degree
 
-DegreeWs carve_degree(Arena& a, int64_t N, int64_t D) {
+DegreeWs carve_degree(Arena& a, int64_t N, int64_t D, bool prefixes) {
   DegreeWs w;
   const int dp = padded_dim(D);
   w.plan = plan_rowsum(N, N, dp);
@@ -232,7 +225,9 @@ DegreeWs carve_degree(Arena& a, int64_t N, int64_t D) {
   w.wp = a.fspan(size_t(w.cols.npad) * 16);  // one float4 per lane per 16-point tile
   w.q = a.take<float>(size_t(N));
   w.w = a.take<float>(size_t(N));
-  w.part = a.fspan(std::max(part_rows_bound(w.rows.npad, N), sym_part_rows(w.rows.npad, SYM_NIB)));
+  w.part = a.fspan(std::max(part_rows_bound(w.rows.npad, N),
+                            prefixes ? sym_part_rows_within(w.rows.npad, SYM_NIB)
+                                     : sym_part_rows(w.rows.npad, SYM_NIB)));
   w.colfix = a.take<unsigned long long>(size_t(w.rows.npad));
   w.qsum = a.take<double>(2 * size_t(qsum_words(w.rows.npad)));
   w.flag = a.take<int>(1);

@@ -7,6 +7,7 @@
 
 #include <string>
 
+#include "fd_plans.hpp"
 #include "flashdiff.h"
 
 namespace fd {
@@ -66,21 +67,6 @@ struct Arena {
 };
 
 // ---------------------------------------------------------------- geometry
-constexpr int TILE = 16;          // points per MFMA tile
-constexpr int WG_THREADS = 256;   // four wave64 per workgroup
-constexpr int ROW_PAD = 512;      // row packs: whole workgroups of 4 waves x 8 row tiles
-constexpr int COL_PAD = 32;       // column packs: whole pairs of 16-point tiles
-// Longest column range one workgroup of a product or row-sum plan streams
-// (tiles of 16 points); longer ranges are split.  The workgroups that run
-// together on an XCD start a split together and drift apart; over 4,096
-// tiles (a few tens of MB of column operands) their working set stays
-// cache-resident, over 32,768 it did not always (the bfloat16 product at
-// N = 2^21, b = 64 then ran 1.5 to 2.2 s against 1.43 s).
-constexpr int64_t SPLIT_SPAN_TILES = 4096;
-
-inline int64_t round_up(int64_t x, int64_t m) { return (x + m - 1) / m * m; }
-inline int64_t ceil_div(int64_t x, int64_t m) { return (x + m - 1) / m; }
-
 // Padded contraction width used for a feature dimension D (multiple of 4).
 int padded_dim(int64_t D);
 // Supported feature dimensions and block widths.
@@ -197,19 +183,6 @@ PoisonGate poison_gate(fd_dtype xt, const CentreWs& c, double beta, const int* f
 // Floats per point of a pack region (large enough for either pack kind).
 int pack_floats_per_point(int64_t D);
 
-// Plan of one fused product / degree launch.
-struct KVPlan {
-  int dp = 0, ncb = 0, nib = 0;
-  int64_t njb = 0;        // column tiles of 16
-  int64_t nrt = 0;        // row tiles of 64*nib
-  int nsplit = 1;         // column splits
-  int64_t jb_per_split = 0;
-};
-
-// Tiling of a fused product (rows per wave tuned by shape) and of a row sum.
-KVPlan plan_product(int64_t Nr, int64_t Nc, int dp, int b);
-KVPlan plan_rowsum(int64_t Nr, int64_t Nc, int dp);
-
 // Workspace carving helpers (size when arena.measuring).
 PointPack carve_pack(Arena& a, int64_t n, int dp, int64_t pad);
 
@@ -260,7 +233,6 @@ void launch_product_column(const KVPlan& p, const PointPack& rows, const PointPa
 // out = K w (wp.p == NULL: w = 1).
 void launch_rowsum(const KVPlan& p, const PointPack& rows, const PointPack& cols, FSpan wp,
                    bool diag, float* out, FSpan part, hipStream_t stream);
-KVPlan plan_rowsum_sym(int64_t N, int64_t npad, int dp, int nib);
 // The symmetric path piece by piece (the two normalisation passes fuse their
 // epilogues into its reduction): whether it applies, one pass of the kernel
 // (row partials in part, fixed-point column sums added into colfix, which the
@@ -306,12 +278,6 @@ void launch_degree_reduce_dsq(const SymPass& sp, const PointPack& rows, const Po
                               const PoisonGate& poison, hipStream_t stream);
 // Words of a partial-sum buffer of q (one per reduction workgroup).
 int64_t qsum_words(int64_t npad);
-// Row tiles per wave of the symmetric row sums, and the fewest column splits
-// of their large-problem plans.
-constexpr int SYM_NIB = 8;
-constexpr int64_t SYM_MIN_SPLITS = 16;
-// Row slots of the partial sums of a symmetric row-sum plan with npad rows.
-size_t sym_part_rows(int64_t npad, int nib);
 // d, s from q and t; with qsum (nqsum words) also s_off.
 void launch_degree_finish(const float* q, const float* t, int64_t n, double alpha, float* d,
                           float* s, const double* qsum, int64_t nqsum, double* s_off,

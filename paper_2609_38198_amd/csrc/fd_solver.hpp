@@ -38,7 +38,8 @@ ProductWs carve_product(Arena& a, int64_t Nr, int64_t Nc, int64_t D, int b);
 void product_apply(ProductWs& w, const float* sl, const float* sr, const float* V, int64_t ldv,
                    int b, float* Y, int64_t ldy, bool diag, hipStream_t stream);
 
-DegreeWs carve_degree(Arena& a, int64_t N, int64_t D);
+// prefixes: degree_view may be taken of it (the partial sums hold every shorter plan).
+DegreeWs carve_degree(Arena& a, int64_t N, int64_t D, bool prefixes = false);
 // q, d, s (any may be NULL) and s_off, from X; with `poison` the outputs are NaN
 // where X is not finite or beta is out of range.
 void degree_run(DegreeWs& w, const void* X, fd_dtype xt, int64_t N, int64_t D, int64_t ldx,
@@ -53,9 +54,6 @@ void degree_run_dyadic(DegreeWs& w, const void* X, fd_dtype xt, int64_t N, int64
                        int64_t ldx, double beta0, int nb, double alpha, float* q, float* d,
                        float* s, double* s_off, hipStream_t stream);
 
-// Row slots of a partial-sum buffer large enough for every plan with at most
-// npad rows and nc columns (see plan_product).
-size_t part_rows_bound(int64_t npad, int64_t nc);
 // Views of workspace carved for a larger problem, for n <= the carved size.
 PointPack pack_view(const PointPack& big, int64_t n, int64_t pad);
 DegreeWs degree_view(const DegreeWs& big, int64_t n);

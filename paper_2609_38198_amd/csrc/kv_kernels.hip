@@ -1126,109 +1126,6 @@ int64_t qsum_words(int64_t npad) { return ceil_div(npad, 256); }
 
 // ------------------------------------------------------------------ host side
 
-// Workgroups of one resident round: products and symmetric row sums hold two
-// waves per SIMD, so 256 CUs take two four-wave workgroups each.
-constexpr int64_t ONE_ROUND = 512;
-
-// `round`: split the columns for one resident round of workgroups (never more
-// than ONE_ROUND) instead of for >= 2048
-static KVPlan plan_tiles(int64_t Nr, int64_t Nc, int dp, int b, int nib, bool round) {
-  KVPlan p;
-  p.dp = dp;
-  p.ncb = int(ceil_div(b, 16));
-  p.nib = nib;
-  p.njb = ceil_div(Nc, TILE);
-  const int64_t rows_per_wg = 4 * p.nib * TILE;
-  p.nrt = ceil_div(round_up(Nr, ROW_PAD), rows_per_wg);
-  // aim for >= 2048 workgroups (eight per CU), keep >= 8 column tiles per split
-  int64_t ns = std::max<int64_t>(1, round ? ONE_ROUND / p.nrt : ceil_div(2048, p.nrt));
-  ns = std::min<int64_t>(ns, std::max<int64_t>(1, p.njb / 8));
-  // at most SPLIT_SPAN_TILES column tiles per workgroup: the workgroups that
-  // run together on an XCD start a split together and drift apart as they go;
-  // over a shorter span they stay close enough to share column tiles in L2
-  ns = std::max<int64_t>(ns, ceil_div(p.njb, SPLIT_SPAN_TILES));
-  ns = std::min<int64_t>(ns, 64);
-  // splits hold an even number of column tiles (the split product takes them in pairs)
-  p.jb_per_split = round_up(ceil_div(p.njb, ns), 2);
-  p.nsplit = int(ceil_div(p.njb, p.jb_per_split));
-  return p;
-}
-
-// Row tiles per wave and splits of the fused product.
-//
-// Eight row tiles for one 16-column block at D <= 12 above 2^28 pairs (6-torus,
-// b = 16, microseconds for eight / four: N = 65,536 862 / 898, N = 32,768
-// 256 / 270, N = 18,000 104 / 106: two instructions per exponent tile leave room
-// for more independent chains).  Four below, where twice the workgroups count
-// for more (N = 8,192 43 / 38, N = 4,096 27 / 26, N = 1,000 25 / 21; equal at
-// 16,384), and on every other shape (the fastest or tied in D in {4, 12, 30, 64},
-// b in {8 .. 64}; two and eight are 11-17% slower at D = 30, b = 32).
-//
-// One round of workgroups up to 3 * 2^27 pairs (about N = 20,000): each
-// workgroup's start and its partial product, written and read again, cost more
-// there than the uneven end of a few long workgroups (2048 workgroups / one
-// round: D = 30, b = 32, N = 8,192 67 / 57, 20,000 173 / 165; 6-torus, b = 32,
-// N = 16,384 115 / 102, b = 16, N = 16,384 95 / 87).  Beyond, the uneven end
-// does (D = 30, b = 32, N = 28,000 289 / 296; b = 16, N = 24,000 182 / 186).
-constexpr int64_t WIDE_ROWS_PAIRS = int64_t(1) << 28;
-constexpr int64_t ONE_ROUND_PAIRS = int64_t(3) << 27;
-
-KVPlan plan_product(int64_t Nr, int64_t Nc, int dp, int b) {
-  const double pairs = double(Nr) * double(Nc);
-  const int nib = (b <= 16 && dp <= 12 && pairs > double(WIDE_ROWS_PAIRS)) ? 8 : 4;
-  return plan_tiles(Nr, Nc, dp, b, nib, pairs <= double(ONE_ROUND_PAIRS));
-}
-
-// Row sums: eight row tiles per wave (more independent exponent chains per
-// column tile than four; measured faster on every shape).
-KVPlan plan_rowsum(int64_t Nr, int64_t Nc, int dp) {
-  return plan_tiles(Nr, Nc, dp, 1, 8, false);
-}
-
-// Symmetric row sums (one point set): workgroups of 4 waves x nib row tiles
-// own blocks of 64 nib points; a block's column range (its own block and about
-// half of the others) is split.  nrt holds the number of blocks.  From 64
-// blocks up, for >= 2048 workgroups and by whole blocks (at least
-// SYM_MIN_SPLITS of them): the workgroups whose windows start at the same
-// block then read the same column tiles, and the kernel runs them side by side
-// on one XCD so that they share its L2.  Up to 48 blocks, for one resident
-// round: a workgroup's column sums end in atomic adds, and fewer, longer
-// workgroups make fewer of them (fd_degree, 2048 workgroups / one round in
-// microseconds: D = 30, N = 9,000 79 / 66, N = 16,000 140 / 115; D = 12,
-// N = 20,000 168 / 151; bfloat16 points, D = 30, N = 9,000 59 / 54), down to four
-// column tiles a workgroup (eight / four: N = 2,048 37 / 33, N = 512 34 / 29).
-// In between the uneven end of one round begins to cost more than it saves
-// (bfloat16 points, D = 30, N = 28,000: 215 / 221).
-KVPlan plan_rowsum_sym(int64_t N, int64_t npad, int dp, int nib) {
-  KVPlan p;
-  p.dp = dp;
-  p.ncb = 1;
-  p.nib = nib;
-  p.njb = ceil_div(N, TILE);
-  const int64_t BT = 4 * nib;
-  p.nrt = npad / (BT * TILE);
-  const int64_t span_blocks = 1 + (p.nrt - 1) / 2 + (p.nrt % 2 == 0 ? 1 : 0);  // longest range
-  if (p.nrt >= 64) {
-    const int64_t ns = std::max<int64_t>(SYM_MIN_SPLITS, ceil_div(2048, p.nrt));
-    const int64_t jbk = std::max<int64_t>(1, span_blocks / ns);
-    p.jb_per_split = jbk * BT;
-    p.nsplit = int(ceil_div(span_blocks, jbk));
-    return p;
-  }
-  const int64_t span = BT * span_blocks;
-  int64_t ns =
-      std::max<int64_t>(1, p.nrt <= 48 ? ONE_ROUND / p.nrt : ceil_div(2048, p.nrt));
-  ns = std::min<int64_t>(ns, std::max<int64_t>(1, span / 4));
-  ns = std::min<int64_t>(ns, 64);
-  p.jb_per_split = round_up(ceil_div(span, ns), 2);
-  p.nsplit = int(ceil_div(span, p.jb_per_split));
-  return p;
-}
-
-size_t sym_part_rows(int64_t npad, int nib) {
-  return size_t(plan_rowsum_sym(npad, npad, 4, nib).nsplit) * size_t(npad);
-}
-
 static inline size_t lane4_extent(int64_t tiles, int groups) {
   return size_t(tiles) * groups * 64 * 4;
 }

@@ -115,14 +115,15 @@ struct SolverWs {
   int mm_cap = 0, b = 0;
 };
 
-// prod_width: widest product the caller will run (b, or 64 for the Nystrom pass)
+// prod_width: widest product the caller will run (b, or 64 for the Nystrom pass);
+// prefixes: the caller solves prefixes of the N points too
 static SolverWs carve_solver_ws(Arena& a, int64_t N, int64_t D, int b, int mm_cap,
-                                int prod_width) {
+                                int prod_width, bool prefixes = false) {
   SolverWs w;
   w.N = N;
   w.mm_cap = mm_cap;
   w.b = b;
-  w.deg = carve_degree(a, N, D);
+  w.deg = carve_degree(a, N, D, prefixes);
   // the product shares the degree pass's point packs
   w.prod.plan = plan_product(N, N, padded_dim(D), prod_width);
   w.prod.rows = w.deg.rows;
@@ -444,7 +445,7 @@ static ContWs carve_continuation(Arena& a, int64_t nmax, int64_t nsteps, int64_t
   c.nmax = nmax;
   c.k = k;
   const SolverLayout L = solver_layout(nmax, b, k, o);
-  c.sw = carve_solver_ws(a, nmax, D, b, L.mm, 64);
+  c.sw = carve_solver_ws(a, nmax, D, b, L.mm, 64, true);
   c.store_psi = a.take<float>(size_t(nsteps) * nmax * k);
   c.store_q = a.take<float>(size_t(nsteps) * nmax);
   c.ext = a.take<float>(size_t(nmax) * k);

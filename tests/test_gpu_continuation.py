@@ -135,3 +135,21 @@ def test_noisy_torus6_ladder_at_its_sizes():
     cold = fd.fd_block_lanczos(tX[:16384], 2.0, k, b)
     assert eval_ok(lad.evals[t2], cold.evals), (np.abs(np.asarray(lad.evals[t2]) -
                                                        np.asarray(cold.evals)).max())
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+def test_prefix_with_more_partial_sums_than_the_whole(dtype):
+    """45,568 points (89 blocks of 512) split their symmetric row sums 45 ways,
+    65,536 points 18 ways: the shorter solve needs more partial sums."""
+    import torch
+
+    x = to_dev(inputs.torus_points(65536, 2, seed=5).astype(np.float32), device())
+    if dtype == "bf16":
+        x = x.to(torch.bfloat16)
+    ns, bs = [45568, 65536], [2.0, 2.0]
+    case(f"continuation 45568 -> 65536 {dtype}")
+    lad = fd.fd_continuation(x, ns, bs, 4, 8)
+    assert lad.steps_done == 2
+    for t, n in enumerate(ns):
+        cold = fd.fd_block_lanczos(x[:n], bs[t], 4, 8)
+        assert eval_ok(lad.evals[t], cold.evals[:4])
