@@ -68,7 +68,10 @@ ProductWs carve_product(Arena& a, int64_t Nr, int64_t Nc, int64_t D, int b) {
   w.vp = a.fspan(size_t(w.cols.npad) * w.plan.ncb * 16);
   w.vscale = a.fspan(VSCALE_FLOATS);
   w.part = a.fspan(part_rows_bound(w.rows.npad, Nc) * w.plan.ncb * 16);
-  if (b == 1) w.colfix = a.take<unsigned long long>(size_t(w.rows.npad));
+  if (b == 1) {
+    w.colfix = a.take<unsigned long long>(size_t(w.rows.npad));
+    w.colfix_lo = a.take<unsigned long long>(size_t(w.rows.npad));
+  }
   w.flag = a.take<int>(1);
   w.centre = carve_centre(a, Nc, Nr);
   return w;
@@ -89,7 +92,10 @@ static ProductWs carve_product_exact(Arena& a, int64_t Nr, int64_t Nc, int64_t D
   const size_t part_row =
       std::max(size_t(rp.nsplit) * w.rows.npad, sym_part_rows(w.rows.npad, SYM_NIB));
   w.part = a.fspan(b == 1 ? part_row : part_prod);
-  if (b == 1) w.colfix = a.take<unsigned long long>(size_t(w.rows.npad));
+  if (b == 1) {
+    w.colfix = a.take<unsigned long long>(size_t(w.rows.npad));
+    w.colfix_lo = a.take<unsigned long long>(size_t(w.rows.npad));
+  }
   w.flag = a.take<int>(1);
   w.centre = carve_centre(a, Nc, Nr);
   return w;
@@ -154,7 +160,7 @@ static void product_run(ProductWs& w, const float* sl, int b, float* Y, int64_t 
     // one right-hand side: weighted row sums K (sr v) on the vector ALUs (no
     // matrix-core contraction padded to 16 columns), then the row scale
     launch_product_column(plan_rowsum(w.rows.n, w.cols.n, w.rows.dp), w.rows, w.cols, w.vp,
-                          w.vscale, diag, sl, Y, ldy, w.part, w.colfix, poison, stream);
+                          w.vscale, diag, sl, Y, ldy, w.part, w.colfix, w.colfix_lo, poison, stream);
     return;
   }
   launch_product(w.plan, w.rows, w.cols, w.vp, w.vscale, diag, sl, Y, ldy, b, w.part, poison,
@@ -209,6 +215,7 @@ static void matmul_run(ProductWs& w, const void* Xr, const void* Xc, int64_t D, 
   in.vscale = w.vscale;
   in.nvmax = vmax_blocks(w.cols.n);
   in.zero1 = w.colfix;
+  in.zero2 = w.colfix_lo;
   in.nzero = w.colfix != nullptr ? w.rows.npad : 0;
   launch_packs(in, w.rows, w.cols, w.centre, st);
   product_run(w, sl, b, Y, ldy, diag, poison_gate(xt, w.centre, beta, w.flag), st);
@@ -236,9 +243,9 @@ DegreeWs carve_degree(Arena& a, int64_t N, int64_t D, bool prefixes) {
 }
 
 // Row and column packs of one point set at one bandwidth, with the column-sum
-// words of the symmetric passes cleared (sq: the squared kernel's too).
+// words of the symmetric passes (and the squared kernel's, where carved) cleared.
 static void degree_packs(DegreeWs& w, const void* X, fd_dtype xt, int64_t D, int64_t ldx,
-                         double beta, bool sq, int* flag, hipStream_t stream) {
+                         double beta, int* flag, hipStream_t stream) {
   PackIn in;
   in.Xr = in.Xc = X;
   in.xt = xt;
@@ -247,7 +254,7 @@ static void degree_packs(DegreeWs& w, const void* X, fd_dtype xt, int64_t D, int
   in.beta = beta;
   in.flag = flag;
   in.zero1 = w.colfix;
-  in.zero2 = sq ? w.sq_colfix : nullptr;
+  in.zero2 = w.sq_colfix;
   in.nzero = w.rows.npad;
   launch_packs(in, w.rows, w.cols, w.centre, stream);
 }
@@ -289,7 +296,7 @@ void degree_run(DegreeWs& w, const void* X, fd_dtype xt, int64_t N, int64_t D, i
                 bool poison, hipStream_t stream) {
   degree_prologue(w, X, xt, N, D, ldx, stream);
   int* flag = poison ? w.flag : nullptr;
-  degree_packs(w, X, xt, D, ldx, beta, false, flag, stream);
+  degree_packs(w, X, xt, D, ldx, beta, flag, stream);
   degree_passes(w, N, alpha, q, d, s, s_off, poison_gate(xt, w.centre, beta, flag), stream);
 }
 
@@ -307,14 +314,14 @@ void degree_run_dyadic(DegreeWs& w, const void* X, fd_dtype xt, int64_t N, int64
   auto off_at = [s_off](int l) { return s_off != nullptr ? s_off + l : nullptr; };
   auto beta_of = [beta0](int l) { return std::ldexp(beta0, l); };
   degree_prologue(w, X, xt, N, D, ldx, stream);
-  degree_packs(w, X, xt, D, ldx, beta_of(0), true, w.flag, stream);
+  degree_packs(w, X, xt, D, ldx, beta_of(0), w.flag, stream);
   // the largest bandwidth decides (every level's outputs are poisoned)
   const PoisonGate poison = poison_gate(xt, w.centre, beta_of(nb - 1), w.flag);
   if (alpha == 0.0 || xt == FD_BF16) {
     // no weighted pass to carry the squares (alpha = 0), or bfloat16 inputs
     // (stated level by level): fd_degree's passes
     for (int l = 0; l < nb; ++l) {
-      if (l > 0) degree_packs(w, X, xt, D, ldx, beta_of(l), true, nullptr, stream);
+      if (l > 0) degree_packs(w, X, xt, D, ldx, beta_of(l), nullptr, stream);
       degree_passes(w, N, alpha, at(q, l), at(d, l), at(s, l), off_at(l), poison, stream);
     }
     return;
@@ -330,7 +337,7 @@ void degree_run_dyadic(DegreeWs& w, const void* X, fd_dtype xt, int64_t N, int64
                          poison, stream);
   for (int l = 0; l < nb; ++l) {
     // (the column-sum words are zero already; clearing them again is harmless)
-    if (l > 0) degree_packs(w, X, xt, D, ldx, beta_of(l), true, nullptr, stream);
+    if (l > 0) degree_packs(w, X, xt, D, ldx, beta_of(l), nullptr, stream);
     if (l + 1 == nb) {
       const SymPass p2 = launch_rowsum_sym_pass(w.plan, w.rows, w.cols, w.wp, w.part, w.colfix,
                                                 stream);

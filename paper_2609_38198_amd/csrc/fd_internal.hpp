@@ -223,13 +223,13 @@ void launch_product(const KVPlan& p, const PointPack& rows, const PointPack& col
                     FSpan vscale, bool diag, const float* sl, float* Y, int64_t ldy, int b,
                     FSpan part, const PoisonGate& poison, hipStream_t stream);
 // Y[:, 0] = diag(sl) K diag(sr) v for one column from its weight pack: on one
-// point set (colfix set: npad cleared words, left cleared) the symmetric row
-// sums, or the plain ones where the column holds a NaN or an infinity; else
-// the plain ones.
+// point set (colfix, colfix_lo set: npad cleared words each, left cleared) the
+// symmetric row sums, or the plain ones where the column holds a NaN or an
+// infinity or spans more than column_range; else the plain ones.
 void launch_product_column(const KVPlan& p, const PointPack& rows, const PointPack& cols, FSpan wp,
                            FSpan vscale, bool diag, const float* sl, float* Y, int64_t ldy,
-                           FSpan part, unsigned long long* colfix, const PoisonGate& poison,
-                           hipStream_t stream);
+                           FSpan part, unsigned long long* colfix, unsigned long long* colfix_lo,
+                           const PoisonGate& poison, hipStream_t stream);
 // out = K w (wp.p == NULL: w = 1).
 void launch_rowsum(const KVPlan& p, const PointPack& rows, const PointPack& cols, FSpan wp,
                    bool diag, float* out, FSpan part, hipStream_t stream);
@@ -248,6 +248,13 @@ struct SymPass {
 };
 // Second output of a weighted symmetric pass: the unit-weight row sums (per
 // split, part) and fixed-point column sums (colfix) of the squared kernel.
+// Fixed-point column sums: one word per point with `frac` fractional bits, or
+// (lo set) two, the workgroups' words split at WIDE_SPLIT bits (fd_plans.hpp).
+struct ColumnWords {
+  unsigned long long* hi = nullptr;
+  unsigned long long* lo = nullptr;
+  int frac = 0;
+};
 struct SymSquares {
   float* part = nullptr;
   unsigned long long* colfix = nullptr;
@@ -255,11 +262,13 @@ struct SymSquares {
 bool rowsum_sym_applies(const PointPack& rows, const PointPack& cols, bool diag,
                         const unsigned long long* colfix);
 // sq_part / sq_colfix (weighted passes only): also the squared-kernel sums, whose
-// reduction uses the returned inv_fix as well.
+// reduction uses the returned inv_fix as well.  colfix_lo (weighted passes
+// only): two words per column sum.
 SymPass launch_rowsum_sym_pass(const KVPlan& p, const PointPack& rows, const PointPack& cols,
                                FSpan wp, FSpan part, unsigned long long* colfix,
                                hipStream_t stream, FSpan sq_part = FSpan{},
-                               unsigned long long* sq_colfix = nullptr);
+                               unsigned long long* sq_colfix = nullptr,
+                               unsigned long long* colfix_lo = nullptr);
 void launch_degree_reduce_q(const SymPass& sp, const PointPack& rows, const PointPack& cols,
                             FSpan part, unsigned long long* colfix, float* q, double alpha,
                             FSpan wp, double* qsum, const PoisonGate& poison, hipStream_t stream);

@@ -6,6 +6,7 @@
 #include <stdint.h>
 
 #include <algorithm>
+#include <cmath>
 
 namespace fd {
 
@@ -156,6 +157,24 @@ inline size_t sym_part_rows_within(int64_t npad, int nib) {
     need = std::max(need, sym_part_rows(k * block, nib));
   return need;
 }
+
+// Column sums of a single-column product over the symmetric row sums.  A wave's
+// contribution (weights below 1, 128 rows) is rounded to WIDE_FRAC fractional
+// bits; a workgroup adds at most four of them to a column (below 2^9, so that
+// its 64-bit word holds them), splits the word and adds its signed upper part
+// and its lower WIDE_SPLIT bits to two global words: no sum over the up to 2^21
+// blocks takes bits from the fraction (one 64-bit word would have 40 at 2^20
+// points, where results of small weights lost up to 2% of themselves).
+constexpr int WIDE_FRAC = 53;
+constexpr int WIDE_SPLIT = 32;
+
+// Widest column (largest over smallest |weight|) that takes them.  A result
+// holds its own point's weight (K_ii = 1), at least half of 1 / range, and up to
+// npad / 256 roundings of 2^-(WIDE_FRAC + 1) each: at this range they come to
+// 2^-18 of that weight if all have one sign and their full size (the float32 sums of a
+// row's 256-term chains may lose 2^-16).  Wider columns, sparse ones among them,
+// take the plain float32 sums.
+inline float column_range(int64_t npad) { return std::ldexp(1.f, 43) / float(npad); }
 
 // Every plan has nsplit <= max(ceil(2048 / row blocks), ceil(column tiles /
 // SPLIT_SPAN_TILES)), so the partial buffers of any problem with at most npad

@@ -9,7 +9,7 @@ namespace fd {
 struct ProductWs {
   PointPack rows, cols;
   FSpan vp, vscale, part;
-  unsigned long long* colfix = nullptr;  // single columns: npad column-sum words
+  unsigned long long *colfix = nullptr, *colfix_lo = nullptr;  // single columns: npad column-sum words each
   int* flag = nullptr;  // set when a point set holds a non-finite value
   CentreWs centre;      // common centre of the row and column sets
   KVPlan plan;
@@ -24,7 +24,7 @@ struct DegreeWs {
   unsigned long long* colfix = nullptr;  // npad words: column sums of the symmetric row sums
   double* qsum = nullptr;                // twice qsum_words(npad): partial sums of q
   FSpan sq_part;                          // squared-kernel row partials (dyadic levels)
-  unsigned long long* sq_colfix = nullptr;
+  unsigned long long* sq_colfix = nullptr;  // their column sums; cleared by the packs too
   int* flag = nullptr;  // set when X holds a non-finite value
   CentreWs centre;      // centre of X
   KVPlan plan;

@@ -932,41 +932,40 @@ void rowsum_hx_u(const KVPlan& p, const PointPack& rows, const PointPack& cols, 
     rowsum_hx_launch<RID, 4, false>(p, rows, cols, wp, diag, out, part, stream);
 }
 
-template <int RID, int NIB, bool UNIT, bool SQ>
+template <int RID, int NIB, bool UNIT, bool SQ, bool TWO = false>
 void rowsum_sym_hx_launch(const KVPlan& p, const PointPack& rows, const PointPack& cols,
-                          const float* wp, float* part, unsigned long long* colfix,
-                          int frac, const SymSquares& sq, hipStream_t stream) {
+                          const float* wp, float* part, const ColumnWords& col,
+                          const SymSquares& sq, hipStream_t stream) {
   const unsigned grid = unsigned(p.nrt * p.nsplit);
   const typename HxTile<RID>::Args ta{reinterpret_cast<const uintx4*>(cols.xp.p),
                                       reinterpret_cast<const uintx4*>(rows.xp.p)};
-  hipLaunchKernelGGL((rowsum_sym_kernel<HxTile<RID>, NIB, UNIT, SQ>), dim3(grid),
+  hipLaunchKernelGGL((rowsum_sym_kernel<HxTile<RID>, NIB, UNIT, SQ, TWO>), dim3(grid),
                      dim3(WG_THREADS), 0, stream, ta, reinterpret_cast<const floatx4*>(wp), p.nrt,
                      p.njb, p.jb_per_split,
-                     int64_t(p.nsplit), part, rows.npad, colfix,
-                     std::ldexp(1.0 / HxTile<RID>::ONE, frac), sq.part, sq.colfix,
-                     std::ldexp(1.0 / (double(HxTile<RID>::ONE) * HxTile<RID>::ONE), frac),
+                     int64_t(p.nsplit), part, rows.npad, col.hi, col.lo,
+                     std::ldexp(1.0 / HxTile<RID>::ONE, col.frac), sq.part, sq.colfix,
+                     std::ldexp(1.0 / (double(HxTile<RID>::ONE) * HxTile<RID>::ONE), col.frac),
                      gate_of(rows));
   FD_LAUNCH_CHECK();
 }
 
 template <int RID>
 void rowsum_sym_hx_u(const KVPlan& p, const PointPack& rows, const PointPack& cols,
-                     const float* wp, float* part, unsigned long long* colfix, int frac,
+                     const float* wp, float* part, const ColumnWords& col,
                      const SymSquares& sq, hipStream_t stream) {
   if (sq.part != nullptr) {
     // squared sums: weighted passes of the eight-tile plan only
     FD_REQUIRE(p.nib == 8 && wp != nullptr, FD_ERR_INVALID_ARG,
                "internal: squared sums need a weighted eight-tile pass");
-    rowsum_sym_hx_launch<RID, 8, false, true>(p, rows, cols, wp, part, colfix, frac, sq,
-                                              stream);
+    rowsum_sym_hx_launch<RID, 8, false, true>(p, rows, cols, wp, part, col, sq, stream);
     return;
   }
   if (wp == nullptr)
-    rowsum_sym_hx_launch<RID, 8, true, false>(p, rows, cols, wp, part, colfix, frac, sq,
-                                              stream);
+    rowsum_sym_hx_launch<RID, 8, true, false>(p, rows, cols, wp, part, col, sq, stream);
+  else if (col.lo != nullptr)
+    rowsum_sym_hx_launch<RID, 8, false, false, true>(p, rows, cols, wp, part, col, sq, stream);
   else
-    rowsum_sym_hx_launch<RID, 8, false, false>(p, rows, cols, wp, part, colfix, frac, sq,
-                                               stream);
+    rowsum_sym_hx_launch<RID, 8, false, false>(p, rows, cols, wp, part, col, sq, stream);
 }
 
 void check_hx(const KVPlan& p, const PointPack& rows, const PointPack& cols) {
@@ -1117,8 +1116,8 @@ void launch_product_hx(const KVPlan& p, const PointPack& rows, const PointPack& 
 }
 
 void launch_rowsum_sym_hx(const KVPlan& p, const PointPack& rows, const PointPack& cols,
-                          const float* wp, float* part, unsigned long long* colfix,
-                          int frac, const SymSquares& sq, hipStream_t stream) {
+                          const float* wp, float* part, const ColumnWords& col,
+                          const SymSquares& sq, hipStream_t stream) {
   FD_REQUIRE(rows.rid >= 0 && rows.rid < HX_RECIPES && rows.rid == cols.rid && rows.row_side &&
                  !cols.row_side && rows.n == cols.n,
              FD_ERR_INVALID_ARG, "internal: symmetric row sums need one point set");
@@ -1130,13 +1129,13 @@ void launch_rowsum_sym_hx(const KVPlan& p, const PointPack& rows, const PointPac
     check_span(r.xp, size_t(r.npad / TILE) * R.nb * 64 * 4, "split row pack");
     check_span(c.xp, size_t(round_up(p.njb, 2)) * R.nc * 64 * 4, "split column pack");
     switch (r.rid) {
-      case 0: return rowsum_sym_hx_u<0>(p, r, c, wp, part, colfix, frac, sq, stream);
-      case 1: return rowsum_sym_hx_u<1>(p, r, c, wp, part, colfix, frac, sq, stream);
-      case 2: return rowsum_sym_hx_u<2>(p, r, c, wp, part, colfix, frac, sq, stream);
-      case 3: return rowsum_sym_hx_u<3>(p, r, c, wp, part, colfix, frac, sq, stream);
-      case 4: return rowsum_sym_hx_u<4>(p, r, c, wp, part, colfix, frac, sq, stream);
-      case 5: return rowsum_sym_hx_u<5>(p, r, c, wp, part, colfix, frac, sq, stream);
-      case 6: return rowsum_sym_hx_u<6>(p, r, c, wp, part, colfix, frac, sq, stream);
+      case 0: return rowsum_sym_hx_u<0>(p, r, c, wp, part, col, sq, stream);
+      case 1: return rowsum_sym_hx_u<1>(p, r, c, wp, part, col, sq, stream);
+      case 2: return rowsum_sym_hx_u<2>(p, r, c, wp, part, col, sq, stream);
+      case 3: return rowsum_sym_hx_u<3>(p, r, c, wp, part, col, sq, stream);
+      case 4: return rowsum_sym_hx_u<4>(p, r, c, wp, part, col, sq, stream);
+      case 5: return rowsum_sym_hx_u<5>(p, r, c, wp, part, col, sq, stream);
+      case 6: return rowsum_sym_hx_u<6>(p, r, c, wp, part, col, sq, stream);
     }
   });
 }

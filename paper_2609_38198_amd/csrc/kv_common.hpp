@@ -103,23 +103,17 @@ __device__ __forceinline__ bool poisoned(const PoisonGate& g) {
 
 constexpr int PACK_THREADS = 128;  // workgroup of the pack kernels
 
-// Widest column (largest over smallest |sr v|) that a single-column product takes
-// through the fixed-point column sums.  They resolve 2^-44 of the largest
-// weight at N = 65,536; a sum holds its own point's weight (K_ii = 1), so within
-// this range it keeps about 2^-20 of itself.  Sparse or decaying columns go to
-// the float32 sums, which keep far smaller results too.
-constexpr float COLUMN_RANGE = 16777216.f;  // 2^24
-
 // The V part of a pack launch: V (n x b, ldv) times sr, as the split pack of
 // ncb 16-column blocks over npairs pairs of 16-point tiles, or (ncb = 0) as the
 // weight pack of its one column over ntiles tiles; with nvmax that column is
 // scaled by 2^-e to below 1 (colscale[0] = e, colscale[1] = 1 where it holds a
-// NaN or an infinity or spans more than COLUMN_RANGE, else 0).
+// NaN or an infinity or spans more than `range`, else 0).
 struct PackV {
   const float* V = nullptr;
   const float* sr = nullptr;
   int64_t n = 0, ldv = 0, npairs = 0, ntiles = 0;
   int b = 0, ncb = 0, nvmax = 0;
+  float range = 0.f;             // column_range
   const float* vpart = nullptr;  // nvmax x 64 partial column maxima
   float* colscale = nullptr;
   VSplit* vp = nullptr;
@@ -155,7 +149,7 @@ __device__ __forceinline__ void pack_v_block(const PackV& a, int64_t blk, int* e
         bad = fmaxf(bad, __shfl_xor(bad, o));
         mn = fminf(mn, __shfl_xor(mn, o));
       }
-      if (mn * COLUMN_RANGE < m) bad = 1.f;
+      if (mn * a.range < m) bad = 1.f;
       ex1 = bad != 0.f ? 0 : 14 - vscale_exponent(m);
       if (idx == 0) {
         a.colscale[0] = float(ex1);
@@ -285,12 +279,12 @@ void launch_product_hx(const KVPlan& p, const PointPack& rows, const PointPack& 
 void launch_rowsum_hx(const KVPlan& p, const PointPack& rows, const PointPack& cols,
                       const float* wp, bool diag, float* out, float* part, hipStream_t stream);
 // Symmetric row sums of one point set (rows.n == cols.n): per-split row partials
-// into part ([nsplit][rows.npad]) and column sums added into colfix (64-bit fixed
-// point with `frac` fractional bits; weights in [-1, 1]).  With sq.part set
+// into part ([nsplit][rows.npad]) and column sums added into col (fixed point;
+// weights in [-1, 1]).  With sq.part set
 // (weighted passes only), the unit-weight sums of the squared kernel K^2 (the
 // kernel at twice the bandwidth) go the same way into sq.part and sq.colfix.
 void launch_rowsum_sym_hx(const KVPlan& p, const PointPack& rows, const PointPack& cols,
-                          const float* wp, float* part, unsigned long long* colfix, int frac,
+                          const float* wp, float* part, const ColumnWords& col,
                           const SymSquares& sq, hipStream_t stream);
 
 // Scheduling pattern for a region holding M matrix instructions and E

@@ -883,13 +883,13 @@ struct Bf16Tile {
 };
 
 // One column on one point set: Y_i = sl_i 2^e (row partials + fixed-point column
-// sums), which are left cleared; where the column was not finite (bad != 0) from
-// the plain row sums' partials instead.
+// sums in two words), which are left cleared; where the column could not be
+// taken so (bad != 0) from the plain row sums' partials instead.
 __global__ __launch_bounds__(256) void column_finish_kernel(
     const float* __restrict__ part, int nsplit_plain, int nsplit_sym, int64_t nrpad,
-    unsigned long long* __restrict__ colfix, double inv_fix, const float* __restrict__ colscale,
-    const float* __restrict__ sl, int64_t n, int64_t npad, float* __restrict__ Y, int64_t ldy,
-    PoisonGate poison) {
+    unsigned long long* __restrict__ colfix, unsigned long long* __restrict__ colfix_lo,
+    const float* __restrict__ colscale, const float* __restrict__ sl, int64_t n, int64_t npad,
+    float* __restrict__ Y, int64_t ldy, PoisonGate poison) {
   const int64_t i = int64_t(blockIdx.x) * 256 + threadIdx.x;
   const bool sym = colfix != nullptr && colscale[1] == 0.f;
   if (i < n) {
@@ -897,12 +897,15 @@ __global__ __launch_bounds__(256) void column_finish_kernel(
     double s = 0.0;
 #pragma unroll 8
     for (int k = 0; k < ns; ++k) s += double(part[k * nrpad + i]);
-    if (sym) s += double(static_cast<long long>(colfix[i])) * inv_fix;
+    if (sym)
+      s += (double(static_cast<long long>(colfix[i])) * (1ull << WIDE_SPLIT) +
+            double(colfix_lo[i])) *
+           (1.0 / double(1ull << WIDE_FRAC));
     float y = float(ldexp(s, int(colscale[0])));
     if (sl != nullptr) y = sl[i] * y;
     Y[i * ldy] = poisoned(poison) ? __builtin_nanf("") : y;
   }
-  if (colfix != nullptr && i < npad) colfix[i] = 0ull;
+  if (colfix != nullptr && i < npad) colfix[i] = colfix_lo[i] = 0ull;
 }
 
 // Y = diag(sl) (sum over splits of part) diag(colscale), NaN where the call is
@@ -1196,6 +1199,7 @@ static PackV pack_v_args(const float* V, int64_t n, int64_t b, int64_t ldv, cons
     if (nvmax > 0) {
       check_span(vscale, VSCALE_FLOATS, "column scales");
       v.nvmax = int(nvmax);
+      v.range = column_range(round_up(n, ROW_PAD));
       v.colscale = vscale.p;
       v.vpart = vscale.p + 64;
     }
@@ -1403,9 +1407,9 @@ bool rowsum_sym_applies(const PointPack& rows, const PointPack& cols, bool diag,
   return colfix != nullptr && diag && rows.bf16 == cols.bf16 && rows.n == cols.n;
 }
 
-template <int DC, bool UNIT>
+template <int DC, bool UNIT, bool TWO = false>
 static void rowsum_sym_bf16(const KVPlan& p, const PointPack& rows, const PointPack& cols,
-                            const float* wp, float* part, unsigned long long* colfix, int frac,
+                            const float* wp, float* part, const ColumnWords& col,
                             hipStream_t stream) {
   using T = Bf16Tile<DC>;
   const typename T::Args ta{reinterpret_cast<const uintx4*>(cols.xp.p),
@@ -1413,16 +1417,17 @@ static void rowsum_sym_bf16(const KVPlan& p, const PointPack& rows, const PointP
                             reinterpret_cast<const uintx4*>(rows.xp.p), rows.ar.p,
                             float(2.0 * rows.beta * LOG2E)};
   ProfScope prof(FD_KERNEL_ROWSUM, stream);
-  hipLaunchKernelGGL((rowsum_sym_kernel<T, 8, UNIT>), dim3(unsigned(p.nrt * p.nsplit)),
+  hipLaunchKernelGGL((rowsum_sym_kernel<T, 8, UNIT, false, TWO>), dim3(unsigned(p.nrt * p.nsplit)),
                      dim3(WG_THREADS), 0, stream, ta, reinterpret_cast<const floatx4*>(wp), p.nrt,
-                     p.njb, p.jb_per_split, int64_t(p.nsplit), part, rows.npad, colfix,
-                     std::ldexp(1.0, frac), nullptr, nullptr, 0.0, gate_of(rows));
+                     p.njb, p.jb_per_split, int64_t(p.nsplit), part, rows.npad, col.hi, col.lo,
+                     std::ldexp(1.0, col.frac), nullptr, nullptr, 0.0, gate_of(rows));
   FD_LAUNCH_CHECK();
 }
 
 SymPass launch_rowsum_sym_pass(const KVPlan& p, const PointPack& rows, const PointPack& cols,
                                FSpan wp, FSpan part, unsigned long long* colfix, hipStream_t stream,
-                               FSpan sq_part, unsigned long long* sq_colfix) {
+                               FSpan sq_part, unsigned long long* sq_colfix,
+                               unsigned long long* colfix_lo) {
   check_tiles(p, rows, cols);
   FD_REQUIRE(rowsum_sym_applies(rows, cols, true, colfix), FD_ERR_INVALID_ARG,
              "internal: symmetric row sums need one point set");
@@ -1430,8 +1435,13 @@ SymPass launch_rowsum_sym_pass(const KVPlan& p, const PointPack& rows, const Poi
   if (wp.p != nullptr) check_span(wp, lane4_extent(sp.njb, 1), "weight pack");
   check_span(part, size_t(sp.nsplit) * rows.npad, "partial row sums");
   // fixed point with F fractional bits: the total of weights in [-1, 1] over
-  // npad columns stays below 2^62 / 4 (and so does that of K^2 <= 1)
-  const int F = 62 - int(std::ceil(std::log2(double(rows.npad)))) - 2;
+  // npad columns stays below 2^62 / 4 (and so does that of K^2 <= 1); two words
+  // have no total to leave room for
+  FD_REQUIRE(colfix_lo == nullptr || (wp.p != nullptr && sq_part.p == nullptr),
+             FD_ERR_INVALID_ARG, "internal: column words");
+  const int F = colfix_lo != nullptr ? WIDE_FRAC
+                                     : 62 - int(std::ceil(std::log2(double(rows.npad)))) - 2;
+  const ColumnWords col{colfix, colfix_lo, F};
   SymSquares sq;
   if (sq_part.p != nullptr) {
     FD_REQUIRE(wp.p != nullptr && sq_colfix != nullptr, FD_ERR_INVALID_ARG,
@@ -1442,15 +1452,17 @@ SymPass launch_rowsum_sym_pass(const KVPlan& p, const PointPack& rows, const Poi
   if (rows.bf16) {
     FD_REQUIRE(rows.dc == cols.dc && sq.part == nullptr && sp.nrt * 4 * sp.nib * TILE == rows.npad, FD_ERR_INVALID_ARG,
                "internal: symmetric row-sum plan");
-    const bool unit = wp.p == nullptr;
+    const bool unit = wp.p == nullptr, two = colfix_lo != nullptr;
     if (rows.dc == 1)
-      unit ? rowsum_sym_bf16<1, true>(sp, rows, cols, wp.p, part.p, colfix, F, stream)
-           : rowsum_sym_bf16<1, false>(sp, rows, cols, wp.p, part.p, colfix, F, stream);
+      unit  ? rowsum_sym_bf16<1, true>(sp, rows, cols, wp.p, part.p, col, stream)
+      : two ? rowsum_sym_bf16<1, false, true>(sp, rows, cols, wp.p, part.p, col, stream)
+            : rowsum_sym_bf16<1, false>(sp, rows, cols, wp.p, part.p, col, stream);
     else
-      unit ? rowsum_sym_bf16<2, true>(sp, rows, cols, wp.p, part.p, colfix, F, stream)
-           : rowsum_sym_bf16<2, false>(sp, rows, cols, wp.p, part.p, colfix, F, stream);
+      unit  ? rowsum_sym_bf16<2, true>(sp, rows, cols, wp.p, part.p, col, stream)
+      : two ? rowsum_sym_bf16<2, false, true>(sp, rows, cols, wp.p, part.p, col, stream)
+            : rowsum_sym_bf16<2, false>(sp, rows, cols, wp.p, part.p, col, stream);
   } else {
-    launch_rowsum_sym_hx(sp, rows, cols, wp.p, part.p, colfix, F, sq, stream);
+    launch_rowsum_sym_hx(sp, rows, cols, wp.p, part.p, col, sq, stream);
   }
   return SymPass{int(sp.nsplit), std::ldexp(1.0, -F)};
 }
@@ -1534,8 +1546,8 @@ void launch_rowsum(const KVPlan& p, const PointPack& rows, const PointPack& cols
 
 void launch_product_column(const KVPlan& p, const PointPack& rows, const PointPack& cols, FSpan wp,
                            FSpan vscale, bool diag, const float* sl, float* Y, int64_t ldy,
-                           FSpan part, unsigned long long* colfix, const PoisonGate& poison,
-                           hipStream_t stream) {
+                           FSpan part, unsigned long long* colfix, unsigned long long* colfix_lo,
+                           const PoisonGate& poison, hipStream_t stream) {
   check_tiles(p, rows, cols);
   check_span(part, size_t(p.nsplit) * rows.npad, "partial row sums");
   check_span(vscale, VSCALE_FLOATS, "column scales");
@@ -1544,11 +1556,12 @@ void launch_product_column(const KVPlan& p, const PointPack& rows, const PointPa
     // K is symmetric: each tile off the diagonal blocks once (the whole call on
     // the 6-torus set-up, N = 65,536, D = 32: 762 -> 596 us).  Column sums are
     // fixed point against the column's largest weight, so a NaN, an infinity or
-    // a wide range (zeros among others, COLUMN_RANGE) takes the plain sums: both
+    // a wide range (zeros among others, column_range) takes the plain sums: both
     // are launched, and the column's flag closes one of them.
     PointPack r = rows, c = cols;
     r.vbad = c.vbad = vscale.p + 1;
-    sp = launch_rowsum_sym_pass(p, r, c, wp, part, colfix, stream);
+    FD_REQUIRE(colfix_lo != nullptr, FD_ERR_INVALID_ARG, "internal: column words");
+    sp = launch_rowsum_sym_pass(p, r, c, wp, part, colfix, stream, FSpan{}, nullptr, colfix_lo);
     r.serves_bad = c.serves_bad = 1;
     launch_rowsum_pass(p, r, c, wp, diag, nullptr, part.p, stream);
   } else {
@@ -1556,7 +1569,7 @@ void launch_product_column(const KVPlan& p, const PointPack& rows, const PointPa
     launch_rowsum_pass(p, rows, cols, wp, diag, nullptr, part.p, stream);
   }
   hipLaunchKernelGGL(column_finish_kernel, dim3(blocks_for(rows.npad, 256)), dim3(256), 0, stream,
-                     part.p, p.nsplit, sp.nsplit, rows.npad, colfix, sp.inv_fix, vscale.p, sl,
+                     part.p, p.nsplit, sp.nsplit, rows.npad, colfix, colfix_lo, vscale.p, sl,
                      rows.n, rows.npad, Y, ldy, poison);
   FD_LAUNCH_CHECK();
 }

@@ -131,7 +131,13 @@ static SolverWs carve_solver_ws(Arena& a, int64_t N, int64_t D, int b, int mm_ca
   w.prod.vp = a.fspan(size_t(w.prod.cols.npad) * w.prod.plan.ncb * 16);
   w.prod.vscale = a.fspan(VSCALE_FLOATS);
   w.prod.part = a.fspan(part_rows_bound(w.prod.rows.npad, N) * w.prod.plan.ncb * 16);
-  w.prod.colfix = w.deg.colfix;  // single-column products: cleared by the degree passes
+  if (b == 1) {
+    // single-column products: the degree pass's words and as many again, both
+    // cleared by its packs
+    w.deg.sq_colfix = a.take<unsigned long long>(size_t(w.deg.rows.npad));
+    w.prod.colfix = w.deg.colfix;
+    w.prod.colfix_lo = w.deg.sq_colfix;
+  }
   w.d = a.take<float>(size_t(N));
   w.s = a.take<float>(size_t(N));
   w.s_off = a.take<double>(1);

@@ -33,7 +33,8 @@ namespace {
 // fixed-point scale assumes weights in [-1, 1] (the normalisation weights
 // q^-alpha with q >= 1 are; a single right-hand side is scaled by a power of
 // two) and leaves a factor 4 of headroom below 2^63 for
-// the total.
+// the total, or (TWO) for the workgroup's own sums only, whose words
+// then go to two global words (WIDE_FRAC in fd_plans.hpp).
 
 // Column tiles whose fixed-point column sums a workgroup gathers in LDS
 // (SYM_CHUNK x 16 x 8 bytes) before adding them into global memory; even.
@@ -175,14 +176,18 @@ __device__ __forceinline__ void sym_own_tile(const typename T::Col& c, const flo
 // SQ (weighted passes only): also the row and column sums of the squared
 // kernel, K^2 1 = K(2 beta) 1 (eq. kernel), into part2 / colfix2 with the scale
 // fix_scale2 per unit of (ONE K)^2.
-template <class T, int NIB, bool UNIT, bool SQ = false>
+// TWO (weighted passes only): column sums in two words, into colfix and
+// colfix_lo (an instantiation of its own: chosen at run time, the normalisation's
+// weighted pass came out 1% slower at N = 200,003, D = 30).
+template <class T, int NIB, bool UNIT, bool SQ = false, bool TWO = false>
 __global__ __launch_bounds__(WG_THREADS)
 __attribute__((amdgpu_waves_per_eu(T::template waves<NIB, SQ>()))) void rowsum_sym_kernel(
     typename T::Args ta, const floatx4* __restrict__ wp, int64_t nblk, int64_t njb,
     int64_t jb_per_split, int64_t nsplit, float* __restrict__ part, int64_t nrpad,
-    unsigned long long* __restrict__ colfix, double fix_scale, float* __restrict__ part2,
+    unsigned long long* __restrict__ colfix, unsigned long long* __restrict__ colfix_lo,
+    double fix_scale, float* __restrict__ part2,
     unsigned long long* __restrict__ colfix2, double fix_scale2, HxGate gate) {
-  static_assert(!(SQ && UNIT), "squared sums ride on a weighted pass");
+  static_assert(!((SQ || TWO) && UNIT), "squared sums and two words are weighted passes'");
   if (hx_gate_closed(gate)) return;
   constexpr int BT = 4 * NIB;  // tiles per block
   const int lane = threadIdx.x & 63;
@@ -356,7 +361,17 @@ __attribute__((amdgpu_waves_per_eu(T::template waves<NIB, SQ>()))) void rowsum_s
         for (int e = threadIdx.x; e < SYM_CHUNK * TILE; e += WG_THREADS) {
           const unsigned long long v = lds_col[e];
           const int Jc = c0 + e / TILE < jj_end ? tile_of(c0 + e / TILE) : -1;
-          if (v != 0ull && Jc >= 0) atomicAdd(colfix + int64_t(Jc) * TILE + e % TILE, v);
+          if (v != 0ull && Jc >= 0) {
+            const int64_t j = int64_t(Jc) * TILE + e % TILE;
+            if constexpr (!TWO) {
+              atomicAdd(colfix + j, v);
+            } else {
+              // arithmetic shift: hi 2^WIDE_SPLIT + lo is the signed word
+              atomicAdd(colfix + j, static_cast<unsigned long long>(static_cast<long long>(v) >>
+                                                                    WIDE_SPLIT));
+              atomicAdd(colfix_lo + j, v & ((1ull << WIDE_SPLIT) - 1));
+            }
+          }
           lds_col[e] = 0ull;
           if constexpr (SQ) {
             const unsigned long long v2 = lds_col2[e];

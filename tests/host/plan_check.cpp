@@ -2,8 +2,10 @@
 // and undefined-behaviour sanitizers by tests/test_host_plans.py.  A mode per
 // property; the exit status is 0 when it holds, and the first failures are
 // printed.
+#include <cmath>
 #include <cstdio>
 #include <cstring>
+#include <random>
 
 #include "fd_plans.hpp"
 
@@ -58,9 +60,52 @@ static void products() {
           }
 }
 
+// The single column's sums: contributions of waves next to the smallest weight of
+// the widest column, one per 256 rows, rounded, gathered four at a time, split
+// into two words and put together again, against their exact sum; and the
+// largest contributions a workgroup gathers.
+static void columns() {
+  std::mt19937_64 rng(7);
+  const double unit = std::ldexp(1.0, WIDE_FRAC);
+  auto total = [&](int64_t count, auto value, long double& exact) {
+    uint64_t hi = 0, lo = 0;
+    exact = 0;
+    for (int64_t k = 0; k < count; k += 4) {
+      uint64_t word = 0;
+      for (int e = 0; e < 4; ++e) {
+        const float v = value();
+        exact += (long double)v;
+        word += uint64_t(std::llrint(double(v) * unit));
+      }
+      hi += uint64_t(int64_t(word) >> WIDE_SPLIT);
+      lo += word & ((uint64_t(1) << WIDE_SPLIT) - 1);
+    }
+    return (double(int64_t(hi)) * double(uint64_t(1) << WIDE_SPLIT) + double(lo)) / unit;
+  };
+  for (int e = 9; e <= 30; ++e) {
+    const int64_t npad = int64_t(1) << e, count = std::max<int64_t>(4, npad / 256);
+    const double own = 0.5 / double(column_range(npad));
+    for (double spread : {1.0, 1e-3, 1e-7}) {
+      std::uniform_real_distribution<double> u(-1.0, 1.0);
+      long double exact = 0;
+      const double got = total(count, [&] { return float(own * spread * u(rng)); }, exact);
+      const double err = std::fabs(double((long double)got - exact));
+      if (err > std::ldexp(own, -18)) fail("column sum, 2^-60", e, 0, (long long)(err * 0x1p60), (long long)(std::ldexp(own, -18) * 0x1p60));
+    }
+  }
+  // 128 rows of the largest weight, with kernel values a little above 1
+  for (float v : {128.f * 1.0001f, -128.f * 1.0001f}) {
+    long double exact = 0;
+    const double got = total(1 << 20, [&] { return v; }, exact);
+    if (std::fabs(got - double(exact)) > std::fabs(double(exact)) * 1e-15)
+      fail("largest column", 0, 0, (long long)exact, (long long)got);
+  }
+}
+
 int main(int argc, char** argv) {
   if (argc == 2 && !std::strcmp(argv[1], "prefixes")) prefixes();
   else if (argc == 2 && !std::strcmp(argv[1], "products")) products();
+  else if (argc == 2 && !std::strcmp(argv[1], "columns")) columns();
   else return 2;
   std::printf("%d failures\n", failures);
   return failures ? 1 : 0;

@@ -7,8 +7,8 @@ blocks, and 64 blocks and more, where column splits become whole blocks.
 Tolerances: the vectors of fd_degree and one float32 column to 1e-5 (the
 stated tolerance of float32 arithmetic); bfloat16 points enter exactly, so
 their sums keep that bar.  One column's sums along the columns are fixed point
-with at least 42 fractional bits against the largest weight: a column spread
-over 2^16 keeps 2^-26 of its smallest entries.
+with 53 fractional bits against the largest weight, for columns whose span
+leaves 2^-18 of the smallest weight at this size.
 """
 import numpy as np
 import pytest
@@ -115,6 +115,28 @@ def test_one_column_keeps_small_results(n, kind):
     seen = size > 1e-30
     assert seen.sum() > n // 2
     assert (np.abs(Y - ref) <= 1e-4 * size)[seen].all()
+
+
+@pytest.mark.parametrize("n, span", [(1 << 16, 26.9), (1 << 18, 23.9), (1 << 18, 24.9),
+                                     (1 << 18, 25.1), (1 << 20, 22.9), (1 << 20, 23.9)])
+def test_one_column_near_the_widest_span(n, span):
+    """Two clusters far apart, one with weights 2^span below the other's, in
+    sizes where a row's result is little more than its own weight: on both
+    sides of the span (2^43 / n) up to which column sums are fixed point.
+
+    Each result to 1e-5 of its sum: 2^-18 of it for the fixed point, and 2e-6
+    for the exponents (B = beta log2(e) max|x|^2 < 60).
+    """
+    case(f"one column n={n} span=2^{span}")
+    g = torch.Generator().manual_seed(1)
+    x = torch.randn(n, 64, generator=g) * 0.37
+    x[::2, 0] += 6.0
+    v = torch.ones(n, 1)
+    v[1::2] = 2.0 ** -span
+    Y = to_np(fd.fd_kernel_matmul(x.to(device()), None, 1.0, v.to(device())))[:, 0]
+    rows = 2 * np.linspace(0, n // 2 - 1, 12).astype(int) + 1
+    ref = ok.kernel_matmul(x[rows].double().numpy(), x.double().numpy(), 1.0, v.double().numpy())[:, 0]
+    assert (np.abs(Y[rows] - ref) <= 1e-5 * ref).all()
 
 
 def test_one_column_eigensolve_matches_a_wider_one():

@@ -1,6 +1,6 @@
 """The work splits of the products and the row sums on the CPU, under the address
 and undefined-behaviour sanitizers: the extents of their partial sums over the
-whole range of sizes."""
+whole range of sizes, and the fixed-point column sums of a single column."""
 import os
 import shutil
 import subprocess
@@ -28,4 +28,9 @@ def driver(tmp_path_factory):
 @pytest.mark.parametrize("mode", ["prefixes", "products"])
 def test_extents_of_partial_sums(driver, mode):
     res = subprocess.run([driver, mode], capture_output=True, text=True)
+    assert res.returncode == 0, res.stdout + res.stderr
+
+
+def test_single_column_sums(driver):
+    res = subprocess.run([driver, "columns"], capture_output=True, text=True)
     assert res.returncode == 0, res.stdout + res.stderr
