@@ -827,10 +827,12 @@ rowsum_bf16_kernel(
 }
 
 // Tile policy of the symmetric row sums (sym_rowsum.hpp).  fd_degree plus a
-// 64-column product at N = 131,072, D = 64 takes 10.3 ms with it and 14.0 ms
+// 64-column product at N = 131,072, D = 64 takes 10.7 ms with it and 14.1 ms
 // with the plain sums (each entry evaluated twice).  The accumulator
-// starts at the column offsets -r_j / 2, and K = 2^(scale2 u + c_i) with
-// c_i = -scale2 r_i / 2 per row (one FMA per entry), clamped to [0, 1].
+// starts at the offsets -r_i / 2 - r_j / 2, as in the plain sums (half_sqdist), and
+// K = 2^(scale2 u), clamped to [0, 1]: large offsets of near points cancel
+// before anything is scaled, so that points that coincide give K = 1 where the
+// sums are exact (scaled on its own, a row offset loses 2^-25 of 2 beta r^2).
 template <int DC>
 struct Bf16Tile {
   static constexpr float ONE = 1.f;
@@ -844,7 +846,7 @@ struct Bf16Tile {
   };
   struct Row {
     uintx4 b[DC];
-    float c;
+    float off;
   };
   struct Col {
     uintx4 a[DC];
@@ -857,7 +859,7 @@ struct Bf16Tile {
   static __device__ __forceinline__ void load_row(Row& r, const Args& a, int64_t tile, int lane) {
 #pragma unroll
     for (int c = 0; c < DC; ++c) r.b[c] = a.xb[(tile * DC + c) * 64 + lane];
-    r.c = a.scale2 * a.ar[tile * TILE + (lane & 15)];
+    r.off = a.ar[tile * TILE + (lane & 15)];
   }
   static __device__ __forceinline__ void load_col(Col& c, const Args& a, int64_t tile, int lane) {
 #pragma unroll
@@ -867,18 +869,20 @@ struct Bf16Tile {
   static __device__ __forceinline__ void consume(const Row& r) {
 #pragma unroll
     for (int c = 0; c < DC; ++c) asm volatile("" ::"v"(r.b[c]));
-    asm volatile("" ::"v"(r.c));
+    asm volatile("" ::"v"(r.off));
   }
   static __device__ __forceinline__ floatx4 tile(const Col& c, const Row& r) {
-    floatx4 t = c.off;
+    floatx4 t;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) t[e] = r.off + c.off[e];
 #pragma unroll
     for (int k = 0; k < DC; ++k)
       t = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, c.a[k]),
                                                   __builtin_bit_cast(bf16x8, r.b[k]), t, 0, 0, 0);
     return t;
   }
-  static __device__ __forceinline__ float value(float t, const Row& r, const Args& a) {
-    return exp2_unit(fmaf(t, a.scale2, r.c));
+  static __device__ __forceinline__ float value(float t, const Row&, const Args& a) {
+    return exp2_unit(t * a.scale2);
   }
 };
 

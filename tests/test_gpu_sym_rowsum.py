@@ -60,6 +60,25 @@ def test_bfloat16_normalisation_with_whole_block_splits_and_dyadic_levels():
         assert rel_fro(to_np(lev.d)[l][rows], dd) <= TOL_F32
 
 
+@pytest.mark.parametrize("n", [700, 2048])
+@pytest.mark.parametrize("beta", [37.0, 1234.5, 7.7e4])
+def test_bfloat16_points_that_coincide_far_from_the_origin(n, beta):
+    """64 places on a grid of 4 (norms up to 1e4, exact in float32) at beta |x|^2
+    far beyond any budget: a kernel value is 1 within a place, and at most
+    exp(-16 beta) = 0 in float32 between them, so that the sums are counts."""
+    case(f"coincident bf16 points n={n} beta={beta}")
+    base = 4.0 * torch.randint(-8, 9, (64, 16), generator=torch.Generator().manual_seed(3))
+    place = torch.arange(n) % 64
+    assert len(torch.unique(base, dim=0)) == 64
+    x = base[place].to(torch.bfloat16).to(device())
+    count = torch.bincount(place, minlength=64)[place].double().numpy()
+    deg = fd.fd_degree(x, beta, 0.5)
+    assert np.array_equal(to_np(deg.q), count)
+    assert rel_fro(to_np(deg.d), np.ones(n)) <= TOL_F32
+    Y = fd.fd_kernel_matmul(x, None, beta, torch.ones(n, 1, device=device()))
+    assert np.array_equal(to_np(Y)[:, 0], count)
+
+
 @pytest.mark.parametrize("n, d", SIZES + [(40001, 12)])
 @pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
 def test_one_column(n, d, dtype):
