@@ -407,6 +407,7 @@ struct PackBf16Args {
   PackBf16Side row, col;
   int64_t ldx, nbr, nbc;
   int D, dc, vec;
+  float pad;  // offset of the padding points
   const int* flags;
   int nflags;
   int* flag;
@@ -467,8 +468,7 @@ __global__ __launch_bounds__(PACK_THREADS) void pack_bf16_kernel(PackBf16Args a)
   }
   r += __shfl_xor(r, 16);
   r += __shfl_xor(r, 32);
-  // padded points: a huge negative offset makes their kernel values exactly 0
-  const float off = real ? float(-0.5 * r) : -1e30f;
+  const float off = real ? float(-0.5 * r) : a.pad;
   if (s.ar != nullptr && g == 0) s.ar[i] = off;
   if (s.ap != nullptr) {
     floatx4 q;
@@ -1167,6 +1167,11 @@ static void launch_packs_bf16(const PackIn& in, const PackV& v, PointPack& rows,
   // eight features at a time where every row starts on 16 bytes
   a.vec = in.ldx % 8 == 0 && reinterpret_cast<uintptr_t>(in.Xr) % 16 == 0 &&
           reinterpret_cast<uintptr_t>(in.Xc) % 16 == 0;
+  // padding points: an infinite offset makes their kernel values 0 at any
+  // bandwidth (a finite one, -1e30, was too near below beta = 5e-29); at
+  // beta = 0, where only products go, it is finite (0 times it is 0) and their
+  // rows of V are 0
+  a.pad = in.beta > 0.0 ? -__builtin_inff() : -1e30f;
   constexpr int TPB = PACK_THREADS / 64;
   a.nbr = ceil_div(a.row.ntiles, TPB);
   a.nbc = ceil_div(a.col.ntiles, TPB);

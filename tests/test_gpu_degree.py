@@ -144,3 +144,17 @@ def test_symmetric_row_sums_match_plain_product_and_repeat_bitwise():
         bound = 2 * 2.0**-24 * 2 * beta * np.log2(np.e) * float((w.X.astype(np.float64) ** 2).sum(1).max())
         assert rel_fro(q, k1) <= 1e-6
         assert np.abs(q / k1 - 1.0).max() <= bound * np.log(2) + 1e-6
+
+
+@pytest.mark.parametrize("n", [5, 1000, 1500, 2049])
+@pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
+def test_tiny_bandwidths_count_the_points(n, dtype):
+    """Every kernel value is 1 and padding points do not count: q = N exactly
+    (sums of ones), at bandwidths down to the smallest float32."""
+    x = torch.randn(n, 8, generator=torch.Generator().manual_seed(n)).to(dtype).to(device())
+    for beta in (1e-28, 1e-30, 1e-36, 1e-38, 1e-44):
+        case(f"tiny bandwidth n={n} {dtype} beta={beta}")
+        deg = fd.fd_degree(x, beta, 0.5)
+        assert (to_np(deg.q) == n).all()
+        assert float(to_np(deg.s_off)[0]) == n * (n - 1)
+        assert np.abs(to_np(deg.d) - 1).max() <= TOL_F32
