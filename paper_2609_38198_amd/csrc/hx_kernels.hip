@@ -675,6 +675,9 @@ __attribute__((amdgpu_waves_per_eu(2))) void product_hx_kernel(
   }
   }
 
+  // read once: between stores to Y the compiler would read the words again for
+  // every element (32% of a product of 2^20 rows and 512 columns)
+  const bool bad = part == nullptr && poisoned(poison);
 #pragma unroll
   for (int ib = 0; ib < NIB; ++ib)
 #pragma unroll
@@ -688,7 +691,7 @@ __attribute__((amdgpu_waves_per_eu(2))) void product_hx_kernel(
           part[(split * nrpad + i) * (NCB * 16) + c] = v[e];
         } else if (i < Nr && c < b) {
           const float y = v[e] * colscale[c];
-          Y[i * ldy + c] = poisoned(poison) ? __builtin_nanf("") : (sl != nullptr) ? y * sl[i] : y;
+          Y[i * ldy + c] = bad ? __builtin_nanf("") : (sl != nullptr) ? y * sl[i] : y;
         }
       }
     }
