@@ -66,7 +66,7 @@ ProductWs carve_product(Arena& a, int64_t Nr, int64_t Nc, int64_t D, int b) {
   w.rows = carve_pack(a, Nr, dp, ROW_PAD);
   w.cols = carve_pack(a, Nc, dp, COL_PAD);
   w.vp = a.fspan(size_t(w.cols.npad) * w.plan.ncb * 16);
-  w.vscale = a.fspan(VSCALE_FLOATS);
+  w.vscale = a.fspan(vscale_floats(Nc));
   w.part = a.fspan(part_rows_bound(w.rows.npad, Nc) * w.plan.ncb * 16);
   if (b == 1) {
     w.colfix = a.take<unsigned long long>(size_t(w.rows.npad));
@@ -86,7 +86,7 @@ static ProductWs carve_product_exact(Arena& a, int64_t Nr, int64_t Nc, int64_t D
   w.rows = carve_pack(a, Nr, dp, ROW_PAD);
   w.cols = carve_pack(a, Nc, dp, COL_PAD);
   w.vp = a.fspan(size_t(w.cols.npad) * w.plan.ncb * 16);
-  w.vscale = a.fspan(VSCALE_FLOATS);
+  w.vscale = a.fspan(vscale_floats(Nc));
   const KVPlan rp = plan_rowsum(Nr, Nc, dp);
   const size_t part_prod = size_t(w.plan.nsplit) * w.rows.npad * w.plan.ncb * 16;
   const size_t part_row =
@@ -213,7 +213,6 @@ static void matmul_run(ProductWs& w, const void* Xr, const void* Xc, int64_t D, 
   in.ncb = b == 1 ? 0 : w.plan.ncb;
   in.vp = w.vp;
   in.vscale = w.vscale;
-  in.nvmax = vmax_blocks(w.cols.n);
   in.zero1 = w.colfix;
   in.zero2 = w.colfix_lo;
   in.nzero = w.colfix != nullptr ? w.rows.npad : 0;

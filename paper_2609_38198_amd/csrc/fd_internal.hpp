@@ -110,12 +110,14 @@ struct PointPack {
 // flags: one word per prologue workgroup, non-zero where it met a NaN or an
 // infinity.
 struct CentreWs {
-  double* part = nullptr;               // nblk x D column partial sums
+  double* part = nullptr;               // D finished column sums, then nblk x D partial ones
+  const double* sums = nullptr;         // nsums x D sums that the consumers add (set by the prologue)
   unsigned long long* r2max = nullptr;  // float64 bits of max ||x - mean||^2
   int* flags = nullptr;                 // nblk words, then nblk2 of a second point set
   int64_t n = 0;                        // points the partial sums cover (set by the prologue)
   int nblk = 0, nblk2 = 0;              // workgroups carved for
   int used = 0, used2 = 0;              // workgroups the last prologue ran
+  int nsums = 0;
 };
 CentreWs carve_centre(Arena& a, int64_t n, int64_t n2 = 0);
 
@@ -132,8 +134,8 @@ struct PrologueIn {
   int64_t nv = 0, b = 0, ldv = 0;
   const float* sr = nullptr;
 };
-// Everything in one launch: centre.part, centre.flags, vscale's partial
-// maxima; clears centre.r2max (the packs raise it).
+// Everything in one launch (two for large sets): centre.part, centre.flags,
+// vscale's maxima; clears centre.r2max (the packs raise it).
 void launch_prologue(const PrologueIn& in, CentreWs& c, FSpan vscale, hipStream_t stream);
 // r2max over X[0:n] from the prologue's sums, without packing (a no-op for bfloat16).
 void launch_radius(const void* X, fd_dtype xt, int64_t n, int64_t D, int64_t ldx,
@@ -203,7 +205,6 @@ struct PackIn {
   const float* sr = nullptr;
   int ncb = 0;
   FSpan vp, vscale;
-  int64_t nvmax = 0;  // prologue workgroups that left column maxima
   unsigned long long *zero1 = nullptr, *zero2 = nullptr;
   int64_t nzero = 0;
 };
@@ -211,11 +212,9 @@ void launch_packs(const PackIn& in, PointPack& rows, PointPack& cols, const Cent
                   hipStream_t stream);
 void launch_pack_w(const float* w, int64_t n, int64_t npad, FSpan wp, hipStream_t stream);
 // Split float16 pack of sr * V with per-column power-of-two scales, in two
-// launches (column maxima, pack).  vscale (VSCALE_FLOATS): 64 inverse scales,
-// then VMAX_BLOCKS x 64 partial maxima.
-constexpr int VMAX_BLOCKS = 128;
-constexpr int VSCALE_FLOATS = 64 + 64 * VMAX_BLOCKS;
-int64_t vmax_blocks(int64_t n);
+// launches (column maxima, pack).  vscale (vscale_floats(n)): 64 inverse scales,
+// 64 column maxima where the prologue finishes them, then its partial maxima.
+size_t vscale_floats(int64_t n);
 void launch_pack_v_split(const float* V, int64_t n, int64_t b, int64_t ldv, const float* sr,
                          int ncb, int64_t npad, FSpan vp, FSpan vscale, hipStream_t stream);
 // Y = diag(sl) K diag(sr) V from packed operands (V packed with sr applied).

@@ -1038,7 +1038,7 @@ void launch_packs_hx(const PackIn& in, const PackV& v, PointPack& rows, PointPac
                      const CentreWs& centre, hipStream_t stream) {
   const int rid = hx_recipe_for(in.D);
   FD_REQUIRE(rid >= 0, FD_ERR_UNSUPPORTED, "feature dimension above 64");
-  FD_REQUIRE(centre.part != nullptr && centre.used > 0 && in.nzero <= rows.npad,
+  FD_REQUIRE(centre.nsums > 0 && in.nzero <= rows.npad,
              FD_ERR_INVALID_ARG, "internal: packs before the prologue");
   const int wide = hx_full_offset_recipe(rid);
   PackHxArgs a{};
@@ -1048,9 +1048,9 @@ void launch_packs_hx(const PackIn& in, const PackV& v, PointPack& rows, PointPac
   a.nbr = ceil_div(rows.npad, PACK_THREADS);
   a.nbc = ceil_div(cols.npad, PACK_THREADS);
   a.D = int(in.D);
-  a.nblk = centre.used;
+  a.nblk = centre.nsums;
   a.neg_bl = -(in.beta * LOG2E);
-  a.part = centre.part;
+  a.part = centre.sums;
   a.nmean = centre.n;
   a.r2max = centre.r2max;
   a.flags = centre.flags;

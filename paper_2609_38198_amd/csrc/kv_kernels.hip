@@ -67,16 +67,33 @@ PointPack carve_pack(Arena& a, int64_t n, int dp, int64_t pad) {
 // workgroup leaves its partial result for the consumer to add, so that nothing
 // has to be cleared beforehand.
 
-constexpr int PRO_BLOCKS = 128;     // workgroups per point set
-constexpr int PRO_MIN_ROWS = 128;   // rows a workgroup should at least have
+//
+// For a large set the bandwidth counts after all: up to 1024 workgroups, and a
+// second launch (prologue_finish_kernel) that adds their results once, where
+// every pack workgroup would add them again.  300 rows against n columns, one
+// launch of 128 workgroups / two (us): for the maxima of V, D = 12, b = 64
+// n = 65,536 100 / 74, 200,000 243 / 170, b = 16 n = 50,000 49 / 49, 65,536 58 / 56,
+// b = 1 n = 36,000 42 / 45: from 3 * 2^18 values on.  For the column sums,
+// b = 8, D = 30 n = 200,000 137 / 107, D = 64 n = 262,144 244 / 189, D = 12
+// n = 524,288 236 / 213, but D = 12 n = 65,536 74 / 85, D = 4 n = 200,000 102 / 127:
+// adding 128 partial sums first spreads the pack's waves, which otherwise all
+// raise the radius word at once: from 2^22 values on.
 
-static int prologue_blocks(int64_t n) {
+constexpr int PRO_BLOCKS = 128;     // workgroups per point set in one launch
+constexpr int PRO_MIN_ROWS = 128;   // rows a workgroup should at least have
+constexpr int64_t PRO_LARGE_N = 32768, PRO_LARGE_VALUES = int64_t(3) << 18;
+constexpr int64_t PRO_LARGE_SUMS = int64_t(1) << 22;
+constexpr int PRO_LARGE_BLOCKS = 1024, PRO_LARGE_ROWS = 256;
+
+// Workgroups over n rows of `width` values (sums: of column sums); more than
+// PRO_BLOCKS: two launches.
+static int prologue_blocks(int64_t n, int64_t width, bool sums = false) {
+  if (n > PRO_LARGE_N && n * width >= (sums ? PRO_LARGE_SUMS : PRO_LARGE_VALUES))
+    return int(std::min<int64_t>(PRO_LARGE_BLOCKS, ceil_div(n, PRO_LARGE_ROWS)));
   return int(std::min<int64_t>(PRO_BLOCKS, std::max<int64_t>(1, ceil_div(n, PRO_MIN_ROWS))));
 }
 
-int64_t vmax_blocks(int64_t n) {
-  return std::min<int64_t>(VMAX_BLOCKS, std::max<int64_t>(1, ceil_div(n, PRO_MIN_ROWS)));
-}
+size_t vscale_floats(int64_t n) { return 128 + 64 * size_t(prologue_blocks(n, MAX_B)); }
 
 __device__ __forceinline__ bool x_load(const float* X, int64_t e, float& v) {
   v = X[e];
@@ -188,6 +205,49 @@ __device__ __forceinline__ void prologue_vmax(const PrologueArgs& a, int blk, fl
   if (int(threadIdx.x) < a.b) a.vpart[blk * 64 + threadIdx.x] = red[threadIdx.x];
 }
 
+// The partial results of a large set's prologue added (float64 sums) or compared
+// (maxima; with b = 1 the column's flag and its smallest value too) over its
+// workgroups, eight columns per workgroup: [0, ceil(D / 8)) of X, then of V.
+__global__ __launch_bounds__(256) void prologue_finish_kernel(
+    const double* __restrict__ part, int nblk, int D, int nxb, double* __restrict__ sums,
+    const float* __restrict__ vpart, int nblkv, int b, float* __restrict__ vmax) {
+  __shared__ double red[256];
+  const bool points = int(blockIdx.x) < nxb;
+  const int c = 8 * (int(blockIdx.x) - (points ? 0 : nxb)) + int(threadIdx.x) % 8;
+  const int rl = int(threadIdx.x) / 8;
+  const bool least = !points && b == 1 && c == 2;
+  double r = least ? double(__builtin_inff()) : 0.0;
+  if (points) {
+    if (c < D) {
+#pragma unroll 8
+      for (int k = rl; k < nblk; k += 32) r += part[int64_t(k) * D + c];
+    }
+  } else if (c < (b == 1 ? 3 : b)) {
+#pragma unroll 8
+    for (int k = rl; k < nblkv; k += 32) {
+      const double v = double(vpart[k * 64 + c]);
+      r = least ? fmin(r, v) : fmax(r, v);
+    }
+  }
+  red[threadIdx.x] = r;
+  __syncthreads();
+  for (int w = 128; w >= 8; w >>= 1) {
+    if (int(threadIdx.x) < w) {
+      const double o = red[threadIdx.x + w];
+      red[threadIdx.x] = points ? red[threadIdx.x] + o
+                         : least ? fmin(red[threadIdx.x], o)
+                                 : fmax(red[threadIdx.x], o);
+    }
+    __syncthreads();
+  }
+  if (threadIdx.x >= 8) return;
+  if (points) {
+    if (c < D) sums[c] = red[threadIdx.x];
+  } else if (c < (b == 1 ? 3 : b)) {
+    vmax[c] = float(red[threadIdx.x]);
+  }
+}
+
 // Workgroups [0, nblk): X; [nblk, nblk + nblk2): X2; the rest: V.
 template <typename T>
 __global__ __launch_bounds__(256) void prologue_kernel(PrologueArgs a) {
@@ -210,9 +270,9 @@ __global__ __launch_bounds__(256) void prologue_kernel(PrologueArgs a) {
 
 CentreWs carve_centre(Arena& a, int64_t n, int64_t n2) {
   CentreWs c;
-  c.nblk = prologue_blocks(n);
-  c.nblk2 = n2 > 0 ? prologue_blocks(n2) : 0;
-  c.part = a.take<double>(size_t(c.nblk) * MAX_D);
+  c.nblk = prologue_blocks(n, MAX_D);
+  c.nblk2 = n2 > 0 ? prologue_blocks(n2, MAX_D) : 0;
+  c.part = a.take<double>((size_t(c.nblk) + 1) * MAX_D);
   c.r2max = a.take<unsigned long long>(1);
   c.flags = a.take<int>(size_t(c.nblk) + size_t(c.nblk2));
   return c;
@@ -226,24 +286,24 @@ void launch_prologue(const PrologueIn& in, CentreWs& c, FSpan vscale, hipStream_
   a.n2 = in.n2;
   a.ldx = in.ldx;
   a.D = int(in.D);
-  a.nblk = in.X != nullptr ? prologue_blocks(in.n) : 0;
-  a.nblk2 = in.X2 != nullptr ? prologue_blocks(in.n2) : 0;
+  a.nblk = in.X != nullptr ? prologue_blocks(in.n, in.D, in.xt == FD_F32) : 0;
+  a.nblk2 = in.X2 != nullptr ? prologue_blocks(in.n2, in.D) : 0;
   FD_REQUIRE(a.nblk <= c.nblk && a.nblk2 <= c.nblk2 && in.D <= MAX_D && in.b <= MAX_B,
              FD_ERR_INVALID_ARG, "internal: prologue workspace");
   a.tcx = a.nblk > 0 ? column_lanes(in.D) : 1;
-  a.part = in.xt == FD_F32 ? c.part : nullptr;
+  a.part = in.xt == FD_F32 && a.nblk > 0 ? c.part + MAX_D : nullptr;
   a.r2max = a.nblk > 0 ? c.r2max : nullptr;
   a.flags = c.flags;
   if (in.V != nullptr) {
-    check_span(vscale, VSCALE_FLOATS, "column scales");
+    check_span(vscale, vscale_floats(in.nv), "column scales");
     a.V = in.V;
     a.sr = in.sr;
     a.nv = in.nv;
     a.ldv = in.ldv;
     a.b = int(in.b);
     a.tcv = column_lanes(in.b);
-    a.nblkv = int(vmax_blocks(in.nv));
-    a.vpart = vscale.p + 64;
+    a.nblkv = prologue_blocks(in.nv, in.b);
+    a.vpart = vscale.p + 128;
   }
   c.n = in.n;
   c.used = a.nblk;
@@ -254,6 +314,18 @@ void launch_prologue(const PrologueIn& in, CentreWs& c, FSpan vscale, hipStream_
   else
     hipLaunchKernelGGL(prologue_kernel<float>, grid, dim3(256), 0, stream, a);
   FD_LAUNCH_CHECK();
+  c.sums = a.part;
+  c.nsums = a.nblk;
+  const int nxb = a.part != nullptr && a.nblk > PRO_BLOCKS ? int(ceil_div(in.D, 8)) : 0;
+  const int nvb = a.nblkv > PRO_BLOCKS ? int(ceil_div(in.b == 1 ? 3 : in.b, 8)) : 0;
+  if (nxb + nvb == 0) return;
+  hipLaunchKernelGGL(prologue_finish_kernel, dim3(unsigned(nxb + nvb)), dim3(256), 0, stream,
+                     a.part, a.nblk, a.D, nxb, c.part, a.vpart, a.nblkv, a.b, vscale.p + 64);
+  FD_LAUNCH_CHECK();
+  if (nxb > 0) {
+    c.sums = c.part;
+    c.nsums = 1;
+  }
 }
 
 // r2max = max_i ||x_i - mu||^2 over X[0:n] (raise_r2max).
@@ -279,10 +351,10 @@ __global__ __launch_bounds__(256) void radius_max_kernel(const float* __restrict
 void launch_radius(const void* X, fd_dtype xt, int64_t n, int64_t D, int64_t ldx,
                    const CentreWs& c, hipStream_t stream) {
   if (xt != FD_F32) return;
-  FD_REQUIRE(c.n == n && c.used > 0, FD_ERR_INVALID_ARG, "internal: radius before the prologue");
+  FD_REQUIRE(c.n == n && c.nsums > 0, FD_ERR_INVALID_ARG, "internal: radius before the prologue");
   const unsigned grid = unsigned(std::min<int64_t>(1024, std::max<int64_t>(1, ceil_div(n, 256))));
   hipLaunchKernelGGL(radius_max_kernel, dim3(grid), dim3(256), 0, stream,
-                     static_cast<const float*>(X), n, int(D), ldx, c.part, c.used, c.r2max);
+                     static_cast<const float*>(X), n, int(D), ldx, c.sums, c.nsums, c.r2max);
   FD_LAUNCH_CHECK();
 }
 
@@ -1193,9 +1265,16 @@ static void launch_packs_bf16(const PackIn& in, const PackV& v, PointPack& rows,
 // The V part of a pack: the split pack of V[0:n, 0:b] (ncb > 0) or the weight
 // pack of its one column (ncb = 0) for a column side of npad points.
 static PackV pack_v_args(const float* V, int64_t n, int64_t b, int64_t ldv, const float* sr,
-                         int ncb, int64_t npad, FSpan vp, FSpan vscale, int64_t nvmax) {
+                         int ncb, int64_t npad, FSpan vp, FSpan vscale) {
   PackV v;
   if (V == nullptr) return v;
+  check_span(vscale, vscale_floats(n), "column scales");
+  v.colscale = vscale.p;
+  // the finished maxima, or the prologue's partial ones
+  const int nblk = prologue_blocks(n, b);
+  const bool finished = nblk > PRO_BLOCKS;
+  v.nvmax = finished ? 1 : nblk;
+  v.vpart = vscale.p + (finished ? 64 : 128);
   v.V = V;
   v.sr = sr;
   v.n = n;
@@ -1208,25 +1287,13 @@ static PackV pack_v_args(const float* V, int64_t n, int64_t b, int64_t ldv, cons
     v.ntiles = npad / TILE;
     check_span(vp, lane4_extent(v.ntiles, 1), "weight pack");
     v.wp = reinterpret_cast<floatx4*>(vp.p);
-    if (nvmax > 0) {
-      check_span(vscale, VSCALE_FLOATS, "column scales");
-      v.nvmax = int(nvmax);
-      v.range = column_range(round_up(n, ROW_PAD));
-      v.colscale = vscale.p;
-      v.vpart = vscale.p + 64;
-    }
+    v.range = column_range(round_up(n, ROW_PAD));
     return v;
   }
-  FD_REQUIRE(npad % (2 * TILE) == 0 && npad >= n && b <= ncb * 16 && b <= 64 &&
-                 nvmax <= VMAX_BLOCKS,
-             FD_ERR_INVALID_ARG, "internal: bad split V pack geometry");
+  FD_REQUIRE(npad % (2 * TILE) == 0 && npad >= n && b <= ncb * 16 && b <= 64, FD_ERR_INVALID_ARG, "internal: bad split V pack geometry");
   v.npairs = npad / (2 * TILE);
   // one VSplit (32 bytes = 8 floats) per lane per pair per column block
   check_span(vp, size_t(v.npairs) * ncb * 64 * 8, "split V pack");
-  check_span(vscale, VSCALE_FLOATS, "column scales");
-  v.nvmax = int(nvmax);
-  v.colscale = vscale.p;
-  v.vpart = vscale.p + 64;
   v.vp = reinterpret_cast<VSplit*>(vp.p);
   return v;
 }
@@ -1235,7 +1302,7 @@ void launch_packs(const PackIn& in, PointPack& rows, PointPack& cols, const Cent
                   hipStream_t stream) {
   rows.beta = cols.beta = in.beta;
   const PackV v = pack_v_args(in.V, cols.n, in.b, in.ldv, in.sr, in.ncb, cols.npad, in.vp,
-                              in.vscale, in.nvmax);
+                              in.vscale);
   if (in.xt == FD_BF16) {
     launch_packs_bf16(in, v, rows, cols, centre, stream);
     return;
@@ -1287,7 +1354,7 @@ void launch_pack_v_split(const float* V, int64_t n, int64_t b, int64_t ldv, cons
     CentreWs none;
     launch_prologue(in, none, vscale, stream);
   }
-  const PackV v = pack_v_args(V, n, b, ldv, sr, ncb, npad, vp, vscale, vmax_blocks(n));
+  const PackV v = pack_v_args(V, n, b, ldv, sr, ncb, npad, vp, vscale);
   hipLaunchKernelGGL(pack_v_kernel, dim3(blocks_for(pack_v_items(v), PACK_THREADS)),
                      dim3(PACK_THREADS), 0, stream, v);
   FD_LAUNCH_CHECK();
@@ -1348,7 +1415,7 @@ void launch_product(const KVPlan& p, const PointPack& rows, const PointPack& col
              FD_ERR_INVALID_ARG, "internal: block width does not match the plan");
   FD_REQUIRE(p.jb_per_split % 2 == 0 && round_up(p.njb, 2) * TILE <= cols.npad,
              FD_ERR_INVALID_ARG, "internal: column pairs do not fit the pack");
-  check_span(vscale, VSCALE_FLOATS, "column scales");
+  check_span(vscale, 64, "column scales");
   const float* cs = vscale.p;
   float* pp = nullptr;
   if (p.nsplit > 1) {
@@ -1562,7 +1629,7 @@ void launch_product_column(const KVPlan& p, const PointPack& rows, const PointPa
                            const PoisonGate& poison, hipStream_t stream) {
   check_tiles(p, rows, cols);
   check_span(part, size_t(p.nsplit) * rows.npad, "partial row sums");
-  check_span(vscale, VSCALE_FLOATS, "column scales");
+  check_span(vscale, 64, "column scales");
   SymPass sp;
   if (rowsum_sym_applies(rows, cols, diag, colfix)) {
     // K is symmetric: each tile off the diagonal blocks once (the whole call on

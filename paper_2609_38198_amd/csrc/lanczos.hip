@@ -129,7 +129,7 @@ static SolverWs carve_solver_ws(Arena& a, int64_t N, int64_t D, int b, int mm_ca
   w.prod.rows = w.deg.rows;
   w.prod.cols = w.deg.cols;
   w.prod.vp = a.fspan(size_t(w.prod.cols.npad) * w.prod.plan.ncb * 16);
-  w.prod.vscale = a.fspan(VSCALE_FLOATS);
+  w.prod.vscale = a.fspan(vscale_floats(N));
   w.prod.part = a.fspan(part_rows_bound(w.prod.rows.npad, N) * w.prod.plan.ncb * 16);
   if (b == 1) {
     // single-column products: the degree pass's words and as many again, both
