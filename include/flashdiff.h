@@ -156,10 +156,13 @@ fd_status fd_kernel_matmul(const void* Xr, int64_t Nr, const void* Xc, int64_t N
 /* Allocation-free variant of fd_kernel_matmul, for callers that cannot
  * allocate device memory (code under HIP graph capture, tight serving loops,
  * harnesses that forbid hipMalloc).  Same arguments and result as
- * fd_kernel_matmul (the same kernels, bit for bit), without the workspace: the
+ * fd_kernel_matmul (the same kernels, bit for bit, while all their temporaries
+ * fit), without the workspace: the
  * temporaries live in a scratch array built into the library,
  * fd_kernel_matmul_noalloc_limit() bytes (256 MiB) per device, which each
- * device holds from the library's load until the process ends.  A problem
+ * device holds from the library's load until the process ends.  A problem next
+ * to the limit takes kernels with smaller temporaries (b = 1 on one point set:
+ * within 12% of the largest size; others: within 1%), equal to rounding.  One
  * whose temporaries do not fit returns FD_ERR_WORKSPACE (for example, b = 16
  * fits up to about 2^18 points with D <= 12).  The call allocates nothing.
  * Every call on one device shares that device's scratch, and a call only

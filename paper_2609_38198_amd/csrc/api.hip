@@ -78,27 +78,55 @@ ProductWs carve_product(Arena& a, int64_t Nr, int64_t Nc, int64_t D, int b) {
 }
 
 // The same regions sized for exactly the plan the call will run (the bound
-// above covers every plan up to the given sizes).
-static ProductWs carve_product_exact(Arena& a, int64_t Nr, int64_t Nc, int64_t D, int b) {
+// above covers every plan up to the given sizes).  sym: a single column takes the
+// symmetric row sums; cap: prologue workgroups.
+static ProductWs carve_product_exact(Arena& a, int64_t Nr, int64_t Nc, int64_t D, int b, bool sym,
+                                     int cap) {
   ProductWs w;
   const int dp = padded_dim(D);
+  w.cap = cap;
   w.plan = plan_product(Nr, Nc, dp, b);
   w.rows = carve_pack(a, Nr, dp, ROW_PAD);
   w.cols = carve_pack(a, Nc, dp, COL_PAD);
   w.vp = a.fspan(size_t(w.cols.npad) * w.plan.ncb * 16);
-  w.vscale = a.fspan(vscale_floats(Nc));
+  w.vscale = a.fspan(vscale_floats(Nc, cap));
   const KVPlan rp = plan_rowsum(Nr, Nc, dp);
   const size_t part_prod = size_t(w.plan.nsplit) * w.rows.npad * w.plan.ncb * 16;
-  const size_t part_row =
-      std::max(size_t(rp.nsplit) * w.rows.npad, sym_part_rows(w.rows.npad, SYM_NIB));
-  w.part = a.fspan(b == 1 ? part_row : part_prod);
-  if (b == 1) {
+  size_t part_row = size_t(rp.nsplit) * w.rows.npad;
+  if (sym) {
+    part_row = std::max(part_row, sym_part_rows(w.rows.npad, SYM_NIB));
     w.colfix = a.take<unsigned long long>(size_t(w.rows.npad));
     w.colfix_lo = a.take<unsigned long long>(size_t(w.rows.npad));
   }
+  w.part = a.fspan(b == 1 ? part_row : part_prod);
   w.flag = a.take<int>(1);
-  w.centre = carve_centre(a, Nc, Nr);
+  w.centre = carve_centre(a, Nc, Nr, cap);
   return w;
+}
+
+// The fullest variant of those whose regions fit `bytes` of scratch, or else
+// the smallest one: a problem near the limit gives up the symmetric row sums of
+// a single column first (its words and partial sums are up to half of the
+// total; the plain ones take 1.5 times as long), then prologue workgroups.
+struct ExactVariant {
+  bool sym = false;
+  int cap = PROLOGUE_CAP;
+  size_t bytes = 0;
+};
+static ExactVariant pick_product_exact(int64_t Nr, int64_t Nc, int64_t D, int b, bool one_set,
+                                       size_t bytes) {
+  ExactVariant v;
+  for (int sym = b == 1 && one_set && Nr == Nc; sym >= 0; --sym)
+    for (int cap : {PROLOGUE_CAP, 128, 32, 8}) {
+      Arena m;
+      m.measuring = true;
+      carve_product_exact(m, Nr, Nc, D, b, sym != 0, cap);
+      v.sym = sym != 0;
+      v.cap = cap;
+      v.bytes = m.used;
+      if (m.used <= bytes) return v;
+    }
+  return v;
 }
 
 // Scratch of the allocation-free product: one array per device, held until
@@ -197,6 +225,7 @@ static void matmul_run(ProductWs& w, const void* Xr, const void* Xc, int64_t D, 
   pro.b = b;
   pro.ldv = ldv;
   pro.sr = sr;
+  pro.cap = w.cap;
   launch_prologue(pro, w.centre, w.vscale, st);
   PackIn in;
   in.Xr = Xr;
@@ -213,6 +242,7 @@ static void matmul_run(ProductWs& w, const void* Xr, const void* Xc, int64_t D, 
   in.ncb = b == 1 ? 0 : w.plan.ncb;
   in.vp = w.vp;
   in.vscale = w.vscale;
+  in.cap = w.cap;
   in.zero1 = w.colfix;
   in.zero2 = w.colfix_lo;
   in.nzero = w.colfix != nullptr ? w.rows.npad : 0;
@@ -471,17 +501,15 @@ fd_status fd_kernel_matmul_noalloc(const void* Xr, int64_t Nr, const void* Xc, i
     FD_REQUIRE(V != nullptr && Y != nullptr, FD_ERR_INVALID_ARG, "V and Y must not be NULL");
     FD_REQUIRE(b >= 1 && b <= MAX_B, FD_ERR_INVALID_ARG, "b must be in [1, 64]");
     FD_REQUIRE(ldv >= b && ldy >= b, FD_ERR_INVALID_ARG, "ldv and ldy must be >= b");
-    Arena m;
-    m.measuring = true;
-    carve_product_exact(m, Nr, Nc, D, int(b));
-    FD_REQUIRE(m.used <= SCRATCH_BYTES, FD_ERR_WORKSPACE,
-               "problem too large for the built-in scratch: needs " + std::to_string(m.used) +
+    const ExactVariant v = pick_product_exact(Nr, Nc, D, int(b), Xr == Xc, SCRATCH_BYTES);
+    FD_REQUIRE(v.bytes <= SCRATCH_BYTES, FD_ERR_WORKSPACE,
+               "problem too large for the built-in scratch: needs " + std::to_string(v.bytes) +
                    " bytes, the scratch holds " + std::to_string(SCRATCH_BYTES) +
                    " (use fd_kernel_matmul with a workspace)");
     Arena a;
     a.base = scratch_on_current_device();
     a.cap = SCRATCH_BYTES;
-    ProductWs w = carve_product_exact(a, Nr, Nc, D, int(b));
+    ProductWs w = carve_product_exact(a, Nr, Nc, D, int(b), v.sym, v.cap);
     hipStream_t st = static_cast<hipStream_t>(stream);
     matmul_run(w, Xr, Xc, D, ldx, xt, beta, sl, sr, V, int(b), ldv, Y, ldy, st);
   });

@@ -109,6 +109,7 @@ struct PointPack {
 // the same order) and the largest squared distance of a point from the mean.
 // flags: one word per prologue workgroup, non-zero where it met a NaN or an
 // infinity.
+constexpr int PROLOGUE_CAP = 1024;  // prologue workgroups per set at most
 struct CentreWs {
   double* part = nullptr;               // D finished column sums, then nblk x D partial ones
   const double* sums = nullptr;         // nsums x D sums that the consumers add (set by the prologue)
@@ -119,7 +120,7 @@ struct CentreWs {
   int used = 0, used2 = 0;              // workgroups the last prologue ran
   int nsums = 0;
 };
-CentreWs carve_centre(Arena& a, int64_t n, int64_t n2 = 0);
+CentreWs carve_centre(Arena& a, int64_t n, int64_t n2 = 0, int cap = PROLOGUE_CAP);
 
 // What one call reads before its kernel passes: the points X (column sums and
 // finiteness), a second point set X2 (finiteness), and a block V (column
@@ -133,6 +134,7 @@ struct PrologueIn {
   const float* V = nullptr;
   int64_t nv = 0, b = 0, ldv = 0;
   const float* sr = nullptr;
+  int cap = PROLOGUE_CAP;  // what the regions were carved for
 };
 // Everything in one launch (two for large sets): centre.part, centre.flags,
 // vscale's maxima; clears centre.r2max (the packs raise it).
@@ -205,6 +207,7 @@ struct PackIn {
   const float* sr = nullptr;
   int ncb = 0;
   FSpan vp, vscale;
+  int cap = PROLOGUE_CAP;  // the prologue's
   unsigned long long *zero1 = nullptr, *zero2 = nullptr;
   int64_t nzero = 0;
 };
@@ -214,7 +217,7 @@ void launch_pack_w(const float* w, int64_t n, int64_t npad, FSpan wp, hipStream_
 // Split float16 pack of sr * V with per-column power-of-two scales, in two
 // launches (column maxima, pack).  vscale (vscale_floats(n)): 64 inverse scales,
 // 64 column maxima where the prologue finishes them, then its partial maxima.
-size_t vscale_floats(int64_t n);
+size_t vscale_floats(int64_t n, int cap = PROLOGUE_CAP);
 void launch_pack_v_split(const float* V, int64_t n, int64_t b, int64_t ldv, const float* sr,
                          int ncb, int64_t npad, FSpan vp, FSpan vscale, hipStream_t stream);
 // Y = diag(sl) K diag(sr) V from packed operands (V packed with sr applied).

@@ -12,6 +12,7 @@ struct ProductWs {
   unsigned long long *colfix = nullptr, *colfix_lo = nullptr;  // single columns: npad column-sum words each
   int* flag = nullptr;  // set when a point set holds a non-finite value
   CentreWs centre;      // common centre of the row and column sets
+  int cap = PROLOGUE_CAP;  // prologue workgroups carved for
   KVPlan plan;
 };
 

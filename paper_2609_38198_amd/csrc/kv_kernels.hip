@@ -83,17 +83,18 @@ constexpr int PRO_BLOCKS = 128;     // workgroups per point set in one launch
 constexpr int PRO_MIN_ROWS = 128;   // rows a workgroup should at least have
 constexpr int64_t PRO_LARGE_N = 32768, PRO_LARGE_VALUES = int64_t(3) << 18;
 constexpr int64_t PRO_LARGE_SUMS = int64_t(1) << 22;
-constexpr int PRO_LARGE_BLOCKS = 1024, PRO_LARGE_ROWS = 256;
+constexpr int PRO_LARGE_ROWS = 256;
 
-// Workgroups over n rows of `width` values (sums: of column sums); more than
-// PRO_BLOCKS: two launches.
-static int prologue_blocks(int64_t n, int64_t width, bool sums = false) {
+// Workgroups over n rows of `width` values (sums: of column sums), at most `cap`;
+// more than PRO_BLOCKS: two launches.
+static int prologue_blocks(int64_t n, int64_t width, int cap, bool sums = false) {
   if (n > PRO_LARGE_N && n * width >= (sums ? PRO_LARGE_SUMS : PRO_LARGE_VALUES))
-    return int(std::min<int64_t>(PRO_LARGE_BLOCKS, ceil_div(n, PRO_LARGE_ROWS)));
-  return int(std::min<int64_t>(PRO_BLOCKS, std::max<int64_t>(1, ceil_div(n, PRO_MIN_ROWS))));
+    return int(std::min<int64_t>(cap, ceil_div(n, PRO_LARGE_ROWS)));
+  return int(std::min<int64_t>(std::min(cap, PRO_BLOCKS),
+                               std::max<int64_t>(1, ceil_div(n, PRO_MIN_ROWS))));
 }
 
-size_t vscale_floats(int64_t n) { return 128 + 64 * size_t(prologue_blocks(n, MAX_B)); }
+size_t vscale_floats(int64_t n, int cap) { return 128 + 64 * size_t(prologue_blocks(n, MAX_B, cap)); }
 
 __device__ __forceinline__ bool x_load(const float* X, int64_t e, float& v) {
   v = X[e];
@@ -268,10 +269,10 @@ __global__ __launch_bounds__(256) void prologue_kernel(PrologueArgs a) {
   prologue_vmax(a, blk - a.nblk2, reinterpret_cast<float*>(red));
 }
 
-CentreWs carve_centre(Arena& a, int64_t n, int64_t n2) {
+CentreWs carve_centre(Arena& a, int64_t n, int64_t n2, int cap) {
   CentreWs c;
-  c.nblk = prologue_blocks(n, MAX_D);
-  c.nblk2 = n2 > 0 ? prologue_blocks(n2, MAX_D) : 0;
+  c.nblk = prologue_blocks(n, MAX_D, cap);
+  c.nblk2 = n2 > 0 ? prologue_blocks(n2, MAX_D, cap) : 0;
   c.part = a.take<double>((size_t(c.nblk) + 1) * MAX_D);
   c.r2max = a.take<unsigned long long>(1);
   c.flags = a.take<int>(size_t(c.nblk) + size_t(c.nblk2));
@@ -286,8 +287,8 @@ void launch_prologue(const PrologueIn& in, CentreWs& c, FSpan vscale, hipStream_
   a.n2 = in.n2;
   a.ldx = in.ldx;
   a.D = int(in.D);
-  a.nblk = in.X != nullptr ? prologue_blocks(in.n, in.D, in.xt == FD_F32) : 0;
-  a.nblk2 = in.X2 != nullptr ? prologue_blocks(in.n2, in.D) : 0;
+  a.nblk = in.X != nullptr ? prologue_blocks(in.n, in.D, in.cap, in.xt == FD_F32) : 0;
+  a.nblk2 = in.X2 != nullptr ? prologue_blocks(in.n2, in.D, in.cap) : 0;
   FD_REQUIRE(a.nblk <= c.nblk && a.nblk2 <= c.nblk2 && in.D <= MAX_D && in.b <= MAX_B,
              FD_ERR_INVALID_ARG, "internal: prologue workspace");
   a.tcx = a.nblk > 0 ? column_lanes(in.D) : 1;
@@ -295,14 +296,14 @@ void launch_prologue(const PrologueIn& in, CentreWs& c, FSpan vscale, hipStream_
   a.r2max = a.nblk > 0 ? c.r2max : nullptr;
   a.flags = c.flags;
   if (in.V != nullptr) {
-    check_span(vscale, vscale_floats(in.nv), "column scales");
+    check_span(vscale, vscale_floats(in.nv, in.cap), "column scales");
     a.V = in.V;
     a.sr = in.sr;
     a.nv = in.nv;
     a.ldv = in.ldv;
     a.b = int(in.b);
     a.tcv = column_lanes(in.b);
-    a.nblkv = prologue_blocks(in.nv, in.b);
+    a.nblkv = prologue_blocks(in.nv, in.b, in.cap);
     a.vpart = vscale.p + 128;
   }
   c.n = in.n;
@@ -1265,13 +1266,14 @@ static void launch_packs_bf16(const PackIn& in, const PackV& v, PointPack& rows,
 // The V part of a pack: the split pack of V[0:n, 0:b] (ncb > 0) or the weight
 // pack of its one column (ncb = 0) for a column side of npad points.
 static PackV pack_v_args(const float* V, int64_t n, int64_t b, int64_t ldv, const float* sr,
-                         int ncb, int64_t npad, FSpan vp, FSpan vscale) {
+                         int ncb, int64_t npad, FSpan vp, FSpan vscale,
+                         int cap = PROLOGUE_CAP) {
   PackV v;
   if (V == nullptr) return v;
-  check_span(vscale, vscale_floats(n), "column scales");
+  check_span(vscale, vscale_floats(n, cap), "column scales");
   v.colscale = vscale.p;
   // the finished maxima, or the prologue's partial ones
-  const int nblk = prologue_blocks(n, b);
+  const int nblk = prologue_blocks(n, b, cap);
   const bool finished = nblk > PRO_BLOCKS;
   v.nvmax = finished ? 1 : nblk;
   v.vpart = vscale.p + (finished ? 64 : 128);
@@ -1302,7 +1304,7 @@ void launch_packs(const PackIn& in, PointPack& rows, PointPack& cols, const Cent
                   hipStream_t stream) {
   rows.beta = cols.beta = in.beta;
   const PackV v = pack_v_args(in.V, cols.n, in.b, in.ldv, in.sr, in.ncb, cols.npad, in.vp,
-                              in.vscale);
+                              in.vscale, in.cap);
   if (in.xt == FD_BF16) {
     launch_packs_bf16(in, v, rows, cols, centre, stream);
     return;
@@ -1636,7 +1638,8 @@ void launch_product_column(const KVPlan& p, const PointPack& rows, const PointPa
     // the 6-torus set-up, N = 65,536, D = 32: 762 -> 596 us).  Column sums are
     // fixed point against the column's largest weight, so a NaN, an infinity or
     // a wide range (zeros among others, column_range) takes the plain sums: both
-    // are launched, and the column's flag closes one of them.
+    // are launched, and the column's flag closes one of them.  (No colfix: a
+    // caller without room for the words takes the plain sums.)
     PointPack r = rows, c = cols;
     r.vbad = c.vbad = vscale.p + 1;
     FD_REQUIRE(colfix_lo != nullptr, FD_ERR_INVALID_ARG, "internal: column words");

@@ -140,3 +140,35 @@ def test_flow_workspace_and_validation_without_gpu():
     bad = fd.flow_default_opts(max_probes=0)
     assert lib.fd_beta_flow(*args(16, bad)) == 1
     assert lib.fd_beta_flow(*args(16, o)) == 3  # no workspace
+
+
+# (rows, columns, D, b, one point set) that the allocation-free product takes at
+# its limit: every one of them stays accepted.
+NOALLOC_SIZES = [
+    (713632, 713632, 4, 1, True), (540928, 540928, 12, 1, True), (270336, 270336, 32, 1, True),
+    (177792, 177792, 64, 1, True), (1915904, 1000, 4, 1, False), (1314304, 1000, 12, 1, False),
+    (577024, 1000, 32, 1, False), (1008640, 504320, 4, 1, True), (100000, 422848, 30, 1, False),
+    (1, 1357984, 4, 16, False), (1000, 1015136, 12, 16, False), (1, 344448, 64, 2, False),
+    (1000, 260256, 64, 64, False), (100000, 209120, 12, 64, False), (320000, 1000, 62, 32, False),
+    (189440, 189440, 30, 17, True),
+]
+
+
+@pytest.mark.parametrize("nr, nc, d, b, one_set", NOALLOC_SIZES)
+def test_noalloc_accepts_what_fits(nr, nc, d, b, one_set):
+    """The scratch check comes before anything touches the GPU: without one an
+    accepted size ends in FD_ERR_HIP, a refused one in FD_ERR_WORKSPACE."""
+    import torch
+
+    if torch.cuda.is_available():
+        pytest.skip("the pointers are not device memory")
+    lib = fd.load()
+    c = ctypes.c_void_p
+    p = 1 << 20
+
+    def status(nr):
+        return lib.fd_kernel_matmul_noalloc(c(p), nr, c(p if one_set else 2 * p), nc, d, d, 0, 1.0,
+                                            None, None, c(p), b, b, c(p), b, None)
+
+    assert status(nr) == 4, lib.fd_last_error()
+    assert status(1 << 28) == 3

@@ -96,3 +96,32 @@ def test_too_large_is_refused_before_any_work():
     with pytest.raises(fd.FdError) as e:
         fd.fd_kernel_matmul_noalloc(X, None, 1.0, V, Y)
     assert e.value.status == 3  # FD_ERR_WORKSPACE
+
+
+@pytest.mark.parametrize("nr, nc, d, b, dtype", [
+    (640000, 640000, 4, 1, torch.float32),    # single column, symmetric sums
+    (713632, 713632, 4, 1, torch.float32),    # plain sums: no room for the others
+    (177792, 177792, 64, 1, torch.bfloat16),
+    (1915904, 1000, 4, 1, torch.float32),
+    (1, 1357984, 4, 16, torch.float32),       # few prologue workgroups
+    (1000, 260256, 64, 64, torch.float32)])
+def test_sizes_next_to_the_limit(nr, nc, d, b, dtype):
+    case(f"no-alloc next to the limit nr={nr} nc={nc} d={d} b={b} {dtype}")
+    dev = device()
+    g = torch.Generator().manual_seed(nr)
+    x = (torch.randn(nc, d, generator=g) * 0.3).to(dtype)
+    xr = x if nr == nc else (torch.randn(nr, d, generator=g) * 0.3).to(dtype)
+    V = torch.rand(nc, b, generator=g) + 0.5
+    beta = float(np.float32(1.0 / d))
+    rows = np.unique(np.linspace(0, nr - 1, 12).astype(int))
+    X = x.to(dev)
+    R = X if nr == nc else xr.to(dev)
+    Y = torch.empty(nr, b, device=dev)
+    fd.fd_kernel_matmul_noalloc(R, X, beta, V.to(dev), Y)
+    ref = ok.kernel_matmul(xr[rows].double().numpy(), x.double().numpy(), beta, V.double().numpy())
+    tol = TOL_BF16 if dtype == torch.bfloat16 and b > 1 else TOL_F32
+    assert rel_fro(to_np(Y)[rows], ref) <= tol
+    assert rel_fro(to_np(Y), to_np(fd.fd_kernel_matmul(R, X, beta, V.to(dev)))) <= TOL_F32
+    X[nc - 1, d - 1] = float("nan")
+    fd.fd_kernel_matmul_noalloc(R, X, beta, V.to(dev), Y)
+    assert torch.isnan(Y).all()
