@@ -359,7 +359,7 @@ struct PackHxSide {
 };
 struct PackHxArgs {
   PackHxSide row, col;
-  int64_t ldx, nbr, nbc;
+  int64_t ldx, nbr, nbc, blk0;
   int D, nblk;
   double neg_bl;
   const double* part;  // prologue sums (nblk x D) over nmean points
@@ -405,7 +405,7 @@ template <int RID, int WIDE>
 __global__ __launch_bounds__(PACK_THREADS) void pack_hx_kernel(PackHxArgs a) {
   __shared__ double mu[MAX_D], red[PACK_THREADS];
   __shared__ int ex[64];
-  int64_t blk = blockIdx.x;
+  int64_t blk = a.blk0 + blockIdx.x;
   if (blk == 0 && a.flag != nullptr) pack_flag(a.flags, a.nflags, a.flag);
   if (blk >= a.nbr + a.nbc) {
     pack_v_block(a.v, blk - a.nbr - a.nbc, ex);
@@ -1060,10 +1060,8 @@ void launch_packs_hx(const PackIn& in, const PackV& v, PointPack& rows, PointPac
   a.zero1 = in.zero1;
   a.zero2 = in.zero2;
   a.nzero = in.nzero;
-  const dim3 grid{unsigned(a.nbr + a.nbc + ceil_div(pack_v_items(v), PACK_THREADS))};
   auto go = [&](auto kernel) {
-    hipLaunchKernelGGL(kernel, grid, dim3(PACK_THREADS), 0, stream, a);
-    FD_LAUNCH_CHECK();
+    launch_pack_blocks(kernel, a.nbr + a.nbc + ceil_div(pack_v_items(v), PACK_THREADS), a, stream);
   };
   switch (rid) {
     case 0: return go(pack_hx_kernel<0, -1>);

@@ -103,6 +103,19 @@ __device__ __forceinline__ bool poisoned(const PoisonGate& g) {
 
 constexpr int PACK_THREADS = 128;  // workgroup of the pack kernels
 
+// Launches `blocks` workgroups of a pack kernel.  A launch holds fewer than 2^32
+// threads, and a side of a set takes up to four threads a point, its V eight:
+// beyond 2^31 threads the packs go in slices (args.blk0 is a slice's first block).
+template <class K, class A>
+void launch_pack_blocks(K kernel, int64_t blocks, A args, hipStream_t stream) {
+  constexpr int64_t SLICE = (int64_t(1) << 31) / PACK_THREADS;
+  for (args.blk0 = 0; args.blk0 < blocks; args.blk0 += SLICE) {
+    hipLaunchKernelGGL(kernel, dim3(unsigned(std::min(SLICE, blocks - args.blk0))),
+                       dim3(PACK_THREADS), 0, stream, args);
+    FD_LAUNCH_CHECK();
+  }
+}
+
 // The V part of a pack launch: V (n x b, ldv) times sr, as the split pack of
 // ncb 16-column blocks over npairs pairs of 16-point tiles, or (ncb = 0) as the
 // weight pack of its one column over ntiles tiles; with nvmax that column is
@@ -112,6 +125,7 @@ struct PackV {
   const float* V = nullptr;
   const float* sr = nullptr;
   int64_t n = 0, ldv = 0, npairs = 0, ntiles = 0;
+  int64_t blk0 = 0;
   int b = 0, ncb = 0, nvmax = 0;
   float range = 0.f;             // column_range
   const float* vpart = nullptr;  // nvmax x 64 partial column maxima

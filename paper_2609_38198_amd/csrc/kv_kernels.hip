@@ -445,7 +445,7 @@ __device__ __forceinline__ float exp2_unit(float t) {
 
 __global__ __launch_bounds__(PACK_THREADS) void pack_v_kernel(PackV a) {
   __shared__ int ex[64];
-  pack_v_block(a, blockIdx.x, ex);
+  pack_v_block(a, a.blk0 + blockIdx.x, ex);
 }
 
 // Column-pair operands: exponent-contraction inputs of two 16-point tiles and
@@ -478,7 +478,7 @@ struct PackBf16Side {
 };
 struct PackBf16Args {
   PackBf16Side row, col;
-  int64_t ldx, nbr, nbc;
+  int64_t ldx, nbr, nbc, blk0;
   int D, dc, vec;
   float pad;  // offset of the padding points
   const int* flags;
@@ -490,7 +490,7 @@ struct PackBf16Args {
 };
 __global__ __launch_bounds__(PACK_THREADS) void pack_bf16_kernel(PackBf16Args a) {
   __shared__ int ex[64];
-  int64_t blk = blockIdx.x;
+  int64_t blk = a.blk0 + blockIdx.x;
   if (blk == 0 && a.flag != nullptr) pack_flag(a.flags, a.nflags, a.flag);
   if (blk >= a.nbr + a.nbc) {
     pack_v_block(a.v, blk - a.nbr - a.nbc, ex);
@@ -1258,9 +1258,8 @@ static void launch_packs_bf16(const PackIn& in, const PackV& v, PointPack& rows,
   a.zero1 = in.zero1;
   a.zero2 = in.zero2;
   a.nzero = in.nzero;
-  const int64_t grid = a.nbr + a.nbc + ceil_div(pack_v_items(v), PACK_THREADS);
-  hipLaunchKernelGGL(pack_bf16_kernel, dim3(unsigned(grid)), dim3(PACK_THREADS), 0, stream, a);
-  FD_LAUNCH_CHECK();
+  launch_pack_blocks(pack_bf16_kernel,
+                     a.nbr + a.nbc + ceil_div(pack_v_items(v), PACK_THREADS), a, stream);
 }
 
 // The V part of a pack: the split pack of V[0:n, 0:b] (ncb > 0) or the weight
@@ -1357,9 +1356,7 @@ void launch_pack_v_split(const float* V, int64_t n, int64_t b, int64_t ldv, cons
     launch_prologue(in, none, vscale, stream);
   }
   const PackV v = pack_v_args(V, n, b, ldv, sr, ncb, npad, vp, vscale);
-  hipLaunchKernelGGL(pack_v_kernel, dim3(blocks_for(pack_v_items(v), PACK_THREADS)),
-                     dim3(PACK_THREADS), 0, stream, v);
-  FD_LAUNCH_CHECK();
+  launch_pack_blocks(pack_v_kernel, ceil_div(pack_v_items(v), PACK_THREADS), v, stream);
 }
 
 template <int DC, int NCB, int NIB>

@@ -17,6 +17,7 @@ b = 32 and k = 64.
 """
 import numpy as np
 import pytest
+import torch
 
 from gpu_util import TOL_BF16, TOL_F32, case, device, rel_fro, to_dev, to_np
 from oracle import kernel as ok
@@ -153,3 +154,23 @@ def test_grid_torus_top64_closed_form(counts):
     phi = to_np(e.evecs)
     assert np.abs(phi.T @ phi - np.eye(64)).max() <= 1e-5
 
+
+
+def test_more_pack_threads_than_one_launch_holds():
+    """540 million columns: their packs and that of V take 8 threads a column,
+    more than the 2^32 of a launch.  All points coincide but the last one, far
+    away, so that results are counts (sums of ones, exact in float32 here)."""
+    n = 540_000_001
+    case(f"packs in slices nc={n} bf16 b=1")
+    dev = device()
+    need = fd.fd_workspace_size(fd.FD_OP_KERNEL_MATMUL, 3, n, 1, 1)
+    if torch.cuda.mem_get_info()[0] < need + (16 << 30):
+        pytest.skip("not enough free device memory")
+    xc = torch.zeros(n, 1, dtype=torch.bfloat16, device=dev)
+    xc[-1] = 64.0
+    xr = torch.tensor([[0.0], [64.0], [32.0]], dtype=torch.bfloat16, device=dev)
+    V = torch.ones(n, 1, device=dev)
+    V[-1] = 7.0
+    ws = torch.empty(need, dtype=torch.uint8, device=dev)
+    Y = to_np(fd.fd_kernel_matmul(xr, xc, 1.0, V, ws=ws))[:, 0]
+    assert list(Y) == [n - 1, 7.0, 0.0]
