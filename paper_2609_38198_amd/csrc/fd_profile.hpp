@@ -1,5 +1,7 @@
 // RAII bracket of one kernel launch with HIP events (active only when
-// fd_profile_enable(1) was called).
+// fd_profile_enable(1) was called), or of several that serve as one (variants of
+// which the device runs one): a bracket inside another on the same thread is
+// not counted.
 #pragma once
 
 #include <hip/hip_runtime.h>

@@ -1631,6 +1631,7 @@ void launch_product_column(const KVPlan& p, const PointPack& rows, const PointPa
   check_span(vscale, 64, "column scales");
   SymPass sp;
   if (rowsum_sym_applies(rows, cols, diag, colfix)) {
+    ProfScope prof(FD_KERNEL_ROWSUM, stream);  // one of the two variants runs
     // K is symmetric: each tile off the diagonal blocks once (the whole call on
     // the 6-torus set-up, N = 65,536, D = 32: 762 -> 596 us).  Column sums are
     // fixed point against the column's largest weight, so a NaN, an infinity or

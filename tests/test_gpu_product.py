@@ -312,3 +312,25 @@ def test_uncentred_data_is_centred_inside(shift):
     err = rel_fro(Y[rows], ref)
     print(f"shift {shift}: rel err {err:.2e}")
     assert err <= 3e-6
+
+
+@pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
+@pytest.mark.parametrize("b", [1, 5])
+def test_profile_counts_a_product_once(b, dtype):
+    """Variants of which the device runs one count as one launch: two layouts at
+    D = 20, and for a single column the symmetric and the plain sums too."""
+    case(f"profile counts b={b} {dtype}")
+    n = 1500
+    x = torch.randn(n, 20, generator=torch.Generator().manual_seed(1)).to(dtype).to(device())
+    V = torch.ones(n, b, device=device())
+    fd.fd_profile_enable(True)
+    try:
+        for kind in (fd.FD_KERNEL_PRODUCT, fd.FD_KERNEL_ROWSUM):
+            fd.fd_profile_read(kind)
+        for _ in range(3):
+            fd.fd_kernel_matmul(x, None, 0.1, V)
+        prod, rows = (fd.fd_profile_read(k) for k in (fd.FD_KERNEL_PRODUCT, fd.FD_KERNEL_ROWSUM))
+    finally:
+        fd.fd_profile_enable(False)
+    assert (prod[1], rows[1]) == ((0, 3) if b == 1 else (3, 0))
+    assert prod[0] + rows[0] > 0.0
