@@ -73,7 +73,7 @@ int padded_dim(int64_t D);
 constexpr int MAX_D = 64;
 constexpr int MAX_B = 64;
 
-// Packed operands of one point set, produced by launch_pack_points.
+// Packed operands of one point set, produced by launch_packs.
 // float32 X: xp holds the split float16 exponent chunks ([tiles][chunks][64]
 //   uint4; chunk layout by recipe rid, row or column side).
 // bfloat16 X: xp holds [tiles][dc][64] uint4 of raw bfloat16 features,
@@ -232,7 +232,7 @@ void launch_product_column(const KVPlan& p, const PointPack& rows, const PointPa
                            FSpan vscale, bool diag, const float* sl, float* Y, int64_t ldy,
                            FSpan part, unsigned long long* colfix, unsigned long long* colfix_lo,
                            const PoisonGate& poison, hipStream_t stream);
-// out = K w (wp.p == NULL: w = 1).
+// out = K w.
 void launch_rowsum(const KVPlan& p, const PointPack& rows, const PointPack& cols, FSpan wp,
                    bool diag, float* out, FSpan part, hipStream_t stream);
 // The symmetric path piece by piece (the two normalisation passes fuse their

@@ -43,7 +43,7 @@ void residual_norms(const float* Y, const float* W, int64_t ld, int nc, const do
 // S columns.  Vw: m x m scratch
 // (ld m); norms: 2 doubles of
 // scratch; log: jacobi_log_doubles(m) doubles (enough for every size up to m;
-// the rotation log of the one-workgroup path for m <= 192, the block
+// the rotation log of the one-workgroup path for m <= 56, the block
 // rotations of the block path above) and state: 2 ints of scratch.
 // Synchronises the stream once per sweep (once per few sweeps on the
 // one-workgroup path).  Returns the number of sweeps run.

@@ -705,21 +705,21 @@ struct HxCol {
   floatx4 w;
 };
 
-template <int RID, bool UNIT>
+template <int RID>
 __device__ __forceinline__ void load_hx_col(HxCol<RID>& c, const uintx4* __restrict__ xc,
                                             const floatx4* __restrict__ wp, int64_t jb,
                                             int lane) {
   constexpr int NC = Hx<RID>::nc;
 #pragma unroll
   for (int ch = 0; ch < NC; ++ch) c.xa[ch] = xc[(jb * NC + ch) * 64 + lane];
-  if (!UNIT) c.w = wp[jb * 64 + lane];
+  c.w = wp[jb * 64 + lane];
 }
 
 // One column tile against the wave's NIB row tiles: all exponent chains
 // first (independent chains issue back to back and the exponentials can
-// overlap their tail), then K' = 2^t summed (times the weights) on the vector
-// ALUs.
-template <int RID, int NIB, bool UNIT, bool DIAG>
+// overlap their tail), then K' = 2^t summed times the weights on the vector
+// ALUs (one FMA per entry).
+template <int RID, int NIB, bool DIAG>
 __device__ __forceinline__ void hx_rowsum_tile(const HxCol<RID>& c,
                                                const uintx4 (&br)[NIB][Hx<RID>::nb],
                                                float (&acc)[NIB], int64_t jb, int64_t ib0, int g,
@@ -737,20 +737,16 @@ __device__ __forceinline__ void hx_rowsum_tile(const HxCol<RID>& c,
     float k[4];
 #pragma unroll
     for (int r = 0; r < 4; ++r) k[r] = __builtin_amdgcn_exp2f(t[ib][r]);
-    if (UNIT) {
-      acc[ib] += (k[0] + k[1]) + (k[2] + k[3]);
-    } else {
-      // one FMA per entry: as many vector instructions as the unit-weight sum
 #pragma unroll
-      for (int r = 0; r < 4; ++r) acc[ib] = fmaf(k[r], c.w[r], acc[ib]);
-    }
+    for (int r = 0; r < 4; ++r) acc[ib] = fmaf(k[r], c.w[r], acc[ib]);
   }
 }
 
-// Row sums sum_j K_ij w_j (b = 1, the normalisation passes): the same
-// exponent tiles, reduced on the vector ALUs instead of a second contraction.
+// Row sums sum_j K_ij w_j (single columns, the denominators of a Nystrom
+// extension): the same exponent tiles, reduced on the vector ALUs instead of a
+// second contraction.
 // Column tiles stream through two operand buffers used in turn.
-template <int RID, int NIB, bool UNIT>
+template <int RID, int NIB>
 __global__ __launch_bounds__(WG_THREADS)
 __attribute__((amdgpu_waves_per_eu(hx_plain_waves<RID, NIB>()))) void rowsum_hx_kernel(
     const uintx4* __restrict__ xc, const floatx4* __restrict__ wp, const uintx4* __restrict__ xr,
@@ -779,21 +775,20 @@ __attribute__((amdgpu_waves_per_eu(hx_plain_waves<RID, NIB>()))) void rowsum_hx_
 
   auto step = [&](const HxCol<RID>& c, int64_t jb) {
     if (diag && jb >= ib0 && jb < ib0 + NIB)
-      hx_rowsum_tile<RID, NIB, UNIT, true>(c, br, acc, jb, ib0, g, p);
+      hx_rowsum_tile<RID, NIB, true>(c, br, acc, jb, ib0, g, p);
     else
-      hx_rowsum_tile<RID, NIB, UNIT, false>(c, br, acc, jb, ib0, g, p);
+      hx_rowsum_tile<RID, NIB, false>(c, br, acc, jb, ib0, g, p);
   };
   HxCol<RID> b0, b1;
-  b0.w = b1.w = floatx4{1.f, 1.f, 1.f, 1.f};
-  load_hx_col<RID, UNIT>(b0, xc, wp, jb_begin, lane);
+  load_hx_col<RID>(b0, xc, wp, jb_begin, lane);
   __builtin_amdgcn_sched_barrier(0);  // b0's loads ahead of b1's, as in the loop
-  load_hx_col<RID, UNIT>(b1, xc, wp, min(jb_begin + 1, jb_end - 1), lane);
+  load_hx_col<RID>(b1, xc, wp, min(jb_begin + 1, jb_end - 1), lane);
   int chunk = 0;
   for (int64_t jb = jb_begin; jb < jb_end; jb += 2) {
     step(b0, jb);
-    load_hx_col<RID, UNIT>(b0, xc, wp, min(jb + 2, jb_end - 1), lane);
+    load_hx_col<RID>(b0, xc, wp, min(jb + 2, jb_end - 1), lane);
     if (jb + 1 < jb_end) step(b1, jb + 1);
-    load_hx_col<RID, UNIT>(b1, xc, wp, min(jb + 3, jb_end - 1), lane);
+    load_hx_col<RID>(b1, xc, wp, min(jb + 3, jb_end - 1), lane);
     chunk += 2;
     if (chunk >= CHUNK_TILES) {
       chunk = 0;
@@ -907,32 +902,16 @@ void product_hx_ncb(const KVPlan& p, const PointPack& rows, const PointPack& col
   throw Error{FD_ERR_UNSUPPORTED, "block width above 64"};
 }
 
-template <int RID, int NIB, bool UNIT>
+template <int RID>
 void rowsum_hx_launch(const KVPlan& p, const PointPack& rows, const PointPack& cols,
                       const float* wp, bool diag, float* out, float* part, hipStream_t stream) {
   const unsigned grid = unsigned(p.nrt * p.nsplit);
-  hipLaunchKernelGGL((rowsum_hx_kernel<RID, NIB, UNIT>), dim3(grid), dim3(WG_THREADS), 0, stream,
+  hipLaunchKernelGGL((rowsum_hx_kernel<RID, 8>), dim3(grid), dim3(WG_THREADS), 0, stream,
                      reinterpret_cast<const uintx4*>(cols.xp.p),
                      reinterpret_cast<const floatx4*>(wp),
                      reinterpret_cast<const uintx4*>(rows.xp.p), p.nrt, p.njb, p.jb_per_split,
                      int(diag), out, rows.n, part, rows.npad, gate_of(rows));
   FD_LAUNCH_CHECK();
-}
-
-template <int RID>
-void rowsum_hx_u(const KVPlan& p, const PointPack& rows, const PointPack& cols, const float* wp,
-                 bool diag, float* out, float* part, hipStream_t stream) {
-  if (p.nib == 8) {
-    if (wp == nullptr)
-      rowsum_hx_launch<RID, 8, true>(p, rows, cols, wp, diag, out, part, stream);
-    else
-      rowsum_hx_launch<RID, 8, false>(p, rows, cols, wp, diag, out, part, stream);
-    return;
-  }
-  if (wp == nullptr)
-    rowsum_hx_launch<RID, 4, true>(p, rows, cols, wp, diag, out, part, stream);
-  else
-    rowsum_hx_launch<RID, 4, false>(p, rows, cols, wp, diag, out, part, stream);
 }
 
 template <int RID, int NIB, bool UNIT, bool SQ, bool TWO = false>
@@ -1143,17 +1122,17 @@ void launch_rowsum_sym_hx(const KVPlan& p, const PointPack& rows, const PointPac
 
 void launch_rowsum_hx(const KVPlan& p, const PointPack& rows, const PointPack& cols,
                       const float* wp, bool diag, float* out, float* part, hipStream_t stream) {
-  FD_REQUIRE(p.nib == 4 || p.nib == 8, FD_ERR_INVALID_ARG, "internal: row-sum plan");
+  FD_REQUIRE(p.nib == 8 && wp != nullptr, FD_ERR_INVALID_ARG, "internal: row-sum plan");
   dual_dispatch(rows, cols, FD_KERNEL_ROWSUM, stream, [&](const PointPack& r, const PointPack& c) {
     check_hx(p, r, c);
     switch (r.rid) {
-      case 0: return rowsum_hx_u<0>(p, r, c, wp, diag, out, part, stream);
-      case 1: return rowsum_hx_u<1>(p, r, c, wp, diag, out, part, stream);
-      case 2: return rowsum_hx_u<2>(p, r, c, wp, diag, out, part, stream);
-      case 3: return rowsum_hx_u<3>(p, r, c, wp, diag, out, part, stream);
-      case 4: return rowsum_hx_u<4>(p, r, c, wp, diag, out, part, stream);
-      case 5: return rowsum_hx_u<5>(p, r, c, wp, diag, out, part, stream);
-      case 6: return rowsum_hx_u<6>(p, r, c, wp, diag, out, part, stream);
+      case 0: return rowsum_hx_launch<0>(p, r, c, wp, diag, out, part, stream);
+      case 1: return rowsum_hx_launch<1>(p, r, c, wp, diag, out, part, stream);
+      case 2: return rowsum_hx_launch<2>(p, r, c, wp, diag, out, part, stream);
+      case 3: return rowsum_hx_launch<3>(p, r, c, wp, diag, out, part, stream);
+      case 4: return rowsum_hx_launch<4>(p, r, c, wp, diag, out, part, stream);
+      case 5: return rowsum_hx_launch<5>(p, r, c, wp, diag, out, part, stream);
+      case 6: return rowsum_hx_launch<6>(p, r, c, wp, diag, out, part, stream);
     }
   });
 }

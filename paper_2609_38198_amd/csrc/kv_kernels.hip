@@ -431,7 +431,6 @@ __device__ __forceinline__ float exp2_unit(float t) {
   return __builtin_amdgcn_fmed3f(__builtin_amdgcn_exp2f(t), 0.f, 1.f);
 }
 
-// Column-tile operands of one 16-point tile, per lane.
 // ------------------------------------------------------------------ split V pack
 //
 // The K*V contraction runs in float16 with a two-term split of both factors:
@@ -448,8 +447,6 @@ __global__ __launch_bounds__(PACK_THREADS) void pack_v_kernel(PackV a) {
   pack_v_block(a, a.blk0 + blockIdx.x, ex);
 }
 
-// Column-pair operands: exponent-contraction inputs of two 16-point tiles and
-// the split V pack of the pair.
 // ------------------------------------------------------------------ bfloat16 inputs
 //
 // For X in bfloat16 the exponent contraction runs on v_mfma_f32_16x16x32_bf16:
@@ -821,11 +818,11 @@ __attribute__((amdgpu_waves_per_eu(bf16_waves<DC, NCB, NIB>()))) void product_bf
 
 
 // Row sums for bfloat16 inputs: the same half squared distances, K = 2^t
-// clamped to [0, 1], summed (times the weights) on the vector ALUs.  Two waves
+// clamped to [0, 1], summed times the weights on the vector ALUs.  Two waves
 // per SIMD (every variant fits 256 registers): the matrix instructions then
 // accumulate in VGPRs, with no copies out of accumulation registers (bitwise
 // equal results, 13-17% faster bfloat16 degree passes at D = 30 and 64).
-template <int DC, int NIB, bool UNIT>
+template <int DC, int NIB>
 __global__ __launch_bounds__(WG_THREADS) __attribute__((amdgpu_waves_per_eu(2))) void
 rowsum_bf16_kernel(
     const uintx4* __restrict__ xa, const floatx4* __restrict__ aj, const floatx4* __restrict__ wp,
@@ -860,8 +857,7 @@ rowsum_bf16_kernel(
 #pragma unroll
     for (int c = 0; c < DC; ++c) xar[c] = xa[(jb * DC + c) * 64 + lane];
     const floatx4 ajr = aj[jb * 64 + lane];
-    floatx4 w4 = floatx4{1.f, 1.f, 1.f, 1.f};
-    if (!UNIT) w4 = wp[jb * 64 + lane];
+    const floatx4 w4 = wp[jb * 64 + lane];
     const bool dtile = diag && jb >= ib0 && jb < ib0 + NIB;
 #pragma unroll
     for (int ib = 0; ib < NIB; ++ib) {
@@ -874,7 +870,7 @@ rowsum_bf16_kernel(
 #pragma unroll
       for (int r = 0; r < 4; ++r) {
         const float k = exp2_unit(t[r] * scale2);
-        sum = UNIT ? sum + k : fmaf(k, w4[r], sum);
+        sum = fmaf(k, w4[r], sum);
       }
       acc[ib] += sum;
     }
@@ -1100,9 +1096,8 @@ __global__ __launch_bounds__(256) void degree_finish_kernel(
 }
 
 // The two normalisation passes on the symmetric path with their epilogues in
-// the reductions (same arithmetic, in the same order, as reduce_rowsum_sym +
-// pow_neg + pack_w and reduce_rowsum_sym + degree_finish).  One thread per
-// padded point; each clears its fixed-point column sum for the next pass.
+// the reductions.  One thread per padded point; each clears its fixed-point
+// column sum for the next pass.
 
 // Row sum of point i: the split partials, then the fixed-point column sum.
 __device__ __forceinline__ double sym_row_total(const float* __restrict__ part, int nsplit,
@@ -1453,14 +1448,14 @@ void launch_product(const KVPlan& p, const PointPack& rows, const PointPack& col
   }
 }
 
-template <int DC, int NIB, bool UNIT>
-static void rowsum_bf16_nib(const KVPlan& p, const PointPack& rows, const PointPack& cols,
-                            const float* wp, bool diag, float* out, float* part,
-                            hipStream_t stream) {
+template <int DC>
+static void rowsum_bf16_launch(const KVPlan& p, const PointPack& rows, const PointPack& cols,
+                               const float* wp, bool diag, float* out, float* part,
+                               hipStream_t stream) {
   const unsigned grid = unsigned(p.nrt * p.nsplit);
   const float scale2 = float(2.0 * rows.beta * LOG2E);
   ProfScope prof(FD_KERNEL_ROWSUM, stream);
-  hipLaunchKernelGGL((rowsum_bf16_kernel<DC, NIB, UNIT>), dim3(grid), dim3(WG_THREADS), 0, stream,
+  hipLaunchKernelGGL((rowsum_bf16_kernel<DC, 8>), dim3(grid), dim3(WG_THREADS), 0, stream,
                      reinterpret_cast<const uintx4*>(cols.xp.p),
                      reinterpret_cast<const floatx4*>(cols.ap.p),
                      reinterpret_cast<const floatx4*>(wp),
@@ -1468,17 +1463,6 @@ static void rowsum_bf16_nib(const KVPlan& p, const PointPack& rows, const PointP
                      p.jb_per_split, int(diag), scale2, out, rows.n, part, rows.npad, gate_of(rows));
   FD_LAUNCH_CHECK();
 }
-
-template <int DC, bool UNIT>
-static void rowsum_bf16_launch(const KVPlan& p, const PointPack& rows, const PointPack& cols,
-                               const float* wp, bool diag, float* out, float* part,
-                               hipStream_t stream) {
-  if (p.nib == 8)
-    rowsum_bf16_nib<DC, 8, UNIT>(p, rows, cols, wp, diag, out, part, stream);
-  else
-    rowsum_bf16_nib<DC, 4, UNIT>(p, rows, cols, wp, diag, out, part, stream);
-}
-
 
 bool rowsum_sym_applies(const PointPack& rows, const PointPack& cols, bool diag,
                         const unsigned long long* colfix) {
@@ -1589,18 +1573,13 @@ void launch_degree_reduce_dsq(const SymPass& sp, const PointPack& rows, const Po
 // The plain row-sum kernel: partials into pp, or (pp NULL, one split) out.
 static void launch_rowsum_pass(const KVPlan& p, const PointPack& rows, const PointPack& cols,
                                FSpan wp, bool diag, float* out, float* pp, hipStream_t stream) {
-  FD_REQUIRE(p.nib == 4 || p.nib == 8, FD_ERR_INVALID_ARG, "internal: row-sum plan");
-  if (wp.p != nullptr) check_span(wp, lane4_extent(p.njb, 1), "weight pack");
+  FD_REQUIRE(p.nib == 8, FD_ERR_INVALID_ARG, "internal: row-sum plan");
+  check_span(wp, lane4_extent(p.njb, 1), "weight pack");
   if (rows.bf16 || cols.bf16) {
     FD_REQUIRE(rows.bf16 && cols.bf16 && rows.dc == cols.dc, FD_ERR_INVALID_ARG,
                "internal: mixed pack kinds");
-    const bool unit = wp.p == nullptr;
-    if (rows.dc == 1)
-      unit ? rowsum_bf16_launch<1, true>(p, rows, cols, wp.p, diag, out, pp, stream)
-           : rowsum_bf16_launch<1, false>(p, rows, cols, wp.p, diag, out, pp, stream);
-    else
-      unit ? rowsum_bf16_launch<2, true>(p, rows, cols, wp.p, diag, out, pp, stream)
-           : rowsum_bf16_launch<2, false>(p, rows, cols, wp.p, diag, out, pp, stream);
+    if (rows.dc == 1) rowsum_bf16_launch<1>(p, rows, cols, wp.p, diag, out, pp, stream);
+    else rowsum_bf16_launch<2>(p, rows, cols, wp.p, diag, out, pp, stream);
   } else {
     launch_rowsum_hx(p, rows, cols, wp.p, diag, out, pp, stream);
   }
