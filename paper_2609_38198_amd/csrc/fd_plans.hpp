@@ -40,8 +40,13 @@ struct KVPlan {
 constexpr int SYM_NIB = 8;
 constexpr int64_t SYM_MIN_SPLITS = 16;
 
-// Workgroups of one resident round: products and symmetric row sums hold two
-// waves per SIMD, so 256 CUs take two four-wave workgroups each.
+// Workgroups of one resident round: products and most symmetric row sums hold
+// two waves per SIMD, so 256 CUs take two four-wave workgroups each.  The row
+// sums of float32 points with D > 32 (and D = 31, 32 with squared sums) hold one,
+// so that 512 of their workgroups are two rounds: still better than 2048
+// (fd_degree, 2048 / 512 / 256 workgroups, us: D = 40, N = 5,000 74 / 74 / 62,
+// 9,000 126 / 103 / 93, 16,000 269 / 192 / 176, 24,000 389 / 332 / 319; D = 64,
+// N = 16,000 295 / 205 / 188).
 constexpr int64_t ONE_ROUND = 512;
 
 // `round`: split the columns for one resident round of workgroups (never more
@@ -83,7 +88,9 @@ inline KVPlan plan_tiles(int64_t Nr, int64_t Nc, int dp, int b, int nib, bool ro
 // there than the uneven end of a few long workgroups (2048 workgroups / one
 // round: D = 30, b = 32, N = 8,192 67 / 57, 20,000 173 / 165; 6-torus, b = 32,
 // N = 16,384 115 / 102, b = 16, N = 16,384 95 / 87).  Beyond, the uneven end
-// does (D = 30, b = 32, N = 28,000 289 / 296; b = 16, N = 24,000 182 / 186).
+// does (D = 30, b = 32, N = 28,000 289 / 296; b = 16, N = 24,000 182 / 186).  Both
+// lines are by pairs alone and were measured at b = 16 and 32; partial products
+// grow with b (b = 64, 30,011 x 16,384: 18 splits, 139 MB written and read again).
 constexpr int64_t WIDE_ROWS_PAIRS = int64_t(1) << 28;
 constexpr int64_t ONE_ROUND_PAIRS = int64_t(3) << 27;
 

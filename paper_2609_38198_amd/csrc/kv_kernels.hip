@@ -1612,7 +1612,7 @@ void launch_product_column(const KVPlan& p, const PointPack& rows, const PointPa
   if (rowsum_sym_applies(rows, cols, diag, colfix)) {
     ProfScope prof(FD_KERNEL_ROWSUM, stream);  // one of the two variants runs
     // K is symmetric: each tile off the diagonal blocks once (the whole call on
-    // the 6-torus set-up, N = 65,536, D = 32: 762 -> 596 us).  Column sums are
+    // the 6-torus set-up, N = 65,536, D = 32: 885 -> 590 us).  Column sums are
     // fixed point against the column's largest weight, so a NaN, an infinity or
     // a wide range (zeros among others, column_range) takes the plain sums: both
     // are launched, and the column's flag closes one of them.  (No colfix: a

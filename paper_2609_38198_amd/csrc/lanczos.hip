@@ -217,8 +217,10 @@ struct Lanczos {
     gemm_nn(Z, mm, nb, w.Rinv, nb, w.Zt, nb, N, 1.f, 0.f, st);
     fill_normal(w.Zt, nb, N, nb, w.flags, seed, rng_stream++, st);
     // once more against the basis: the triangular factor has enlarged what the
-    // two passes left by at most the pivot bound (1e4), and replaced columns
-    // are random, so one pass takes both to rounding
+    // two passes left by at most the pivot bound (1e4), and of a replaced
+    // column, which is random, about sqrt((N - m) / N) lies outside the basis, so
+    // one pass takes both to rounding (times sqrt(N / (N - m)) for the latter:
+    // bases close to the whole space are the small dense solves)
     if (m > 0) project_out(w.Zt, nb, nb, m);
     gemm_tn(w.Zt, nb, nb, w.Zt, nb, nb, N, w.part, w.G, nullptr, st);
     chol_rinv(w.G, nb, 1e-4, w.Rinv, w.flags, st);
