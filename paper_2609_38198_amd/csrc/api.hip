@@ -116,7 +116,7 @@ struct ExactVariant {
 static ExactVariant pick_product_exact(int64_t Nr, int64_t Nc, int64_t D, int b, bool one_set,
                                        size_t bytes) {
   ExactVariant v;
-  for (int sym = b == 1 && one_set && Nr == Nc; sym >= 0; --sym)
+  for (int sym = b == 1 && one_set && Nr == Nc && Nr >= COLUMN_SYM_POINTS; sym >= 0; --sym)
     for (int cap : {PROLOGUE_CAP, 128, 32, 8}) {
       Arena m;
       m.measuring = true;
@@ -198,7 +198,8 @@ static void product_run(ProductWs& w, const float* sl, int b, float* Y, int64_t 
 void product_apply(ProductWs& w, const float* sl, const float* sr, const float* V, int64_t ldv,
                    int b, float* Y, int64_t ldy, bool diag, hipStream_t stream) {
   launch_pack_v_split(V, w.cols.n, b, ldv, sr, b == 1 ? 0 : w.plan.ncb, w.cols.npad, w.vp,
-                      w.vscale, stream);
+                      w.vscale, stream,
+                      b > 1 || column_sym_applies(w.rows, w.cols, diag, w.colfix));
   product_run(w, sl, b, Y, ldy, diag, PoisonGate{}, stream);
 }
 
@@ -220,7 +221,8 @@ static void matmul_run(ProductWs& w, const void* Xr, const void* Xc, int64_t D, 
     pro.X2 = Xr;
     pro.n2 = w.rows.n;
   }
-  pro.V = V;
+  const bool scaled = b > 1 || column_sym_applies(w.rows, w.cols, diag, w.colfix);
+  pro.V = scaled ? V : nullptr;
   pro.nv = w.cols.n;
   pro.b = b;
   pro.ldv = ldv;
@@ -243,6 +245,7 @@ static void matmul_run(ProductWs& w, const void* Xr, const void* Xc, int64_t D, 
   in.vp = w.vp;
   in.vscale = w.vscale;
   in.cap = w.cap;
+  in.scaled = scaled;
   in.zero1 = w.colfix;
   in.zero2 = w.colfix_lo;
   in.nzero = w.colfix != nullptr ? w.rows.npad : 0;

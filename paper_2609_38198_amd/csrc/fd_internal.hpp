@@ -208,6 +208,7 @@ struct PackIn {
   int ncb = 0;
   FSpan vp, vscale;
   int cap = PROLOGUE_CAP;  // the prologue's
+  bool scaled = true;      // the prologue left V's maxima (else the weight pack is of V itself)
   unsigned long long *zero1 = nullptr, *zero2 = nullptr;
   int64_t nzero = 0;
 };
@@ -219,7 +220,8 @@ void launch_pack_w(const float* w, int64_t n, int64_t npad, FSpan wp, hipStream_
 // 64 column maxima where the prologue finishes them, then its partial maxima.
 size_t vscale_floats(int64_t n, int cap = PROLOGUE_CAP);
 void launch_pack_v_split(const float* V, int64_t n, int64_t b, int64_t ldv, const float* sr,
-                         int ncb, int64_t npad, FSpan vp, FSpan vscale, hipStream_t stream);
+                         int ncb, int64_t npad, FSpan vp, FSpan vscale, hipStream_t stream,
+                         bool scaled = true);
 // Y = diag(sl) K diag(sr) V from packed operands (V packed with sr applied).
 void launch_product(const KVPlan& p, const PointPack& rows, const PointPack& cols, FSpan vp,
                     FSpan vscale, bool diag, const float* sl, float* Y, int64_t ldy, int b,
@@ -227,7 +229,8 @@ void launch_product(const KVPlan& p, const PointPack& rows, const PointPack& col
 // Y[:, 0] = diag(sl) K diag(sr) v for one column from its weight pack: on one
 // point set (colfix, colfix_lo set: npad cleared words each, left cleared) the
 // symmetric row sums, or the plain ones where the column holds a NaN or an
-// infinity or spans more than column_range; else the plain ones.
+// infinity or spans more than column_range; else the plain ones.  The weight
+// pack is a scaled one where column_sym_applies.
 void launch_product_column(const KVPlan& p, const PointPack& rows, const PointPack& cols, FSpan wp,
                            FSpan vscale, bool diag, const float* sl, float* Y, int64_t ldy,
                            FSpan part, unsigned long long* colfix, unsigned long long* colfix_lo,
@@ -261,6 +264,9 @@ struct SymSquares {
   float* part = nullptr;
   unsigned long long* colfix = nullptr;
 };
+// Whether a single-column product takes them.
+bool column_sym_applies(const PointPack& rows, const PointPack& cols, bool diag,
+                        const unsigned long long* colfix);
 bool rowsum_sym_applies(const PointPack& rows, const PointPack& cols, bool diag,
                         const unsigned long long* colfix);
 // sq_part / sq_colfix (weighted passes only): also the squared-kernel sums, whose

@@ -165,6 +165,15 @@ inline size_t sym_part_rows_within(int64_t npad, int nib) {
   return need;
 }
 
+// Points from which a single-column product on one point set takes the symmetric
+// row sums.  Below, a call is its launches: the plain sums need neither the
+// column's maxima nor the second variant of the pass (symmetric / plain, us:
+// D = 4 N = 2,048 22 / 19, 5,000 27 / 24; D = 64 N = 6,000 57 / 52, 8,000 66 / 74,
+// 16,000 121 / 179; bfloat16, D = 12 N = 6,000 29 / 25, 8,000 33 / 34, 16,000
+// 60 / 70; all 700 eigenpairs of 700 points with b = 1 28.8 / 24.6 ms).  At
+// D = 4 in float32 the plain sums stay 3-9% ahead to N = 24,000.
+constexpr int64_t COLUMN_SYM_POINTS = 6144;
+
 // Column sums of a single-column product over the symmetric row sums.  A wave's
 // contribution (weights below 1, 128 rows) is rounded to WIDE_FRAC fractional
 // bits; a workgroup adds at most four of them to a column (below 2^9, so that

@@ -119,7 +119,7 @@ void launch_pack_blocks(K kernel, int64_t blocks, A args, hipStream_t stream) {
 // The V part of a pack launch: V (n x b, ldv) times sr, as the split pack of
 // ncb 16-column blocks over npairs pairs of 16-point tiles, or (ncb = 0) as the
 // weight pack of its one column over ntiles tiles; with nvmax that column is
-// scaled by 2^-e to below 1 (colscale[0] = e, colscale[1] = 1 where it holds a
+// scaled by 2^-e to below 1 (colscale[0] = e or 0, colscale[1] = 1 where it holds a
 // NaN or an infinity or spans more than `range`, else 0).
 struct PackV {
   const float* V = nullptr;
@@ -151,8 +151,9 @@ __device__ __forceinline__ void pack_v_block(const PackV& a, int64_t blk, int* e
   const int g = lane >> 4, p = lane & 15;
   if (a.ncb == 0) {
     int ex1 = 0;
+    float bad = 0.f;
     if (a.nvmax > 0) {
-      float m = 0.f, bad = 0.f, mn = __builtin_inff();
+      float m = 0.f, mn = __builtin_inff();
       for (int k = lane; k < a.nvmax; k += 64) {
         m = fmaxf(m, a.vpart[k * 64]);
         bad = fmaxf(bad, a.vpart[k * 64 + 1]);
@@ -165,10 +166,10 @@ __device__ __forceinline__ void pack_v_block(const PackV& a, int64_t blk, int* e
       }
       if (mn * a.range < m) bad = 1.f;
       ex1 = bad != 0.f ? 0 : 14 - vscale_exponent(m);
-      if (idx == 0) {
-        a.colscale[0] = float(ex1);
-        a.colscale[1] = bad;
-      }
+    }
+    if (idx == 0) {
+      a.colscale[0] = float(ex1);
+      a.colscale[1] = bad;
     }
     if (idx >= a.ntiles * 64) return;
     floatx4 out;

@@ -1260,8 +1260,7 @@ static void launch_packs_bf16(const PackIn& in, const PackV& v, PointPack& rows,
 // The V part of a pack: the split pack of V[0:n, 0:b] (ncb > 0) or the weight
 // pack of its one column (ncb = 0) for a column side of npad points.
 static PackV pack_v_args(const float* V, int64_t n, int64_t b, int64_t ldv, const float* sr,
-                         int ncb, int64_t npad, FSpan vp, FSpan vscale,
-                         int cap = PROLOGUE_CAP) {
+                         int ncb, int64_t npad, FSpan vp, FSpan vscale, int cap, bool scaled) {
   PackV v;
   if (V == nullptr) return v;
   check_span(vscale, vscale_floats(n, cap), "column scales");
@@ -1277,6 +1276,8 @@ static PackV pack_v_args(const float* V, int64_t n, int64_t b, int64_t ldv, cons
   v.ldv = ldv;
   v.b = int(b);
   v.ncb = ncb;
+  if (!scaled) v.nvmax = 0;
+  FD_REQUIRE(scaled || ncb == 0, FD_ERR_INVALID_ARG, "internal: split V pack without maxima");
   if (ncb == 0) {
     FD_REQUIRE(npad % TILE == 0 && npad >= n && b == 1, FD_ERR_INVALID_ARG,
                "internal: bad w pack geometry");
@@ -1298,7 +1299,7 @@ void launch_packs(const PackIn& in, PointPack& rows, PointPack& cols, const Cent
                   hipStream_t stream) {
   rows.beta = cols.beta = in.beta;
   const PackV v = pack_v_args(in.V, cols.n, in.b, in.ldv, in.sr, in.ncb, cols.npad, in.vp,
-                              in.vscale, in.cap);
+                              in.vscale, in.cap, in.scaled);
   if (in.xt == FD_BF16) {
     launch_packs_bf16(in, v, rows, cols, centre, stream);
     return;
@@ -1339,8 +1340,9 @@ static void check_tiles(const KVPlan& p, const PointPack& rows, const PointPack&
 }
 
 void launch_pack_v_split(const float* V, int64_t n, int64_t b, int64_t ldv, const float* sr,
-                         int ncb, int64_t npad, FSpan vp, FSpan vscale, hipStream_t stream) {
-  {
+                         int ncb, int64_t npad, FSpan vp, FSpan vscale, hipStream_t stream,
+                         bool scaled) {
+  if (scaled) {
     PrologueIn in;
     in.V = V;
     in.nv = n;
@@ -1350,7 +1352,7 @@ void launch_pack_v_split(const float* V, int64_t n, int64_t b, int64_t ldv, cons
     CentreWs none;
     launch_prologue(in, none, vscale, stream);
   }
-  const PackV v = pack_v_args(V, n, b, ldv, sr, ncb, npad, vp, vscale);
+  const PackV v = pack_v_args(V, n, b, ldv, sr, ncb, npad, vp, vscale, PROLOGUE_CAP, scaled);
   launch_pack_blocks(pack_v_kernel, ceil_div(pack_v_items(v), PACK_THREADS), v, stream);
 }
 
@@ -1462,6 +1464,11 @@ static void rowsum_bf16_launch(const KVPlan& p, const PointPack& rows, const Poi
                      reinterpret_cast<const uintx4*>(rows.xp.p), rows.ar.p, p.nrt, p.njb,
                      p.jb_per_split, int(diag), scale2, out, rows.n, part, rows.npad, gate_of(rows));
   FD_LAUNCH_CHECK();
+}
+
+bool column_sym_applies(const PointPack& rows, const PointPack& cols, bool diag,
+                        const unsigned long long* colfix) {
+  return rowsum_sym_applies(rows, cols, diag, colfix) && rows.n >= COLUMN_SYM_POINTS;
 }
 
 bool rowsum_sym_applies(const PointPack& rows, const PointPack& cols, bool diag,
@@ -1609,7 +1616,7 @@ void launch_product_column(const KVPlan& p, const PointPack& rows, const PointPa
   check_span(part, size_t(p.nsplit) * rows.npad, "partial row sums");
   check_span(vscale, 64, "column scales");
   SymPass sp;
-  if (rowsum_sym_applies(rows, cols, diag, colfix)) {
+  if (column_sym_applies(rows, cols, diag, colfix)) {
     ProfScope prof(FD_KERNEL_ROWSUM, stream);  // one of the two variants runs
     // K is symmetric: each tile off the diagonal blocks once (the whole call on
     // the 6-torus set-up, N = 65,536, D = 32: 885 -> 590 us).  Column sums are

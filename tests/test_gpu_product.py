@@ -320,7 +320,7 @@ def test_profile_counts_a_product_once(b, dtype):
     """Variants of which the device runs one count as one launch: two layouts at
     D = 20, and for a single column the symmetric and the plain sums too."""
     case(f"profile counts b={b} {dtype}")
-    n = 1500
+    n = 7000
     x = torch.randn(n, 20, generator=torch.Generator().manual_seed(1)).to(dtype).to(device())
     V = torch.ones(n, b, device=device())
     fd.fd_profile_enable(True)

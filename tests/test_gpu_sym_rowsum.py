@@ -60,7 +60,7 @@ def test_bfloat16_normalisation_with_whole_block_splits_and_dyadic_levels():
         assert rel_fro(to_np(lev.d)[l][rows], dd) <= TOL_F32
 
 
-@pytest.mark.parametrize("n", [700, 2048])
+@pytest.mark.parametrize("n", [700, 2048, 6800])
 @pytest.mark.parametrize("beta", [37.0, 1234.5, 7.7e4])
 def test_bfloat16_points_that_coincide_far_from_the_origin(n, beta):
     """64 places on a grid of 4 (norms up to 1e4, exact in float32) at beta |x|^2
@@ -79,7 +79,11 @@ def test_bfloat16_points_that_coincide_far_from_the_origin(n, beta):
     assert np.array_equal(to_np(Y)[:, 0], count)
 
 
-@pytest.mark.parametrize("n, d", SIZES + [(40001, 12)])
+# a single column takes the symmetric sums from 6,144 points on
+COLUMN_SIZES = [(6143, 12), (6144, 40), (6145, 3), (6657, 64), (7001, 30), (40001, 12)]
+
+
+@pytest.mark.parametrize("n, d", SIZES + COLUMN_SIZES)
 @pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
 def test_one_column(n, d, dtype):
     case(f"one column n={n} d={d} {dtype}")
@@ -108,7 +112,7 @@ def test_one_column(n, d, dtype):
     assert torch.equal(Y, fd.fd_kernel_matmul(x, None, beta, V, sl=SL, sr=SR))
 
 
-@pytest.mark.parametrize("n", [513, 5000])
+@pytest.mark.parametrize("n", [513, 5000, 7000])
 @pytest.mark.parametrize("kind", ["one point", "decaying", "normal"])
 def test_one_column_keeps_small_results(n, kind):
     """Each result by itself: sums far below the column's largest value too.
@@ -158,9 +162,9 @@ def test_one_column_near_the_widest_span(n, span):
     assert (np.abs(Y[rows] - ref) <= 1e-5 * ref).all()
 
 
-def test_one_column_eigensolve_matches_a_wider_one():
-    """Block width 1 runs its products as single columns."""
-    n = 1500
+@pytest.mark.parametrize("n", [300, 1500, 6500])
+def test_one_column_eigensolve_matches_a_wider_one(n):
+    """Block width 1 runs its products as single columns (300: in the full space)."""
     case("eigensolve with one column per block")
     x, _ = _points(n, 3, torch.float32)
     a = fd.fd_block_lanczos(x, 0.5, 2, 1)
