@@ -26,6 +26,10 @@ constexpr int64_t SPLIT_SPAN_TILES = 4096;
 inline int64_t round_up(int64_t x, int64_t m) { return (x + m - 1) / m * m; }
 inline int64_t ceil_div(int64_t x, int64_t m) { return (x + m - 1) / m; }
 
+// Column tiles per partial accumulator: the sums over a longer range go to a
+// running total (float32).
+constexpr int CHUNK_TILES = 64;
+
 // Plan of one fused product / degree launch.
 struct KVPlan {
   int dp = 0, ncb = 0, nib = 0;
@@ -33,6 +37,7 @@ struct KVPlan {
   int64_t nrt = 0;        // row tiles of 64*nib
   int nsplit = 1;         // column splits
   int64_t jb_per_split = 0;
+  int chunk = CHUNK_TILES;  // column tiles per partial accumulator (float32 products)
 };
 
 // Row tiles per wave of the symmetric row sums, and the fewest column splits
@@ -70,6 +75,14 @@ inline KVPlan plan_tiles(int64_t Nr, int64_t Nc, int dp, int b, int nib, bool ro
   // splits hold an even number of column tiles (the split product takes them in pairs)
   p.jb_per_split = round_up(ceil_div(p.njb, ns), 2);
   p.nsplit = int(ceil_div(p.njb, p.jb_per_split));
+  // the long ranges of one round would also be longer chains of float32 sums than
+  // those of 2048 workgroups, whose ranges were added in float64: shorter chunks
+  // keep the error (against float64, 2048 workgroups / one round with 64, 16, 8
+  // tiles, 1e-7: N = 16,000, D = 12, b = 32 8.12 / 8.56, 7.93, 7.83; N = 8,000,
+  // D = 30, b = 32 9.33 / 9.56, 9.40, 9.32) for 2% of the time (with 64 tiles / as
+  // here, us: N = 16,384, D = 12, b = 32 99 / 101, b = 64 141 / 144; N = 8,192,
+  // D = 30, b = 32 54.2 / 55.2)
+  if (round) p.chunk = p.jb_per_split <= 32 ? 8 : 16;
   return p;
 }
 

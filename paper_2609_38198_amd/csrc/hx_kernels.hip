@@ -581,7 +581,7 @@ template <int RID, int NCB, int NIB>
 __global__ __launch_bounds__(WG_THREADS)
 __attribute__((amdgpu_waves_per_eu(2))) void product_hx_kernel(
     const uintx4* __restrict__ xc, const VSplit* __restrict__ vp, const uintx4* __restrict__ xr,
-    int64_t nrt, int64_t njp, int64_t jp_per_split, int diag, float m1,
+    int64_t nrt, int64_t njp, int64_t jp_per_split, int diag, int chunk_pairs, float m1,
     const float* __restrict__ colscale, const float* __restrict__ sl, float* __restrict__ Y,
     int64_t ldy, int64_t Nr, int b, float* __restrict__ part, int64_t nrpad, HxGate gate,
     PoisonGate poison) {
@@ -614,11 +614,14 @@ __attribute__((amdgpu_waves_per_eu(2))) void product_hx_kernel(
       tot[wave][ib][cb][lane] = floatx4{0.f, 0.f, 0.f, 0.f};
     }
 
-  int chunk = 0;
+  // counted from where chunk_pairs steps are left to the usual length: with the
+  // length itself as the bound the loops came out 2-3% slower
+  const int chunk0 = CHUNK_TILES / 2 - chunk_pairs;
+  int chunk = chunk0;
   auto fold = [&](int pairs) {
     chunk += pairs;
     if (chunk < CHUNK_TILES / 2) return;
-    chunk = 0;
+    chunk = chunk0;
 #pragma unroll
     for (int ib = 0; ib < NIB; ++ib)
 #pragma unroll
@@ -868,7 +871,7 @@ void product_hx_launch(const KVPlan& p, const PointPack& rows, const PointPack& 
                      reinterpret_cast<const uintx4*>(cols.xp.p),
                      reinterpret_cast<const VSplit*>(vp),
                      reinterpret_cast<const uintx4*>(rows.xp.p), p.nrt, ceil_div(p.njb, 2),
-                     p.jb_per_split / 2, int(diag), -1.0f, colscale, sl, Y, ldy, rows.n, b, part,
+                     p.jb_per_split / 2, int(diag), p.chunk / 2, -1.0f, colscale, sl, Y, ldy, rows.n, b, part,
                      rows.npad, gate_of(rows), poison);
   FD_LAUNCH_CHECK();
 }

@@ -16,7 +16,6 @@ typedef float floatx2 __attribute__((ext_vector_type(2)));
 typedef _Float16 halfx2 __attribute__((ext_vector_type(2)));
 
 constexpr double LOG2E = 1.4426950408889634073599;
-constexpr int CHUNK_TILES = 64;  // column tiles per partial accumulator
 
 // Which of the two layouts of a float32 pack a launch serves (PointPack):
 // every launch of such a pair reads the same device word, and the one whose

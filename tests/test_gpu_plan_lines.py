@@ -55,3 +55,33 @@ def test_row_sums_at_the_lines(n, dtype):
     w = to_np(deg.q) ** -0.5
     dd = w[rows] * ok.kernel_matmul(x64[rows], x64, beta, w[:, None])[:, 0]
     assert rel_fro(to_np(deg.d)[rows], dd) <= TOL_F32
+
+
+def _square_error(n, d, b, seed):
+    """Relative Frobenius error of a square product against float64 (all rows)."""
+    g = torch.Generator(device=device()).manual_seed(seed)
+    x = torch.randn(n, d, generator=g, device=device()) * 0.3
+    V = torch.randn(n, b, generator=g, device=device())
+    beta = float(np.float32(4.0 / d))
+    Y = fd.fd_kernel_matmul(x, None, beta, V).double()
+    xd, num, den = x.double(), 0.0, 0.0
+    r, xt = xd.square().sum(1), xd.T.contiguous()
+    for i in range(0, n, 2000):
+        a = xd[i:i + 2000]
+        h = (r + a.square().sum(1, keepdim=True) - 2 * a @ xt).clamp_(min=0)
+        m = torch.arange(len(a), device=device())
+        h[m, m + i] = 0
+        ref = (-beta * h).exp() @ V.double()
+        num += float((Y[i:i + 2000] - ref).square().sum())
+        den += float(ref.square().sum())
+    return (num / den) ** 0.5
+
+
+@pytest.mark.parametrize("n, d, b, bound", [(5000, 12, 16, 7.48e-7), (8000, 30, 32, 9.38e-7),
+                                            (16000, 12, 32, 8.16e-7), (16000, 30, 16, 9.79e-7)])
+def test_one_round_keeps_the_error_of_many_splits(n, d, b, bound):
+    """Mean over six seeds of inputs, which are the same everywhere and so are the
+    bits of the product; `bound` is the mean with the columns split for 2,048
+    workgroups (7.451, 9.334, 8.122 and 9.738e-7) and half a percent."""
+    case(f"one-round error n={n} d={d} b={b}")
+    assert np.mean([_square_error(n, d, b, seed) for seed in range(6)]) <= bound
