@@ -66,7 +66,6 @@ PointPack carve_pack(Arena& a, int64_t n, int dp, int64_t pad) {
 // and 101 us at 65,536 x 32), four rows in flight per lane, and every
 // workgroup leaves its partial result for the consumer to add, so that nothing
 // has to be cleared beforehand.
-
 //
 // For a large set the bandwidth counts after all: up to 1024 workgroups, and a
 // second launch (prologue_finish_kernel) that adds their results once, where
