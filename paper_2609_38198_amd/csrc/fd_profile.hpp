@@ -20,6 +20,10 @@ class ProfScope {
   ProfScope& operator=(const ProfScope&) = delete;
 
  private:
+  struct Depth {  // a member of its own: undone also where the constructor throws
+    Depth();
+    ~Depth();
+  } depth_;
   hipStream_t stream_;
   hipEvent_t start_ = nullptr;
   hipEvent_t stop_ = nullptr;

@@ -23,8 +23,11 @@ constexpr size_t MAX_EVENTS = 1 << 16;
 thread_local int depth = 0;  // open brackets of this thread
 }  // namespace
 
+ProfScope::Depth::Depth() { ++depth; }
+ProfScope::Depth::~Depth() { --depth; }
+
 ProfScope::ProfScope(int kind, hipStream_t s) : stream_(s) {
-  if (depth++ > 0) return;
+  if (depth > 1) return;
   Pool& p = pool();
   std::lock_guard<std::mutex> g(p.m);
   if (!p.on || kind < 0 || kind >= FD_KERNEL_KINDS) return;
@@ -47,7 +50,6 @@ ProfScope::ProfScope(int kind, hipStream_t s) : stream_(s) {
 }
 
 ProfScope::~ProfScope() {
-  --depth;
   if (stop_ != nullptr) (void)hipEventRecord(stop_, stream_);
 }
 
